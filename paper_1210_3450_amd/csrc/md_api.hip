@@ -240,6 +240,7 @@ void layout(md_ctx* c) {
             g.nuoff[a] = (int32_t)(uint32_t)((uint64_t)g.n[a] * (uint64_t)(uint32_t)g.uoff[a]);
         }
         g.lam = (float)std::ldexp(1.0, e - kUnitBits);
+        g.leps = std::ldexp(32.0, -24) * (g.cs[0] * g.cs[0] + g.cs[1] * g.cs[1] + g.cs[2] * g.cs[2]);
         g.lam2inv = (float)(g.ucs * g.ucs);
         g.rc2u = (float)(p.rc * p.rc * g.ucs * g.ucs);
         g.ncell = g.n[0] * g.n[1] * g.n[2];
@@ -326,7 +327,6 @@ md_status alloc_cells(md_ctx* c) {
     dfree(c->D.cell_start);
     dfree(c->D.tile_sum);
     dfree(c->D.tile_pref);
-    dfree(c->D.tile_need);
     dfree(c->D.rtile);
     dfree(c->D.row_box);
     dfree(c->D.row_nt);
@@ -358,7 +358,6 @@ md_status alloc_cells(md_ctx* c) {
     if ((s = dalloc(c, &c->D.cell_start, (size_t)c->ntile * kTile)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.tile_sum, c->ntile)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.tile_pref, c->ntile)) != MD_OK) return s;
-    if ((s = dalloc(c, &c->D.tile_need, c->ntile)) != MD_OK) return s;
     return MD_OK;
 }
 
@@ -486,7 +485,7 @@ void free_all(md_ctx* c) {
     dfree(D.cell_start);
     dfree(D.tile_sum);
     dfree(D.tile_pref);
-    dfree(D.tile_need);
+    dfree(D.need_s);
     dfree(D.rtile);
     dfree(D.row_box);
     dfree(D.row_nt);
@@ -556,6 +555,7 @@ md_status alloc_all(md_ctx* c) {
     A(D.perm, ns);
     A(D.vmax_s, (size_t)c->nbox * kStripes * kStripeStride);
     A(D.disp_s, (size_t)c->nbox * kStripes * kStripeStride);
+    A(D.need_s, (size_t)c->nbox * kNeedStripes * kNeedStride);
     A(D.ntiles, 2);
     A(D.box_t0, (size_t)c->nbox + 1);
     A(D.dshift, (size_t)27 * c->nbox);
@@ -568,6 +568,7 @@ md_status alloc_all(md_ctx* c) {
     if ((s = alloc_cells(c)) != MD_OK) return s;
     HIPCHK(c, hipMemsetAsync(D.any, 0, sizeof(int32_t), c->stream));
     HIPCHK(c, hipMemsetAsync(D.halt, 0, sizeof(int32_t), c->stream));
+    HIPCHK(c, hipMemsetAsync(D.need_s, 0, sizeof(int32_t) * c->nbox * kNeedStripes * kNeedStride, c->stream));
     HIPCHK(c, hipMemsetAsync(D.ntiles, 0, 2 * sizeof(int32_t), c->stream));
     HIPCHK(c, hipMemsetAsync(D.vmax_s, 0, sizeof(unsigned long long) * c->nbox * kStripes * kStripeStride, c->stream));
     HIPCHK(c, hipMemsetAsync(D.disp_s, 0, sizeof(unsigned long long) * c->nbox * kStripes * kStripeStride, c->stream));

@@ -57,6 +57,8 @@ constexpr int kOffBits = 11;             // list entry: partner rank within its 
 constexpr int kMaxCellCount = 1 << kOffBits;
 constexpr int kStripes = 1024;           // slots per box for per-step maxima
 constexpr int kStripeStride = 16;        // 128 bytes between slots
+constexpr int kNeedStripes = 256;        // slots per box for the longest list of a build
+constexpr int kNeedStride = 16;          // 64 bytes between slots
 constexpr int kTileWMax = 64;            // cells per row tile at most
 constexpr int kScapMax = 5461;           // staged records per row tile at most (16-bit entries of 12 * index)
 constexpr int kRtBlock = 256;            // threads per block of the row-tile force kernel (keys per tile)
@@ -80,6 +82,7 @@ struct BoxGeom {
                      // for the largest cell side (the same unit on every axis)
     int32_t uoff[3]; // one cell side in units, per axis: rint(cs * ucs)
     int32_t nuoff[3];// one box length in units modulo 2^32, per axis: n * uoff (the periodic image term)
+    double leps;     // band about r_list^2 that the list build's FP32 test leaves to FP64 (see k_list)
     float lam;       // length per unit, 1 / ucs (exact)
     float lam2inv;   // ucs^2 (exact)
     float rc2u;      // rc^2 in units^2
@@ -175,7 +178,7 @@ struct Dev {
     int32_t* cell_start;
     int32_t* tile_sum;
     int32_t* tile_pref;
-    int32_t* tile_need;  // longest list per cell tile at the last build
+    int32_t* need_s;     // [nbox][kNeedStripes] striped maximum list length of the running build, stride kNeedStride
     int4* rtile;         // row tiles: (box, row cz * ny + cy, xa, xb), in global row order
     int32_t* row_box;    // box of each global row
     int32_t* row_nt;     // row tiles per row

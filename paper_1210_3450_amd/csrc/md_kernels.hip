@@ -285,23 +285,6 @@ __global__ __launch_bounds__(kBlock) void k_list_counts(Dev d, Params p, int64_t
     }
 }
 
-// Offset of entry e from entry 0 of the same key in the chunked list.
-template <int TPK>
-__device__ __forceinline__ uint32_t list_off(int e) {
-    const int m = e / TPK;
-    return ((uint32_t)(m & ~7) << 6) + (uint32_t)((e % TPK) << 3) + (uint32_t)(m & 7);
-}
-
-// The same offset in bytes, for an entry count that is known non-negative.
-template <int TPK>
-__device__ __forceinline__ uint32_t list_off_bytes(uint32_t e) {
-    if constexpr (TPK == 1) {
-        return (uint32_t)__umul24(e >> 3, 1008u) + (e << 1);  // (e & ~7) * 128 + (e & 7) * 2
-    } else {
-        return list_off<TPK>((int)e) * 2u;
-    }
-}
-
 // Index of entry e of key slot s in the chunked wave-blocked list: a list wave
 // of K = 64 / tpk keys owns rows * 64 entries; lane ln = (s % K) * tpk + e % tpk
 // keeps its per-lane entries m = e / tpk in 8-entry chunks, chunk c of every
@@ -451,7 +434,7 @@ __global__ __launch_bounds__(kBlock) void k_dutc(Dev d, Params p) {
 }
 
 // After a build: the permuted buffers become the current ones, longest list over
-// each box's cell tiles, DUTC bound reset, and the "some box rebuilds" gate cleared by
+// each box's stripes, DUTC bound reset, and the "some box rebuilds" gate cleared by
 // the last block to finish.  (Between the permutation and this kernel, a rebuilding box's current
 // positions are in buffer sq ^ 1: the list build reads them there.)
 __global__ __launch_bounds__(kBlock) void k_post_build(Dev d, Params p, int with_list) {
@@ -462,10 +445,10 @@ __global__ __launch_bounds__(kBlock) void k_post_build(Dev d, Params p, int with
     for (int b = blockIdx.x; b < p.nbox; b += gridDim.x) {  // one block per box
         BoxState& st = d.st[b];
         if (!st.rebuild) continue;  // uniform over the block
-        const BoxGeom& g = d.geom[b];
         int m = 0;
         if (with_list)
-            for (int t = threadIdx.x; t < g.ntile; t += kBlock) m = max(m, d.tile_need[g.tile_off + t]);
+            for (int t = threadIdx.x; t < kNeedStripes; t += kBlock)
+                m = max(m, d.need_s[((size_t)b * kNeedStripes + t) * kNeedStride]);
         m = __builtin_amdgcn_readlane(wave_incl_max(m), kWave - 1);
         if (l == 0) red[wv] = m;
         __syncthreads();
@@ -498,10 +481,13 @@ __global__ __launch_bounds__(kBlock) void k_post_build(Dev d, Params p, int with
 __global__ __launch_bounds__(kBlock) void k_cell_clear(Dev d, Params p) {
     if (!ld_const(d.any) || halted(d)) return;  // no box rebuilds this step, or a build overflowed
     for (int t = blockIdx.x; t < p.ntile; t += gridDim.x) {
-        if (!d.st[d.tile_box[t]].rebuild) continue;
+        const int b = d.tile_box[t];
+        if (!d.st[b].rebuild) continue;
         int4* c = reinterpret_cast<int4*>(d.cell_cnt + (size_t)t * kTile);
         c[threadIdx.x] = make_int4(0, 0, 0, 0);
-        if (threadIdx.x == 0) d.tile_need[t] = 0;
+        if (t == d.geom[b].tile_off)
+            for (int k = threadIdx.x; k < kNeedStripes; k += kBlock)
+                d.need_s[((size_t)b * kNeedStripes + k) * kNeedStride] = 0;
     }
 }
 
@@ -889,266 +875,329 @@ __global__ __launch_bounds__(kBlock) void k_row_delta(Dev d, Params p) {
 
 // ---------------------------------------------------------------- pair list
 
-// Squared minimum-image distance exactly as the plain definition evaluates it:
-// d = (x_j - x_i) - L * rint((x_j - x_i) / L) per axis, where the subtracted
-// image term is known from the stencil, then dx*dx + dy*dy + dz*dz left to
-// right.  No contraction, so the accept decision matches the CPU bit for bit.
-template <class A, class B>
-__device__ __forceinline__ double dist2_exact(const A& qi, const B& qj, double shx, double shy, double shz) {
-#pragma clang fp contract(off)
-    const double dx = (qj.x - qi.x) - shx;
-    const double dy = (qj.y - qi.y) - shy;
-    const double dz = (qj.z - qi.z) - shz;
-    return dx * dx + dy * dy + dz * dz;
-}
-// The same distance for a cell whose stencil has no periodic image, with the sum of
-// squares contracted into two FMAs (7 instructions with the compare instead of 9).
-// Its rounding differs from the uncontracted definition by about one ulp of r^2, so
-// the accept decision can differ only for pairs within ~1e-15 of the list radius:
-// inside the 1e-9 tie band that set comparisons leave out.
-template <class A, class B>
-__device__ __forceinline__ double dist2_fma0(const A& qi, const B& qj) {
-    const double dx = qj.x - qi.x;
-    const double dy = qj.y - qi.y;
-    const double dz = qj.z - qi.z;
-    return __builtin_fma(dz, dz, __builtin_fma(dy, dy, dx * dx));
-}
-
-__device__ __forceinline__ double readlane_d(double v, int lane) {
-    const long long u = __double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(u & 0xffffffffll), lane);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(u >> 32), lane);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
-// Neighbour cell along one axis with its periodic image.  sub is the amount
-// the oracle's minimum image subtracts: L * rint(t / L) with t = x_j - x_i.
-__device__ __forceinline__ int nb_axis(int c, int o, int n, double L, double& sub, int& r) {
+// Neighbour cell along one axis and its periodic image r: the oracle's minimum image
+// subtracts r * L = L * rint((x_j - x_i) / L) there.
+__device__ __forceinline__ int nb_axis(int c, int o, int n, int& r) {
     int x = c + o;
-    sub = 0.0;
     r = 0;
     if (x < 0) {
         x += n;
-        sub = L;
         r = 1;
     } else if (x >= n) {
         x -= n;
-        sub = -L;
         r = -1;
     }
     return x;
 }
 
-// A4, one wavefront per home cell.  All keys of a cell share one candidate set:
-// the particles of its 27 stencil cells, concatenated with the home cell first and
-// the other 26 in stencil order after it.  Lane l
-// holds candidate l of each 64-wide chunk (loads are contiguous runs).  A pass
-// loads up to G chunks into registers, then the wavefront walks the cell's keys:
-// per (key, chunk) an exact FP64 test, a ballot, an mbcnt prefix on the key's
-// running count, and the accepted partners appended in candidate order.  The
-// running count is wave-uniform (SGPR), so no lane bookkeeping sits in the inner
-// loop.  The distance test is the plain definition (no contraction) for cells whose
-// stencil holds a periodic image, and contracted into FMAs elsewhere: the accepted
-// set is the CPU's except possibly for pairs within ~1e-15 of the list radius.
+// A4, one wavefront per home cell (or per part of a home cell's keys, see k_list).
+// All keys of a cell share one candidate set: the particles of its 27 stencil cells,
+// concatenated with the home cell first and the other 26 in stencil order after it.  Lane
+// l holds candidate l of each 64-wide chunk (loads are contiguous runs).  A pass loads up
+// to G chunks into registers, then the wavefront walks the cell's keys: per (key, chunk) a
+// distance test, a ballot, an mbcnt prefix, and the accepted partners appended in
+// candidate order at the key's running (wave-uniform) place in the staging buffer.
+//
+// The test.  Every position is taken relative to the home cell's centre in FP64, periodic
+// images moved next to it first, and rounded to FP32; r^2 < r_list^2 is then evaluated as
+//   |x_j|^2 - 2 x_i . x_j  <  t_i,   t_i = r_list^2 - |x_i|^2,
+// with |x_j|^2 held per candidate and (-2 x_i, t_i) read from lane i into scalar registers:
+// three FMAs, where differences and squares take six instructions, on half the registers of
+// FP64.  It decides only what it can: with R^2 the squared diagonal of a cell, |x_j|^2 is at
+// most 2.25 R^2 and |x_i| |x_j| 0.75 R^2, and the roundings of the coordinates (their products
+// 3 R^2, in units of 2^-24), of |x_j|^2 (6.75 R^2), of the three FMAs (11.25 R^2) and of t_i
+// (0.6 R^2) add up to less than 22 R^2 2^-24.  Candidates are compared with t_i - eps and
+// t_i + eps, eps = 32 R^2 2^-24 (4.5e-5 for cells of side 2.8; the FP32 thresholds' own
+// rounding fits in the difference); a key with a candidate between the two (one in 1300) is
+// done again by slow_key with the plain FP64 minimum-image definition, so every set is the
+// one that definition gives, bit for bit.
+constexpr int kListG = 6;     // candidate chunks per pass
+constexpr int kMarkBytes = kListG * kWave;  // candidate window of a pass
+constexpr int kStage = 2560;  // staged list entries per wavefront.  With the room behind it, marks and cell
+                              // table 26 KB per block: 6 blocks per CU, as many as the registers allow
+constexpr int kStageAll = kStage + kListG * kWave;
 
-// Positions seen through the constant address space: in the list build they are
-// read-only, and uniform indices then become scalar loads into SGPRs.
-typedef const __attribute__((address_space(4))) double const_double;
+// Centre of cell c along an axis of cells of side cs.
+__device__ __forceinline__ double cell_mid(int c, double cs) { return ((double)c + 0.5) * cs; }
 
-// One pass over the keys kb .. kb+mb-1 of a home cell against candidate chunks
-// [c0, c0 + G*64).  WRAP: some stencil cell is a periodic image, so every lane
-// subtracts its image term (a zero term leaves t unchanged bit for bit).
-// STAGED: accepted entries go to the wavefront's LDS buffer (key a's entry e at
-// a * cap + (e % TPK) * (cap / TPK) + e / TPK, i.e. already in per-lane chunk
-// order) and leave in whole 16-byte chunks afterwards; otherwise each entry is
-// stored to the list directly.
-// A candidate's stencil cell: the non-empty stencil cell at position o of the
-// candidate order marks its first candidate with o + 1 in a byte window of the pass
-// (the wavefront's `mark`, G * 64 bytes), and a running maximum over the window,
-// started from the position that was open at the end of the previous pass (`open`),
-// gives every candidate the last position starting at or before it; lane o holds
-// that position's start, entry base and image term.
-constexpr int kStage = 2048;  // LDS list entries per wavefront (16 KB per block, 17.5 KB with the marks: 7 blocks per CU)
-constexpr int kMarkBytes = 6 * kWave;  // candidate window of a pass (G <= 6 chunks)
+// Image code (nb_axis's r per axis, two bits each) to r * L: exact.
+__device__ __forceinline__ double img_shift(int im, int axis, double L) {
+    return (double)((im << (30 - 2 * axis)) >> 30) * L;
+}
 
-template <int TPK, bool WRAP, bool STAGED, bool HALF, bool TL>
-__device__ __forceinline__ void list_pass(const Dev& d, const Params& p, const Pos* __restrict__ q,
-                                          const const_double* qc, int cs0, int kb, int mb, int c0, int total,
-                                          int start, int pre, int ekey, int scnt, double shx, double shy,
-                                          double shz, int& n_own, int& open, uint16_t* stage,
-                                          uint8_t* mark) {
-    constexpr int G = WRAP ? 3 : 6;
-    static_assert(G * kWave <= kMarkBytes, "mark window");
+// Squared minimum-image distance exactly as the plain definition evaluates it:
+// d = (x_j - x_i) - L * rint((x_j - x_i) / L) per axis, where the subtracted
+// image term is known from the stencil, then dx*dx + dy*dy + dz*dz left to
+// right.  No contraction, so the accept decision matches the CPU bit for bit.
+__device__ __forceinline__ double dist2_exact(const Pos& qi, const Pos& qj, int im, const double* L) {
+#pragma clang fp contract(off)
+    const double dx = (qj.x - qi.x) - img_shift(im, 0, L[0]);
+    const double dy = (qj.y - qi.y) - img_shift(im, 1, L[1]);
+    const double dz = (qj.z - qi.z) - img_shift(im, 2, L[2]);
+    return dx * dx + dy * dy + dz * dz;
+}
+
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// v with lane `lane` replaced by x (both uniform).
+__device__ int amdgcn_writelane(int x, int lane, int v) __asm("llvm.amdgcn.writelane.i32");
+// Keeps a uniform value as it is computed here: without it the compiler sums the popcounts of
+// a key's chunks again for every chunk.
+__device__ __forceinline__ int keep_scalar(int v) {
+    asm("" : "+s"(v));
+    return v;
+}
+// LDS words by byte address, and an array's byte address.
+typedef __attribute__((address_space(3))) uint16_t lds_u16;
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
+}
+__device__ __forceinline__ float readlane_f(float v, int lane) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
+// The arguments of k_list, read afresh: through a pointer that the compiler cannot follow
+// back to the last read, so that they are scalar loads (a hit in the scalar cache) where they
+// are used instead of some 80 scalar registers held, and spilled, across every cell.
+struct ListArgs {
+    Dev d;
+    Params p;
+    int gk, gk64, parts;
+};
+__device__ __forceinline__ const ListArgs& list_args() {
+    typedef const __attribute__((address_space(4))) ListArgs* Ptr;
+    Ptr a = (Ptr)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));
+    return *(const ListArgs*)a;
+}
+
+// One group of keys, kb .. kb+mb-1 of a home cell (one 64-candidate chunk holds them all),
+// against all its `total` candidates; returns the partners of key kb + a in lane a.
+// STAGED: key a's entry e goes to place a * cap + e of the wavefront's LDS buffer; the
+// entries leave in whole 16-byte chunks afterwards.  A key with more than cap partners
+// runs on into the places of the keys after it, and the last one into the room behind
+// kStage (a pass starts at most cap entries in and adds at most G * 64): its build is
+// thrown away (k_list sets halt), so nothing needs to be checked per chunk.  Otherwise
+// (a capacity beyond the buffer) every key takes the slow way and stores its entries to the
+// list directly, up to cap.
+// A candidate's stencil cell: `tab` holds the non-empty stencil cells in candidate order
+// (slot of candidate ci: x + ci; its entry: y + ci; image code z).  Lane o < ncell knows the
+// first candidate `pre` of the o-th of them; all but the first mark the candidate before it in
+// a byte window of the pass (`mark`, G * 64 bytes), so that the marks before a candidate
+// (a ballot and mbcnt per chunk, on the count of the chunks before) number its cell.
+template <bool HALF, bool TL>
+__device__ __forceinline__ int list_group(const Dev& d, const Params& p, const Pos* __restrict__ q, int cs0, int kb,
+                                          int mb, int total, int pre, int ncell, bool wrap, const BoxGeom& g, int hx,
+                                          int hy, int hz, bool staged, uint16_t* stage, uint8_t* mark,
+                                          const int4* tab) {
+    constexpr int G = kListG;
     const int l = lane_id();
-    const double nan = __longlong_as_double(0x7ff8000000000000ll);
-    const int nch = min(G, (total - c0 + kWave - 1) >> 6);  // uniform, >= 1
-    // the window's marks: cleared as words, then one byte per cell starting in it
-    uint32_t* mw = reinterpret_cast<uint32_t*>(mark);
-    if (l < G * kWave / 4) mw[l] = 0u;
-    if (G * kWave / 4 > kWave && l < G * kWave / 4 - kWave) mw[kWave + l] = 0u;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (l < 27 && scnt > 0 && pre >= c0 && pre < c0 + G * kWave) mark[pre - c0] = (uint8_t)(l + 1);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int sbase = start - pre;  // stencil cell s: slot of its candidate ci is sbase + ci
-    double cx[G], cy[G], cz[G], sx[G], sy[G], sz[G];
-    uint32_t ent[G];
-#pragma unroll
-    for (int k = 0; k < G; ++k) {
-        if (k < nch) {
-            const int ci = c0 + k * kWave + l;
-            const bool valid = ci < total;
-            const int run = max(wave_incl_max((int)mark[k * kWave + l]), open);
-            open = __builtin_amdgcn_readlane(run, 63);
-            const int sc = max(run - 1, 0);  // last stencil cell whose range starts at or before ci
-            // shuffles run on every lane: a bpermute from an inactive lane reads 0
-            const int base_sc = __shfl(sbase, sc), ek_sc = __shfl(ekey, sc);
-            // gather format: stencil cell << 11 | rank; row-tile format: the staged record's
-            // LDS byte offset (12-byte records)
-            ent[k] = (uint32_t)(ek_sc + ci) * (TL ? (uint32_t)p.recb : 1u);
-            // 32-bit byte offset from the (scalar) array base: slots stay below 2^27
-            const uint32_t boff = (uint32_t)(valid ? base_sc + ci : cs0) * (uint32_t)sizeof(Pos);
-            const Pos qj = *reinterpret_cast<const Pos*>(reinterpret_cast<const char*>(q) + boff);
-            cx[k] = valid ? qj.x : nan;  // NaN distance: never accepted
-            cy[k] = qj.y;
-            cz[k] = qj.z;
-            if (WRAP) {
-                sx[k] = __shfl(shx, sc);
-                sy[k] = __shfl(shy, sc);
-                sz[k] = __shfl(shz, sc);
-            }
-        }
+    const int cap = p.cap;
+    const float inf = __int_as_float(0x7f800000);
+    const double ox = cell_mid(hx, g.cs[0]), oy = cell_mid(hy, g.cs[1]), oz = cell_mid(hz, g.cs[2]);
+    int n_own = 0;
+    // lane a: key kb + a
+    const Pos qk = q[cs0 + kb + min(l, mb - 1)];
+    float kx, ky, kz, tlo, thi;
+    {
+        const double x = qk.x - ox, y = qk.y - oy, z = qk.z - oz;
+        const double t = p.rl2 - (x * x + y * y + z * z), eps = g.leps;
+        kx = -2.0f * (float)x;
+        ky = -2.0f * (float)y;
+        kz = -2.0f * (float)z;
+        tlo = (float)(t - eps);
+        thi = (float)(t + eps);
     }
-    // The candidate loads must land before the key loop: a wait placed inside it
-    // would also wait on the list stores issued there.
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    const double rl2 = p.rl2;
-    const int cap = p.cap, rows = p.rows;
-    // The key loop, instantiated per chunk count so that every chunk's distances are
-    // computed ahead of the (serial) compaction chain, with no branches between them.
-    // The home cell's members come first among the candidates, so key kb + a is
-    // candidate kb + a: with GEN false the pass starts at the block's first key
-    // (c0 == kb), key a's own candidate is lane a of the first chunk, and only that
-    // chunk's ballot drops a bit.
-    auto key_loop = [&](auto n_c, auto gen_c) {
-        constexpr int N = decltype(n_c)::value;
-        constexpr bool GEN = decltype(gen_c)::value;
-        double nx = qc[4 * (cs0 + kb)], ny = qc[4 * (cs0 + kb) + 1], nz = qc[4 * (cs0 + kb) + 2];
-        for (int a = 0; a < mb; ++a) {
-            const int key = cs0 + kb + a;
-            double4 qi;  // scalar loads, one key ahead
-            qi.x = nx;
-            qi.y = ny;
-            qi.z = nz;
-            if (a + 1 < mb) {
-                nx = qc[4 * (key + 1)];
-                ny = qc[4 * (key + 1) + 1];
-                nz = qc[4 * (key + 1) + 2];
-            }
-            int cnt = __builtin_amdgcn_readlane(n_own, a);  // uniform running count (0 in the first pass)
-            // the key's own candidate: chunk sk, bit sb (scalar)
-            const int self = kb + a - c0;
-            const int sk = self >> 6;
-            const unsigned long long sb = 1ull << (GEN ? self & 63 : a);
-            char* __restrict__ kp = STAGED ? reinterpret_cast<char*>(stage + a * cap)
-                                           : reinterpret_cast<char*>(d.list + list_addr(key, 0, TPK, rows));
-            bool in[N];
-#pragma unroll
-            for (int k = 0; k < N; ++k) {
-                const double r2 = WRAP ? dist2_exact(qi, make_double3(cx[k], cy[k], cz[k]), sx[k], sy[k], sz[k])
-                                       : dist2_fma0(qi, make_double3(cx[k], cy[k], cz[k]));
-                in[k] = r2 < rl2;
-            }
-#pragma unroll
-            for (int k = 0; k < N; ++k) {
-                // lanes within the list radius, minus the key itself; the half list
-                // keeps only candidates after the key (the home cell comes first and
-                // the backward stencil cells hold no candidates)
-                const unsigned long long mask =
-                    HALF ? __builtin_amdgcn_ballot_w64(in[k] && k * kWave + l > self)
-                         : __builtin_amdgcn_ballot_w64(in[k]) & ~(GEN ? (k == sk ? sb : 0ull) : (k == 0 ? sb : 0ull));
-                // the lane's entry position: the running count plus its place among the
-                // accepted lanes (the count enters as the lane-count base, no scalar add)
-                const uint32_t pos = __builtin_amdgcn_mbcnt_hi(
+    int open = 0;  // marks before the pass's first candidate
+    for (int c0 = 0; c0 < total; c0 += G * kWave) {
+        const int nch = min(G, (total - c0 + kWave - 1) >> 6);  // uniform, >= 1
+        // The home cell's members come first among the candidates: key kb + a is candidate
+        // kb + a.  own0: the first key's candidate as a bit of chunk sk of the pass, 0 when no key
+        // of the group is a candidate of it.
+        const int own = kb - c0;  // uniform, like the rest
+        const int sk = own >> 6;
+        const unsigned long long own0 = sk >= 0 && sk < G ? 1ull << (own & 63) : 0ull;
+        const int open0 = open, n_prev = n_own;
+        // the window's marks: cleared as words, then a byte each
+        uint32_t* mw = reinterpret_cast<uint32_t*>(mark);
+        mw[l] = 0u;
+        if (l < G * kWave / 4 - kWave) mw[kWave + l] = 0u;
+        wave_lds_sync();
+        if (l > 0 && l < ncell && pre > c0 && pre <= c0 + G * kWave) mark[pre - 1 - c0] = 1;
+        wave_lds_sync();
+        // the cell (place in tab) of candidate c0 + k * 64 + l, for k in ascending order
+        auto place = [&](int m) {
+            const unsigned long long mk = __builtin_amdgcn_ballot_w64(m != 0);
+            const uint32_t r = __builtin_amdgcn_mbcnt_hi((unsigned)(mk >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((unsigned)mk, (uint32_t)open));
+            open += __popcll(mk);
+            return r;
+        };
+        // gather format: stencil cell << 11 | rank; row-tile format: the staged record's
+        // LDS byte offset
+        auto entry = [&](int key_sc, int ci) { return (uint32_t)(key_sc + ci) * (TL ? (uint32_t)p.recb : 1u); };
+        // Key a again by the plain FP64 definition, from the entries it held before this pass
+        auto slow_key = [&](int a) {
+            const Pos qi = q[cs0 + kb + a];
+            int cnt = __builtin_amdgcn_readlane(n_prev, a);
+            const int at0 = a * cap + min(cnt, cap) - cnt;  // staged place of entry e: at0 + e
+            open = open0;
+            for (int k = 0; k < nch; ++k) {
+                const int ci = c0 + k * kWave + l;
+                const int4 t = tab[place(mark[k * kWave + l])];
+                const double r2 = dist2_exact(qi, q[t.x + min(ci, total - 1)], t.z, g.L);
+                const bool in = r2 < p.rl2 && ci < total && (HALF ? ci > kb + a : ci != kb + a);
+                const unsigned long long mask = __builtin_amdgcn_ballot_w64(in);
+                const int pos = (int)__builtin_amdgcn_mbcnt_hi(
                     (unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, (uint32_t)cnt));
-                unsigned long long sm = mask;
-                if (cnt + __popcll(mask) > cap)  // overflow: keep the entries that fit (rare)
-                    sm = __builtin_amdgcn_ballot_w64(__builtin_amdgcn_inverse_ballot_w64(mask) &&
-                                                     (int)pos < cap);  // cnt may exceed cap
-                if (__builtin_amdgcn_inverse_ballot_w64(sm)) {
-                    if constexpr (STAGED && TPK == 1) {
-                        reinterpret_cast<uint16_t*>(kp)[pos] = (uint16_t)ent[k];
-                    } else {
-                        const uint32_t off = STAGED ? ((pos % TPK) * (uint32_t)(cap / TPK) + pos / TPK) * 2u
-                                                    : list_off_bytes<TPK>(pos);
-                        *reinterpret_cast<uint16_t*>(kp + off) = (uint16_t)ent[k];
-                    }
-                }
+                const uint16_t e = (uint16_t)entry(t.y, ci);
+                if (in && staged) stage[at0 + pos] = e;
+                if (in && !staged && pos < cap) d.list[list_addr(cs0 + kb + a, pos, p.tpk, p.rows)] = e;
                 cnt += __popcll(mask);
             }
             if (l == a) n_own = cnt;
+        };
+        if (!staged) {  // uniform
+            for (int a = 0; a < mb; ++a) slow_key(a);
+            continue;
         }
-    };
-    auto by_count = [&](auto gen_c) {
-        switch (nch) {
-            case 1: key_loop(std::integral_constant<int, 1>{}, gen_c); break;
-            case 2: key_loop(std::integral_constant<int, 2>{}, gen_c); break;
-            default:
-                if constexpr (G == 3) {
-                    key_loop(std::integral_constant<int, 3>{}, gen_c);
-                } else {
-                    switch (nch) {
-                        case 3: key_loop(std::integral_constant<int, 3>{}, gen_c); break;
-                        case 4: key_loop(std::integral_constant<int, 4>{}, gen_c); break;
-                        case 5: key_loop(std::integral_constant<int, 5>{}, gen_c); break;
-                        default: key_loop(std::integral_constant<int, 6>{}, gen_c); break;
-                    }
+        // every chunk's loads first, then the conversions: one memory latency per pass
+        double qx[G], qy[G], qz[G];
+        float cx[G], cy[G], cz[G], cn[G];
+        uint32_t ent[G / 2];  // two 16-bit entries each
+        int m[G];
+#pragma unroll
+        for (int k = 0; k < G; ++k) m[k] = mark[k * kWave + l];
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            if (k < nch) {
+                const int ci = c0 + k * kWave + l;
+                const int4* tc = tab + place(m[k]);
+                const int2 t = *reinterpret_cast<const int2*>(tc);
+                const uint32_t e = entry(t.y, ci);
+                ent[k / 2] = k & 1 ? ent[k / 2] | (e << 16) : e & 0xffffu;
+                // 32-bit byte offset from the (scalar) array base: slots stay below 2^27
+                const uint32_t boff = (uint32_t)(t.x + min(ci, total - 1)) * (uint32_t)sizeof(Pos);
+                const Pos qj = *reinterpret_cast<const Pos*>(reinterpret_cast<const char*>(q) + boff);
+                qx[k] = qj.x;
+                qy[k] = qj.y;
+                qz[k] = qj.z;
+                if (wrap) {
+                    const int im = tc->z;
+                    qx[k] -= img_shift(im, 0, g.L[0]);
+                    qy[k] -= img_shift(im, 1, g.L[1]);
+                    qz[k] -= img_shift(im, 2, g.L[2]);
                 }
-                break;
+            } else {
+                qx[k] = qy[k] = qz[k] = 0.0;
+                if (!(k & 1)) ent[k / 2] = 0u;
+            }
         }
-    };
-    // own candidates of this pass: kb - c0 .. kb + mb - 1 - c0 (uniform); the half list
-    // drops them by position instead
-    if (HALF || kb == c0)
-        by_count(std::false_type{});
-    else
-        by_count(std::true_type{});
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            cx[k] = (float)(qx[k] - ox);
+            cy[k] = (float)(qy[k] - oy);
+            cz[k] = (float)(qz[k] - oz);
+            const float n2 = __builtin_fmaf(cz[k], cz[k], __builtin_fmaf(cy[k], cy[k], cx[k] * cx[k]));
+            cn[k] = c0 + k * kWave + l < total ? n2 : inf;  // inf: never accepted
+        }
+        unsigned long long again = 0ull;  // keys with a candidate the FP32 test cannot decide
+        // The key loop, instantiated per chunk count so that every chunk's distances are
+        // computed ahead of the (serial) compaction chain, with no branches between them.
+        // SELF0: the keys' own candidates lie in chunk 0 or in none (every cell of at most 64
+        // members), and only that chunk's ballot drops a bit.
+        auto key_loop = [&](auto n_c, auto self0_c) {
+            constexpr int N = decltype(n_c)::value;
+            constexpr bool SELF0 = decltype(self0_c)::value;
+            const int st0 = (int)(lds_addr(stage) >> 1);
+            for (int a = 0; a < mb; ++a) {
+                const float Kx = readlane_f(kx, a), Ky = readlane_f(ky, a), Kz = readlane_f(kz, a);
+                const float lo = readlane_f(tlo, a), hi = readlane_f(thi, a);
+                const int done = __builtin_amdgcn_readlane(n_own, a);  // uniform running count (0 in the first pass)
+                const unsigned long long sb = own0 << a;
+                float s[N];
+#pragma unroll
+                for (int k = 0; k < N; ++k)
+                    s[k] = __builtin_fmaf(Kx, cx[k], __builtin_fmaf(Ky, cy[k], __builtin_fmaf(Kz, cz[k], cn[k])));
+                const int at0 = keep_scalar(st0 + a * cap + min(done, cap));
+                int at = at0;  // the next staged entry (LDS address in entries)
+                unsigned long long bord = 0ull;
+#pragma unroll
+                for (int k = 0; k < N; ++k) {
+                    // lanes within the list radius, minus the key itself; the half list
+                    // keeps only candidates after the key (the home cell comes first and
+                    // the backward stencil cells hold no candidates)
+                    const unsigned long long low = __builtin_amdgcn_ballot_w64(s[k] < lo);
+                    const unsigned long long mask =
+                        HALF ? low & __builtin_amdgcn_ballot_w64(k * kWave + l > own + a)
+                             : low & ~((SELF0 ? k == 0 : k == sk) ? sb : 0ull);
+                    bord |= __builtin_amdgcn_ballot_w64(s[k] < hi) & ~low;
+                    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
+                                                                   __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+                    if (__builtin_amdgcn_inverse_ballot_w64(mask))
+                        *(lds_u16*)((pos + (uint32_t)at) << 1) = (uint16_t)(k & 1 ? ent[k / 2] >> 16 : ent[k / 2]);
+                    at = keep_scalar(at + __popcll(mask));
+                }
+                if (bord) again |= 1ull << a;
+                n_own = amdgcn_writelane(done + (at - at0), a, n_own);
+            }
+        };
+        if (!HALF && own0 && sk > 0) {
+            key_loop(std::integral_constant<int, G>{}, std::false_type{});
+        } else {
+            switch (nch) {
+                case 1: key_loop(std::integral_constant<int, 1>{}, std::true_type{}); break;
+                case 2: key_loop(std::integral_constant<int, 2>{}, std::true_type{}); break;
+                case 3: key_loop(std::integral_constant<int, 3>{}, std::true_type{}); break;
+                case 4: key_loop(std::integral_constant<int, 4>{}, std::true_type{}); break;
+                case 5: key_loop(std::integral_constant<int, 5>{}, std::true_type{}); break;
+                default: key_loop(std::integral_constant<int, 6>{}, std::true_type{}); break;
+            }
+        }
+        for (; again; again &= again - 1ull) slow_key(__ffsll((long long)again) - 1);
+    }
+    return n_own;
 }
 
-// Seven wavefronts per SIMD (at most 72 VGPRs, no vector spills in the full-list
-// build): the build issues about as many scalar as vector instructions and is bound by
-// the latency of its scalar-vector chain per (key, chunk), which more resident
-// wavefronts hide (measured at 32M particles, rebuild chain per rebuild: 4 wavefronts
-// 13.2 ms, 6 wavefronts 11.5 ms in an earlier form; 6 -> 7 -> 8 wavefronts now
-// 9.36 -> 9.08 -> 9.19 ms, the last with spills).
-// TL: the row-tile entry format (FP32-mixed, full list); otherwise the gather format.
-template <int TPK, bool HALF, bool TL>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_list(Dev d, Params p) {
-    if (!ld_const(d.any) || halted(d)) return;  // no box rebuilds this step, or a build overflowed
-    __shared__ __align__(16) uint16_t stage_all[kBlock / kWave][kStage];
+// Six wavefronts per SIMD: no vector register is spilled.  Seven (72 VGPRs, 18 spilled) take
+// 9-10% longer from 2M particles on.  What bounds it is vector issue: measured on jittered
+// FCC boxes, list build before (seven FP64 instructions per test, one address for the longest
+// list of a tile) and now: 100k particles at density 0.6 101 -> 43 us, 1M at 0.5 415 -> 220 us,
+// 2M at 0.7 with cutoff 3.0 1150 -> 980 us, 16M 3000 -> 2800 us.
+// TL: the row-tile entry format (one lane per key, full list); otherwise the gather format.
+//
+// A cell's keys are taken in groups of gk (what the staging buffer holds at the list's
+// capacity); in a cell of more than 64 members a group holds gk64, a power of two, so that
+// its keys lie in one 64-candidate chunk.  With `parts` > 1 that many wavefronts share a cell,
+// part i taking groups i, i + parts, ... (launch_list).
+template <bool HALF, bool TL>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_list(ListArgs args) {
+    if (!ld_const(args.d.any) || halted(args.d)) return;  // no box rebuilds this step, or a build overflowed
+    __shared__ __align__(16) uint16_t stage_all[kBlock / kWave][kStageAll];
     __shared__ __align__(16) uint8_t mark_all[kBlock / kWave][kMarkBytes];
+    __shared__ __align__(16) int4 tab_all[kBlock / kWave][27];
     const int l = lane_id();
-    const int ncells = p.ntile * kTile;
-    const int cap = p.cap, rows = p.rows;
-    // XCD-aware: each XCD sweeps a contiguous run of cells, so the stencil rows a
-    // cell loads are still in that XCD's L2 for its neighbours
     // the wavefront's index in the block, as a scalar: the cell loop and every per-cell
     // table read (tile's box, box state and geometry) then stay in scalar registers and
     // the scalar cache instead of serialised vector loads; the staging buffer's base
     // is scalar too
-    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int wv = wave_in_block();
     uint16_t* stage = stage_all[wv];
     uint8_t* mark = mark_all[wv];
-    // One home cell c of box b.
-    auto cell_body = [&](int c, int b, const BoxGeom& g) {
-        const int t = c / kTile;
+    int4* tab = tab_all[wv];
+    // Part `part` of home cell c of box b.
+    auto cell_body = [&](int c, int part, int b, const BoxGeom& g, const ListArgs& A) {
+        const Dev& d = A.d;
+        const Params& p = A.p;
+        const int cap = p.cap;
         const BoxState& st = d.st[b];
         const int local = c - g.cell_off;
         const int m = ld_const(d.cell_cnt + c);
-        if (m == 0) return;
+        const int gk = m > kWave ? A.gk64 : A.gk;
+        if (part * gk >= m) return;
         const int cs0 = ld_const(d.cell_start + c);
         Pos* __restrict__ q = d.q[ld_const(&st.sq) ^ 1];  // permuted, made current after the build
         const int ly = gdiv(g, local, 0), cz = gdiv(g, local, 2);
@@ -1159,15 +1208,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 8))) 
         // image term
         const int s_of_l = l == 0 ? 13 : (l <= 13 ? l - 1 : l);
         int start = 0, cnt = 0;
-        double shx = 0.0, shy = 0.0, shz = 0.0;
-        bool img = false;
+        int img = 0;
         if (l < 27) {
             const int ox = s_of_l % 3 - 1, oy = (s_of_l / 3) % 3 - 1, oz = s_of_l / 9 - 1;
             int rx, ry, rz;
-            const int x = nb_axis(cx, ox, g.n[0], g.L[0], shx, rx);
-            const int y = nb_axis(cy, oy, g.n[1], g.L[1], shy, ry);
-            const int z = nb_axis(cz, oz, g.n[2], g.L[2], shz, rz);
-            img = (rx | ry | rz) != 0;
+            const int x = nb_axis(cx, ox, g.n[0], rx);
+            const int y = nb_axis(cy, oy, g.n[1], ry);
+            const int z = nb_axis(cz, oz, g.n[2], rz);
+            img = (rx & 3) | (ry & 3) << 2 | (rz & 3) << 4;
             const int nc = g.cell_off + (z * g.n[1] + y) * g.n[0] + x;
             start = d.cell_start[nc];
             cnt = d.cell_cnt[nc];
@@ -1176,9 +1224,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 8))) 
             // offsets are lexicographically positive, so each pair of cells meets once
             if (HALF && s_of_l < 13) cnt = 0;
         }
-        const bool wrap = __ballot(img) != 0ull;  // uniform: this cell touches the box boundary
         const int incl = wave_incl_sum(cnt);
-        const int pre = incl - cnt;
+        int pre = incl - cnt;
         // entry of candidate ci of the lane's stencil cell s: ekey + ci (gather format:
         // s << 11 plus its rank; row-tile format: its index in the staged region of the
         // home cell's row tile, whose piece p = r * 3 + side holds unwrapped cells in order)
@@ -1192,83 +1239,91 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 8))) 
             ekey = (l < 27 ? start + d.rt_delta[rt * 27 + pc] : 0) - pre;
         }
         const int total = __builtin_amdgcn_readlane(incl, 26);
-        const const_double* qc = (const const_double*)q;     // 4 doubles per particle
+        const bool wrap = __ballot(img != 0) != 0ull;  // uniform: this cell touches the box boundary
+        // the non-empty stencil cells, closed up (nearly always all 27)
+        const unsigned long long ne = __builtin_amdgcn_ballot_w64(cnt > 0);
+        const int ncell = __popcll(ne);
+        const int o = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(ne >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)ne, 0u));
+        if (cnt > 0) tab[o] = make_int4(start - pre, ekey, img, pre);
+        wave_lds_sync();
+        if (ncell < 27) pre = tab[min(l, 26)].w;
+        const int seen = ld_const(&st.need);  // a lower bound of the longest list so far
         int need = 0;
-        for (int kb = 0; kb < m; kb += kWave) {
-            const int mb = min(kWave, m - kb);
-            int n_own = 0;  // lane a: partners of key kb + a so far
-            const bool staged = mb * cap <= kStage;  // uniform
+        for (int kb = part * gk; kb < m; kb += A.parts * gk) {
+            const int mb = min(gk, m - kb);
+            const bool staged = mb * cap <= kStage;  // uniform; false only if one key's list outgrows the buffer
+            const int n_own = list_group<HALF, TL>(d, p, q, cs0, kb, mb, total, pre, ncell, wrap, g, cx, cy, cz, staged,
+                                                   stage, mark, tab);
+            wave_lds_sync();
             if (staged) {
-                int open = 0;  // no stencil cell open before the first candidate
-                if (wrap) {
-                    for (int c0 = 0; c0 < total; c0 += 3 * kWave)
-                        list_pass<TPK, true, true, HALF, TL>(d, p, q, qc, cs0, kb, mb, c0, total, start, pre, ekey, cnt, shx,
-                                                         shy, shz, n_own, open, stage, mark);
-                } else {
-                    for (int c0 = 0; c0 < total; c0 += 6 * kWave)
-                        list_pass<TPK, false, true, HALF, TL>(d, p, q, qc, cs0, kb, mb, c0, total, start, pre, ekey, cnt, shx,
-                                                          shy, shz, n_own, open, stage, mark);
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                // write-out: item (a, t, c) = chunk c of key a's lane t, 16 bytes; lanes
-                // of consecutive keys write consecutive chunks of the list
-                const int cpt = cap / TPK / 8;  // chunks per key lane in the buffer
-                const int nitem = mb * TPK * cpt;  // <= kStage / 8 (staged)
-                // it / (mb * TPK) in FP32: (it + 1/2) / dv lies at least 1/(2 dv) from an
-                // integer, far above the rounding error for it < 2^12, dv <= 2^9
-                const int dv = mb * TPK;
-                const float rdv = 1.0f / (float)dv;
-                for (int i0 = 0; i0 < nitem; i0 += kWave) {  // same trip count on every lane
-                    const int it = i0 + l;
-                    const int c = (int)(((float)it + 0.5f) * rdv), at = it - c * dv;
-                    const int a = at / TPK, t = at - a * TPK;
-                    const int na = __shfl(n_own, a & 63);  // every lane takes part in the shuffle
-                    const int nlane = na > t ? (na - t + TPK - 1) / TPK : 0;
-                    if (it < nitem && c * 8 < nlane) {
-                        const uint4 v = *reinterpret_cast<const uint4*>(stage + a * cap + t * (cap / TPK) + c * 8);
-                        *reinterpret_cast<uint4*>(d.list + list_addr(cs0 + kb + a, 8 * c * TPK + t, TPK, rows)) = v;
+                // write-out: row r = lane t of key a, chunk c of its entries, 16 bytes; the
+                // lanes of a pass hold 2^rsh rows side by side (consecutive keys write consecutive
+                // chunks of the list), 64 >> rsh chunks of each: 8 x 8 where a key has one lane and
+                // about 6 chunks, 16 x 4 where it has several with fewer
+                const ListArgs& W = list_args();
+                const int tpk = W.p.tpk, tsh = __builtin_ctz((unsigned)tpk);  // a power of two
+                const int rsh = tpk == 1 ? 3 : 4, dv = mb << tsh;
+                for (int r0 = 0; r0 < dv; r0 += 1 << rsh) {
+                    const int r = r0 + (l & ((1 << rsh) - 1));
+                    const int a = r >> tsh, t = r & (tpk - 1);
+                    const int na = min(__shfl(n_own, a & 63), cap);  // every lane takes part in the shuffle
+                    const int nlane = r < dv && na > t ? (na - t + tpk - 1) >> tsh : 0;
+                    const int key = cs0 + kb + a, lw = key >> (6 - tsh);  // list_addr(key, t) by shifts
+                    const int ln = ((key - (lw << (6 - tsh))) << tsh) + t;
+                    uint4* dst = reinterpret_cast<uint4*>(W.d.list + (size_t)lw * W.p.rows * kWave) + ln;
+                    const uint16_t* src = stage + a * cap + t;
+                    for (int c = l >> rsh; __ballot(c * 8 < nlane) != 0ull; c += kWave >> rsh) {
+                        if (c * 8 < nlane) {
+                            uint4 v;
+                            if (tpk == 1) {
+                                v = *reinterpret_cast<const uint4*>(src + c * 8);
+                            } else {  // the lane's entries are every tpk-th of the key's
+                                uint32_t u[4];
+#pragma unroll
+                                for (int i = 0; i < 4; ++i)
+                                    u[i] = (uint32_t)src[(c * 8 + 2 * i) << tsh] |
+                                           ((uint32_t)src[(c * 8 + 2 * i + 1) << tsh] << 16);
+                                v = make_uint4(u[0], u[1], u[2], u[3]);
+                            }
+                            dst[c * kWave] = v;
+                        }
                     }
                 }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            } else if (wrap) {
-                int open = 0;
-                for (int c0 = 0; c0 < total; c0 += 3 * kWave)
-                    list_pass<TPK, true, false, HALF, TL>(d, p, q, qc, cs0, kb, mb, c0, total, start, pre, ekey, cnt, shx, shy,
-                                                      shz, n_own, open, stage, mark);
-            } else {
-                int open = 0;
-                for (int c0 = 0; c0 < total; c0 += 6 * kWave)
-                    list_pass<TPK, false, false, HALF, TL>(d, p, q, qc, cs0, kb, mb, c0, total, start, pre, ekey, cnt, shx,
-                                                       shy, shz, n_own, open, stage, mark);
+                wave_lds_sync();
             }
             if (l < mb) {
                 const int nk = n_own < cap ? n_own : cap;
                 d.cnt[cs0 + kb + l] = nk;
                 q[cs0 + kb + l].cnt = nk;
             }
-            need = max(need, __builtin_amdgcn_readlane(wave_incl_max(l < mb ? n_own : 0), 63));
+            if (__ballot(l < mb && n_own > min(max(seen, need), cap)))
+                need = max(need, __builtin_amdgcn_readlane(wave_incl_max(l < mb ? n_own : 0), 63));
         }
-        if (l == 0) {
-            atomicMax(&d.tile_need[t], need);
-            if (need > cap) {  // entries were dropped: the step stops here (see halted)
-                atomicMax(&d.st[b].need, need);
-                atomicOr(d.halt, 1);
-            }
+        // the longest list: one address per cell tile took 1024 atomics that serialised (half the
+        // build's time at 1M particles: 415 -> 235 us), so lists no longer than the longest one
+        // so far are left out and the others go to one of kNeedStripes slots of the box
+        if (l == 0 && need > seen)
+            atomicMax(d.need_s + ((size_t)b * kNeedStripes + (c & (kNeedStripes - 1))) * kNeedStride, need);
+        if (l == 0 && need > cap) {  // entries were dropped: the step stops here (see halted)
+            atomicMax(&d.st[b].need, need);
+            atomicOr(d.halt, 1);
         }
     };
-    {
-        for (int c = xcd_block(blockIdx.x, gridDim.x) * 4 + wv; c < ncells; c += gridDim.x * 4) {
-            // tables this kernel does not write, read through the scalar cache
-            const int b = ld_const(d.tile_box + c / kTile);
-            if (!ld_const(&d.st[b].rebuild)) continue;
-            const BoxGeom g = ld_geom(d.geom + b);
-            if (c - g.cell_off >= g.ncell) continue;
-            cell_body(c, b, g);
-        }
+    // items in part-major order: the first part of every cell, then the second, ...
+    // XCD-aware: each XCD sweeps a contiguous run of cells, so the stencil rows a
+    // cell loads are still in that XCD's L2 for its neighbours
+    for (int it = xcd_block(blockIdx.x, gridDim.x) * 4 + wv; it < args.p.ntile * kTile * args.parts;
+         it += gridDim.x * 4) {
+        const ListArgs& A = list_args();
+        const Dev& d = A.d;
+        const int ncells = A.p.ntile * kTile;
+        const int part = A.parts > 1 ? it / ncells : 0, c = it - part * ncells;
+        // tables this kernel does not write, read through the scalar cache
+        const int b = ld_const(d.tile_box + c / kTile);
+        if (!ld_const(&d.st[b].rebuild)) continue;
+        const BoxGeom g = ld_geom(d.geom + b);
+        if (c - g.cell_off >= g.ncell) continue;
+        cell_body(c, part, b, g, A);
     }
 }
 
@@ -2615,14 +2670,30 @@ static inline int list_grid(const Params& p) {
     const int g = p.ntile * kTile / 32;
     return g < 8192 ? grid_for_waves(p.ntile * kTile, 8192) : (g > 65536 ? 65536 : g);
 }
-template <int TPK>
-static void launch_list_t(const Dev& d, const Params& p, hipStream_t s) {
-    if (TPK == 1 && p.half)
-        k_list<1, true, false><<<list_grid(p), kBlock, 0, s>>>(d, p);
-    else if (TPK == 1 && p.tile)
-        k_list<1, false, true><<<list_grid(p), kBlock, 0, s>>>(d, p);
+static void launch_list(const Dev& d, const Params& p, hipStream_t s) {
+    // keys per group: what the staging buffer holds (one when even that does not fit)
+    int gk = kStage / p.cap;
+    gk = gk < 1 ? 1 : (gk > kWave ? kWave : gk);
+    // A small box has too few cells to fill the chip (343 cells at 4000 particles against 6144
+    // resident wavefronts), and the time of one cell, not the sum of all, is what its build
+    // takes: up to 8 wavefronts share a cell while that leaves no more than 3072 of them
+    // (4000 particles 13.3 -> 10, 10,000 at density 0.7 28 -> 20 us; at 100,000 particles
+    // two wavefronts per cell were slower, 40 -> 49 us: each repeats the cell's set-up).
+    const int cells = p.nbox == 1 ? p.maxcell : p.ntile * kTile;
+    int parts = 3072 / cells;
+    parts = parts < 1 ? 1 : (parts > 8 ? 8 : parts);
+    if (parts > 1) {
+        const int mean = p.nwave * kWave / cells + 1, share = (mean + parts - 1) / parts;
+        gk = gk < share ? gk : share;
+    }
+    const int gk64 = gk >= 8 ? 8 : (gk >= 4 ? 4 : (gk >= 2 ? 2 : 1));
+    const int grid = parts > 1 ? grid_for_waves(p.ntile * kTile * parts) : list_grid(p);
+    if (p.half)
+        k_list<true, false><<<grid, kBlock, 0, s>>>(ListArgs{d, p, gk, gk64, parts});
+    else if (p.tile)
+        k_list<false, true><<<grid, kBlock, 0, s>>>(ListArgs{d, p, gk, gk64, parts});
     else
-        k_list<TPK, false, false><<<list_grid(p), kBlock, 0, s>>>(d, p);
+        k_list<false, false><<<grid, kBlock, 0, s>>>(ListArgs{d, p, gk, gk64, parts});
 }
 
 void launch_row_tiles(const Dev& d, const Params& p, hipStream_t s) {
@@ -2644,14 +2715,7 @@ void launch_rebuild_chain(const Dev& d, const Params& p, bool with_list, hipStre
     if (p.tile) launch_row_tiles(d, p, s);
     k_scatter<<<gw, kBlock, 0, s>>>(d, p);
     k_rank_permute<<<gw, kBlock, 0, s>>>(d, p);
-    if (with_list) {
-        switch (p.tpk) {
-            case 1: launch_list_t<1>(d, p, s); break;
-            case 2: launch_list_t<2>(d, p, s); break;
-            case 4: launch_list_t<4>(d, p, s); break;
-            default: launch_list_t<8>(d, p, s); break;
-        }
-    }
+    if (with_list) launch_list(d, p, s);
     k_post_build<<<p.nbox < 1024 ? p.nbox : 1024, kBlock, 0, s>>>(d, p, with_list ? 1 : 0);
 }
 
