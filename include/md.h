@@ -76,7 +76,9 @@ typedef enum {
 /* flags */
 #define MD_F_VERIFY_LIST 1u        /* debug: after every force evaluation count pairs within
                                       rc missing from the list (O(n^2) per box) */
-#define MD_F_GRAPH 2u              /* replay md_step chunks as captured HIP graphs */
+#define MD_F_GRAPH 2u              /* replay md_step chunks as captured HIP graphs (ensembles, and one
+                                      box with MD_REBUILD_EVERY_STEP; other one-box runs enqueue a list
+                                      build only where a step needs one and gain nothing from graphs) */
 #define MD_F_TILE_ON 4u            /* row tiles (threads_per_key 0 or 1; the FP32-mixed default for a
                                       largest box of 2^23 particles or more): each row of cells is
                                       cut into runs of cells whose partners (the 9 neighbouring rows,

@@ -57,6 +57,7 @@ constexpr int kOffBits = 11;             // list entry: partner rank within its 
 constexpr int kMaxCellCount = 1 << kOffBits;
 constexpr int kStripes = 1024;           // slots per box for per-step maxima
 constexpr int kStripeStride = 16;        // 128 bytes between slots
+constexpr int kToldRing = 64;            // rebuild decisions in flight to the host (a power of two)
 constexpr int kNeedStripes = 256;        // slots per box for the longest list of a build
 constexpr int kNeedStride = 16;          // 64 bytes between slots
 constexpr int kTileWMax = 64;            // cells per row tile at most
@@ -157,6 +158,7 @@ struct Dev {
     int32_t* halt;       // nonzero after a list build overflowed (list capacity or a row tile's
                          // staging capacity): the kernels of a step return at once until the
                          // host has grown the list or changed its format and cleared it
+    uint32_t* told;      // [kToldRing] pinned host memory: decisions of k_dutc the host waits for
     int32_t* wave_box;   // box of each 64-slot wavefront
     int32_t* tile_box;   // box of each cell tile
     Pos* q[2];
@@ -289,7 +291,8 @@ int rowtile_blocks_per_cu(const Params& p);
 void launch_rebuild_chain(const Dev& d, const Params& p, bool with_list, hipStream_t s);
 void launch_force(const Dev& d, const Params& p, int mode, bool energy, hipStream_t s);
 void launch_kick_drift(const Dev& d, const Params& p, hipStream_t s);
-void launch_dutc(const Dev& d, const Params& p, hipStream_t s);
+// seq: number of the drift whose decision the host waits for (one box), or 0.
+void launch_dutc(const Dev& d, const Params& p, uint32_t seq, hipStream_t s);
 // thermo: bit 0 applies the thermostat half step that ends a step (after the
 // closing kick), bit 1 the one that starts the next step; the velocity factor
 // goes to BoxState::vscale for the next kick (or k_vscale).

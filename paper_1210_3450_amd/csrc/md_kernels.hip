@@ -54,6 +54,11 @@ __device__ __forceinline__ int ld_const(const int32_t* p) {
 // that build found it, until the host has grown the list or changed its format.
 __device__ __forceinline__ bool halted(const Dev& d) { return ld_const(d.halt) != 0; }
 
+// The kernels that carry a step (force pass, kicks, energy sums) also return at once while a
+// list build is pending: the host may enqueue a step before it knows whether that step needs
+// one (md_step); the step is then left out here and enqueued again after the build.
+__device__ __forceinline__ bool step_off(const Dev& d) { return halted(d) || ld_const(d.any) != 0; }
+
 // A box's geometry, read through the scalar cache: no kernel writes it, so the
 // wavefront-uniform reads become scalar loads instead of a chain of vector loads
 // that every store in a loop would force to repeat.
@@ -408,9 +413,21 @@ __device__ double stripe_max(unsigned long long* stripes) {
 
 // After the drift: swap the q/u buffers, accumulate the DUTC bound and decide
 // whether the list must be rebuilt (Sec. II.A).  One block per box.
-__global__ __launch_bounds__(kBlock) void k_dutc(Dev d, Params p) {
+// seq (one box, else 0): the host waits for the decision on this drift, a word of pinned host
+// memory holding seq << 2 | code: 0 go on, 1 list build needed, 2 stopped (see halted).  A
+// drift left out because a build is pending decides nothing.
+__global__ __launch_bounds__(kBlock) void k_dutc(Dev d, Params p, uint32_t seq) {
 #pragma clang fp contract(off)
-    if (halted(d)) return;
+    auto tell = [&](uint32_t code) {
+        if (seq && threadIdx.x == 0)
+            __hip_atomic_store(d.told + (seq & (kToldRing - 1)), (seq << 2) | code, __ATOMIC_RELEASE,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+    };
+    if (halted(d)) {
+        tell(2u);
+        return;
+    }
+    if (seq && ld_const(d.any)) return;
     for (int b = blockIdx.x; b < p.nbox; b += gridDim.x) {
         const double vmax2 = stripe_max(d.vmax_s + (size_t)b * kStripes * kStripeStride);
         double m2 = 0.0;
@@ -429,6 +446,7 @@ __global__ __launch_bounds__(kBlock) void k_dutc(Dev d, Params p) {
                 rb = 1;
             st.rebuild = rb;
             if (rb) atomicOr(d.any, 1);
+            tell(rb ? 1u : 0u);
         }
     }
 }
@@ -1138,7 +1156,7 @@ __device__ __forceinline__ int list_group(const Dev& d, const Params& p, const P
                     const uint32_t pos = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
                                                                    __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
                     if (__builtin_amdgcn_inverse_ballot_w64(mask))
-                        *(lds_u16*)((pos + (uint32_t)at) << 1) = (uint16_t)(k & 1 ? ent[k / 2] >> 16 : ent[k / 2]);
+                        *(lds_u16*)(size_t)((pos + (uint32_t)at) << 1) = (uint16_t)(k & 1 ? ent[k / 2] >> 16 : ent[k / 2]);
                     at = keep_scalar(at + __popcll(mask));
                 }
                 if (bord) again |= 1ull << a;
@@ -1490,7 +1508,7 @@ __device__ __forceinline__ uint32_t force_rec(const Dev& d, uint32_t cc, int s, 
 // F must be zero before the pass.
 template <int PREC, int MODE, int TPK, bool ENERGY, bool HALF = false>
 __global__ __launch_bounds__(kBlock) void k_force(Dev d, Params p) {
-    if (halted(d)) return;
+    if (step_off(d)) return;
     static_assert(!HALF || (MODE == kForceOnly && TPK == 1), "half lists: forces only, one lane per key");
     constexpr int K = kWave / TPK;
     constexpr int U = 8;  // entries per iteration (one 16-byte chunk)
@@ -1852,7 +1870,7 @@ __global__ __launch_bounds__(kBlock) void k_force(Dev d, Params p) {
 // compare and a select); f(rc) rounds to a few 1e-9 in FP32.
 template <int MODE, bool ENERGY, bool CLAMP>
 __global__ __launch_bounds__(kRtBlock) void k_force_t(Dev d, Params p) {
-    if (halted(d)) return;
+    if (step_off(d)) return;
     constexpr int NW = kRtBlock / kWave;  // wavefronts per block
     constexpr int U = 8;       // entries per 16-byte list chunk
     constexpr int kPc = 27;    // pieces of a staged region
@@ -2095,7 +2113,7 @@ struct D3 {
 };
 template <int MODE, bool ENERGY>
 __global__ __launch_bounds__(kRtBlock) void k_force_t64(Dev d, Params p) {
-    if (halted(d)) return;
+    if (step_off(d)) return;
     constexpr int NW = kRtBlock / kWave;
     constexpr int U = 8, kPc = 27, kCopy = 4;
     extern __shared__ D3 stg64[];  // p.scap records of 24 bytes
@@ -2311,7 +2329,7 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t64(Dev d, Params p) {
 // Half-list steps: F is accumulated by atomics, so the integrator runs as its own
 // pass after the force pass.  k_zero_f clears F before the force pass.
 __global__ __launch_bounds__(kBlock) void k_zero_f(Dev d, Params p) {
-    if (halted(d)) return;
+    if (step_off(d)) return;
     const int n = p.nwave * kWave;
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
         d.fx[i] = 0.0;
@@ -2324,7 +2342,7 @@ __global__ __launch_bounds__(kBlock) void k_zero_f(Dev d, Params p) {
 // of the kicked velocities (one lane per key, so list waves are slot waves).
 template <bool ENERGY>
 __global__ __launch_bounds__(kBlock) void k_kick_close(Dev d, Params p) {
-    if (halted(d)) return;
+    if (step_off(d)) return;
     const int l = lane_id();
     for (int w = blockIdx.x * 4 + wave_in_block(); w < p.nwave; w += gridDim.x * 4) {
         const int b = ld_const(d.wave_box + w);
@@ -2353,7 +2371,7 @@ __global__ __launch_bounds__(kBlock) void k_kick_close(Dev d, Params p) {
 // first, with the same forces, as the fused full-list pass does.
 template <bool CLOSE>
 __global__ __launch_bounds__(kBlock) void k_kick_drift(Dev d, Params p) {
-    if (halted(d)) return;
+    if (step_off(d)) return;
     const int l = lane_id();
     for (int w = blockIdx.x * 4 + wave_in_block(); w < p.nwave; w += gridDim.x * 4) {
         const int b = ld_const(d.wave_box + w);
@@ -2435,7 +2453,7 @@ __device__ __forceinline__ void part_range(const Dev& d, const Params& p, const 
 }
 
 __global__ __launch_bounds__(kBlock) void k_energy_segments(Dev d, Params p, int tl) {
-    if (halted(d)) return;
+    if (step_off(d)) return;
     const int b = blockIdx.y, j = blockIdx.x;
     const BoxGeom& g = d.geom[b];
     int w0, w1;
@@ -2458,7 +2476,7 @@ __global__ __launch_bounds__(kBlock) void k_energy_segments(Dev d, Params p, int
 }
 
 __global__ __launch_bounds__(kBlock) void k_energy_reduce(Dev d, Params p, int record, int thermo, int tl) {
-    if (halted(d)) return;
+    if (step_off(d)) return;
     for (int b = blockIdx.x; b < p.nbox; b += gridDim.x) {
         const BoxGeom& g = d.geom[b];
         int w0, w1;
@@ -2514,7 +2532,7 @@ __global__ __launch_bounds__(kBlock) void k_energy_reduce(Dev d, Params p, int r
 // KE partials of the current velocities, in the per-list-wave layout the
 // reduction reads (a slot wave's sum in its first list wave, zeros in the others).
 __global__ __launch_bounds__(kBlock) void k_ke_partial(Dev d, Params p) {
-    if (halted(d)) return;
+    if (step_off(d)) return;
     const int l = lane_id();
     for (int w = blockIdx.x * 4 + wave_in_block(); w < p.nwave; w += gridDim.x * 4) {
         const int b = ld_const(d.wave_box + w);
@@ -2533,7 +2551,7 @@ __global__ __launch_bounds__(kBlock) void k_ke_partial(Dev d, Params p) {
 
 // Apply the pending thermostat factor to the velocities (end of a run of steps).
 __global__ __launch_bounds__(kBlock) void k_vscale(Dev d, Params p) {
-    if (halted(d)) return;
+    if (step_off(d)) return;
     const int l = lane_id();
     for (int w = blockIdx.x * 4 + wave_in_block(); w < p.nwave; w += gridDim.x * 4) {
         const int b = ld_const(d.wave_box + w);
@@ -2843,8 +2861,8 @@ void launch_force(const Dev& d, const Params& p, int mode, bool energy, hipStrea
 void launch_kick_drift(const Dev& d, const Params& p, hipStream_t s) {
     k_kick_drift<false><<<(p.nwave + 3) / 4, kBlock, 0, s>>>(d, p);
 }
-void launch_dutc(const Dev& d, const Params& p, hipStream_t s) {
-    k_dutc<<<p.nbox < 1024 ? p.nbox : 1024, kBlock, 0, s>>>(d, p);
+void launch_dutc(const Dev& d, const Params& p, uint32_t seq, hipStream_t s) {
+    k_dutc<<<p.nbox < 1024 ? p.nbox : 1024, kBlock, 0, s>>>(d, p, seq);
 }
 void launch_energy_reduce(const Dev& d, const Params& p, bool record, int thermo, bool tl, hipStream_t s) {
     const int nparts = tl ? p.maxcell : p.maxslot / kWave * p.tpk;  // a box has at most one row tile per cell
