@@ -520,9 +520,7 @@ void free_all(md_ctx* c) {
     c->bw_alloc = 0;
     if (c->st_h) (void)hipHostFree(c->st_h);
     c->st_h = nullptr;
-    if (c->told_h) (void)hipHostFree(c->told_h);
-    c->told_h = nullptr;
-    D.told = nullptr;
+    c->told_h = D.told = nullptr;
     for (hipEvent_t e : c->ev_force) (void)hipEventDestroy(e);
     for (hipEvent_t e : c->ev_rebuild) (void)hipEventDestroy(e);
     c->ev_force.clear();
@@ -561,7 +559,7 @@ md_status alloc_all(md_ctx* c) {
     A(D.vmax_s, (size_t)c->nbox * kStripes * kStripeStride);
     A(D.disp_s, (size_t)c->nbox * kStripes * kStripeStride);
     A(D.need_s, (size_t)c->nbox * kNeedStripes * kNeedStride);
-    A(D.ntiles, 2);
+    A(D.ntiles, kPostStride * (2 + kPostGroups));
     A(D.box_t0, (size_t)c->nbox + 1);
     A(D.dshift, (size_t)27 * c->nbox);
     A(D.series_ke, (size_t)kMaxSeries * c->nbox);
@@ -574,15 +572,16 @@ md_status alloc_all(md_ctx* c) {
     HIPCHK(c, hipMemsetAsync(D.any, 0, sizeof(int32_t), c->stream));
     HIPCHK(c, hipMemsetAsync(D.halt, 0, sizeof(int32_t), c->stream));
     HIPCHK(c, hipMemsetAsync(D.need_s, 0, sizeof(int32_t) * c->nbox * kNeedStripes * kNeedStride, c->stream));
-    HIPCHK(c, hipMemsetAsync(D.ntiles, 0, 2 * sizeof(int32_t), c->stream));
+    HIPCHK(c, hipMemsetAsync(D.ntiles, 0, kPostStride * (2 + kPostGroups) * sizeof(int32_t), c->stream));
     HIPCHK(c, hipMemsetAsync(D.vmax_s, 0, sizeof(unsigned long long) * c->nbox * kStripes * kStripeStride, c->stream));
     HIPCHK(c, hipMemsetAsync(D.disp_s, 0, sizeof(unsigned long long) * c->nbox * kStripes * kStripeStride, c->stream));
-    HIPCHK(c, hipHostMalloc((void**)&c->st_h, sizeof(BoxState) * c->nbox, hipHostMallocDefault));
-    std::memset(c->st_h, 0, sizeof(BoxState) * c->nbox);
-    for (int b = 0; b < c->nbox; ++b) c->st_h[b].vscale = 1.0;
-    HIPCHK(c, hipHostMalloc((void**)&c->told_h, sizeof(uint32_t) * kToldRing, hipHostMallocDefault));
-    std::memset(c->told_h, 0, sizeof(uint32_t) * kToldRing);
+    // one pinned allocation: the states' mirror, then the decision ring
+    const size_t st_bytes = (sizeof(BoxState) * c->nbox + 255) / 256 * 256;
+    HIPCHK(c, hipHostMalloc((void**)&c->st_h, st_bytes + sizeof(uint32_t) * kToldRing, hipHostMallocDefault));
+    std::memset((void*)c->st_h, 0, st_bytes + sizeof(uint32_t) * kToldRing);
+    c->told_h = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(c->st_h) + st_bytes);
     HIPCHK(c, hipHostGetDevicePointer((void**)&D.told, c->told_h, 0));
+    for (int b = 0; b < c->nbox; ++b) c->st_h[b].vscale = 1.0;
     return MD_OK;
 }
 
@@ -745,9 +744,9 @@ uint32_t next_seq(md_ctx* c) {
 md_status enqueue_ahead(md_ctx* c, int32_t chunk, int32_t done, int32_t energy_every, bool thermo, bool opened) {
     md_status s;
     const int ahead = c->ntotal < 262144 ? 2 : 1;
-    std::vector<uint32_t> opening(chunk + 2, 0);  // drift that opens step k
-    std::vector<size_t> mark(chunk + 2, 0);       // timing events before step k
-    int known = 0;                                // openings decided (and their builds enqueued)
+    uint32_t opening[kChunk + 2] = {};  // drift that opens step k
+    size_t mark[kChunk + 2] = {};       // timing events before step k
+    int known = 0;                      // openings decided (and their builds enqueued)
     if (!opened) {
         if (thermo) {
             launch_ke_partial(c->D, c->P, c->stream);

@@ -55,8 +55,13 @@ constexpr int kUnitBits = 28;            // fixed-point units per cell side: at 
 constexpr int kUnitClamp = 1 << 29;      // |u| bound (two cell sides): pair sums stay in int32
 constexpr int kOffBits = 11;             // list entry: partner rank within its cell
 constexpr int kMaxCellCount = 1 << kOffBits;
-constexpr int kStripes = 1024;           // slots per box for per-step maxima
+constexpr int kStripes = kBlock;          // slots per box for per-step maxima
 constexpr int kStripeStride = 16;        // 128 bytes between slots
+constexpr int kSortBlock = 1024;         // threads per block of the one-block-per-box sort
+constexpr int kSortSlots = 16384;        // slots, and
+constexpr int kSortCells = 12288;        // cells (48 KB of LDS), of the boxes it serves
+constexpr int kPostGroups = 16;          // counters of the post-build kernel's blocks
+constexpr int kPostStride = 16;          // 64 bytes between them
 constexpr int kToldRing = 64;            // rebuild decisions in flight to the host (a power of two)
 constexpr int kNeedStripes = 256;        // slots per box for the longest list of a build
 constexpr int kNeedStride = 16;          // 64 bytes between slots
@@ -185,7 +190,8 @@ struct Dev {
     int32_t* row_box;    // box of each global row
     int32_t* row_nt;     // row tiles per row
     int32_t* row_t0;     // first row tile of each row (exclusive scan of row_nt)
-    int32_t* ntiles;     // [0] row tiles in all, [1] blocks of the post-build kernel done (the last resets it)
+    int32_t* ntiles;     // [0] row tiles in all; then the post-build kernel's counters at stride kPostStride:
+                         // groups done, blocks done per group (the last to count resets each)
     int32_t* box_t0;     // [nbox + 1] first row tile of each box, then the total
     int32_t* cell_rt;    // row tile of each cell
     int32_t* rt_tmp;     // per cell: xa | xb << 16 of the row's k-th tile at (row's first cell + k)

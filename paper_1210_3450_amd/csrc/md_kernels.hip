@@ -391,23 +391,18 @@ __global__ void k_mark_rebuild(Dev d, Params p) {
 }
 
 // Max over a box's striped partial maxima (bit patterns of non-negative doubles),
-// clearing the stripes for the next step.  One block per box.
+// clearing the stripes for the next step.  One block per box, a thread per stripe.
 __device__ double stripe_max(unsigned long long* stripes) {
-    __shared__ double red[kBlock];
-    double m = 0.0;
-    for (int k = threadIdx.x; k < kStripes; k += kBlock) {
-        unsigned long long* a = stripes + (size_t)k * kStripeStride;
-        m = fmax(m, __longlong_as_double((long long)*a));
-        *a = 0ull;
-    }
-    red[threadIdx.x] = m;
+    static_assert(kStripes == kBlock, "one thread per stripe");
+    __shared__ double red[kBlock / kWave];
+    unsigned long long* a = stripes + (size_t)threadIdx.x * kStripeStride;
+    const double m = wave_max(__longlong_as_double((long long)*a));
+    *a = 0ull;
+    __syncthreads();  // red of an earlier call has been read
+    if (lane_id() == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
-    for (int o = kBlock / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + o]);
-        __syncthreads();
-    }
-    const double r = red[0];
-    __syncthreads();
+    double r = red[0];
+    for (int w = 1; w < kBlock / kWave; ++w) r = fmax(r, red[w]);
     return r;
 }
 
@@ -445,7 +440,7 @@ __global__ __launch_bounds__(kBlock) void k_dutc(Dev d, Params p, uint32_t seq) 
             else if (p.policy == MD_REBUILD_EVERY_STEP)
                 rb = 1;
             st.rebuild = rb;
-            if (rb) atomicOr(d.any, 1);
+            if (rb) *d.any = 1;  // a plain store: 40 boxes' atomics on one word took 7 us
             tell(rb ? 1u : 0u);
         }
     }
@@ -457,7 +452,6 @@ __global__ __launch_bounds__(kBlock) void k_dutc(Dev d, Params p, uint32_t seq) 
 // positions are in buffer sq ^ 1: the list build reads them there.)
 __global__ __launch_bounds__(kBlock) void k_post_build(Dev d, Params p, int with_list) {
     __shared__ int red[kBlock / kWave];
-    __shared__ int last;
     if (!*d.any || halted(d)) return;
     const int l = lane_id(), wv = wave_in_block();
     for (int b = blockIdx.x; b < p.nbox; b += gridDim.x) {  // one block per box
@@ -483,14 +477,21 @@ __global__ __launch_bounds__(kBlock) void k_post_build(Dev d, Params p, int with
         }
         __syncthreads();
     }
-    // the last block to finish clears the gate (every block has read it by then)
-    __threadfence();
+    // the last block to count clears the gate: every block has read it by then.  No fence: the
+    // stores above are for later kernels, and a fence here writes back the L2 (256 boxes: 20 us).
+    // Blocks count themselves in groups, then the groups, since atomics on one word take 0.18 us each.
     __syncthreads();
-    if (threadIdx.x == 0) last = atomicAdd(d.ntiles + 1, 1) == (int)gridDim.x - 1;
-    __syncthreads();
-    if (last && threadIdx.x == 0) {
-        d.ntiles[1] = 0;
-        *d.any = 0;
+    if (threadIdx.x == 0) {
+        const int ng = min((int)gridDim.x, kPostGroups), gi = (int)blockIdx.x % kPostGroups;
+        int* mine = d.ntiles + kPostStride * (2 + gi);
+        int* all = d.ntiles + kPostStride;
+        if (atomicAdd(mine, 1) == ((int)gridDim.x - gi + kPostGroups - 1) / kPostGroups - 1) {
+            *mine = 0;
+            if (atomicAdd(all, 1) == ng - 1) {
+                *all = 0;
+                *d.any = 0;
+            }
+        }
     }
 }
 
@@ -610,6 +611,76 @@ __global__ __launch_bounds__(kBlock) void k_scatter(Dev d, Params p) {
         const int s = w * kWave + l;
         if (s - g.slot_off >= g.npart) continue;
         d.perm[d.cell_start[g.cell_off + d.cell_tmp[s]] + d.ticket[s]] = s;
+    }
+}
+
+// The steps from k_cell_clear to k_scatter for boxes of up to kSortSlots slots and
+// kSortCells cells, one block per box with its cell counters in LDS.  There the six launches
+// are mostly launch and drain: 4.5 us each, against 6.8 us for this one at 4000 particles.
+// Its time grows with the box, 32 us at 32,000 particles; an ensemble with boxes of up to
+// 65,536 took 80 us a step against 43 us.
+__global__ __launch_bounds__(kSortBlock) void k_sort_box(Dev d, Params p) {
+    if (!ld_const(d.any) || halted(d)) return;  // no box rebuilds this step, or a build overflowed
+    extern __shared__ int cnt[];                // counters, then first slots, of the box's cells
+    __shared__ int wsum[kSortBlock / kWave];
+    constexpr int U = 4;                        // positions in flight per thread
+    const int tid = threadIdx.x, l = lane_id(), wv = wave_in_block();
+    for (int b = blockIdx.x; b < p.nbox; b += gridDim.x) {
+        if (!ld_const(&d.st[b].rebuild)) continue;  // uniform over the block
+        const BoxGeom g = ld_geom(d.geom + b);
+        Pos* __restrict__ q = d.q[ld_const(&d.st[b].sq)] + g.slot_off;
+        int32_t* __restrict__ cell_tmp = d.cell_tmp + g.slot_off;
+        int32_t* __restrict__ ticket = d.ticket + g.slot_off;
+        for (int c = tid; c < g.ncell; c += kSortBlock) cnt[c] = 0;
+        for (int k = tid; k < kNeedStripes; k += kSortBlock)
+            d.need_s[((size_t)b * kNeedStripes + k) * kNeedStride] = 0;
+        __syncthreads();
+        bool bad = false;
+        for (int s0 = tid; s0 < g.npart; s0 += U * kSortBlock) {
+            Pos x[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) x[k] = q[min(s0 + k * kSortBlock, g.npart - 1)];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int s = s0 + k * kSortBlock;
+                if (s >= g.npart) break;
+                const double x0 = x[k].x, y0 = x[k].y, z0 = x[k].z;
+                const int cx = bin_axis(x[k].x, g.L[0], g.inv[0], g.n[0], bad);
+                const int cy = bin_axis(x[k].y, g.L[1], g.inv[1], g.n[1], bad);
+                const int cz = bin_axis(x[k].z, g.L[2], g.inv[2], g.n[2], bad);
+                // only particles that crossed the box boundary change: write those back
+                if (x[k].x != x0 || x[k].y != y0 || x[k].z != z0) {
+                    q[s].x = x[k].x;
+                    q[s].y = x[k].y;
+                    q[s].z = x[k].z;
+                }
+                const int cid = (cz * g.n[1] + cy) * g.n[0] + cx;
+                cell_tmp[s] = cid;
+                ticket[s] = atomicAdd(&cnt[cid], 1);
+            }
+        }
+        if (bad) atomicOr(&d.st[b].err, 1);
+        __syncthreads();
+        // exclusive scan, a run of cells per thread
+        const int per = (g.ncell + kSortBlock - 1) / kSortBlock, c0 = min(tid * per, g.ncell),
+                  c1 = min(c0 + per, g.ncell);
+        int sum = 0;
+        for (int c = c0; c < c1; ++c) sum += cnt[c];
+        const int incl = wave_incl_sum(sum);
+        if (l == kWave - 1) wsum[wv] = incl;
+        __syncthreads();
+        int run = g.slot_off + incl - sum;
+        for (int w = 0; w < wv; ++w) run += wsum[w];
+        for (int c = c0; c < c1; ++c) {
+            const int m = cnt[c];
+            d.cell_cnt[g.cell_off + c] = m;
+            d.cell_start[g.cell_off + c] = run;
+            cnt[c] = run;
+            run += m;
+        }
+        __syncthreads();
+        for (int s = tid; s < g.npart; s += kSortBlock) d.perm[cnt[cell_tmp[s]] + ticket[s]] = g.slot_off + s;
+        __syncthreads();  // the next box clears the counters
     }
 }
 
@@ -2475,7 +2546,8 @@ __global__ __launch_bounds__(kBlock) void k_energy_segments(Dev d, Params p, int
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_energy_reduce(Dev d, Params p, int record, int thermo, int tl) {
+__global__ __launch_bounds__(kBlock) void k_energy_reduce(Dev d, Params p, int record, int thermo, int tl,
+                                                            int one) {
     if (step_off(d)) return;
     for (int b = blockIdx.x; b < p.nbox; b += gridDim.x) {
         const BoxGeom& g = d.geom[b];
@@ -2483,11 +2555,19 @@ __global__ __launch_bounds__(kBlock) void k_energy_reduce(Dev d, Params p, int r
         part_range(d, p, g, b, tl, w0, w1);
         const int nseg = (w1 - w0 + kRedSeg - 1) / kRedSeg;
         double k = 0.0, e = 0.0, v = 0.0;
-        for (int j = threadIdx.x; j < nseg; j += kBlock) {
-            const double* r = d.red + ((size_t)b * p.redcap + j) * 3;
-            k += r[0];
-            e += r[1];
-            v += r[2];
+        if (one) {  // every box has one segment: summed here as k_energy_segments sums it
+            for (int w = w0 + threadIdx.x; w < w1; w += kBlock) {
+                k += d.ke_part[w];
+                e += d.pe_part[w];
+                v += d.vir_part[w];
+            }
+        } else {
+            for (int j = threadIdx.x; j < nseg; j += kBlock) {
+                const double* r = d.red + ((size_t)b * p.redcap + j) * 3;
+                k += r[0];
+                e += r[1];
+                v += r[2];
+            }
         }
         block_sum3(k, e, v);
         if (threadIdx.x == 0) {
@@ -2724,14 +2804,19 @@ void launch_row_tiles(const Dev& d, const Params& p, hipStream_t s) {
 
 void launch_rebuild_chain(const Dev& d, const Params& p, bool with_list, hipStream_t s) {
     const int gw = grid_for_waves(p.nwave);
-    const int gt = p.ntile < 4096 ? p.ntile : 4096;
-    k_cell_clear<<<gt, kBlock, 0, s>>>(d, p);
-    k_bin<<<gw, kBlock, 0, s>>>(d, p);
-    k_scan_tile<<<gt, kBlock, 0, s>>>(d, p);
-    k_scan_box<<<p.nbox < 1024 ? p.nbox : 1024, kBlock, 0, s>>>(d, p);
-    k_scan_add<<<gt, kBlock, 0, s>>>(d, p);
-    if (p.tile) launch_row_tiles(d, p, s);
-    k_scatter<<<gw, kBlock, 0, s>>>(d, p);
+    if (p.maxslot <= kSortSlots && p.maxcell <= kSortCells) {
+        k_sort_box<<<p.nbox < 1024 ? p.nbox : 1024, kSortBlock, sizeof(int) * p.maxcell, s>>>(d, p);
+        if (p.tile) launch_row_tiles(d, p, s);
+    } else {
+        const int gt = p.ntile < 4096 ? p.ntile : 4096;
+        k_cell_clear<<<gt, kBlock, 0, s>>>(d, p);
+        k_bin<<<gw, kBlock, 0, s>>>(d, p);
+        k_scan_tile<<<gt, kBlock, 0, s>>>(d, p);
+        k_scan_box<<<p.nbox < 1024 ? p.nbox : 1024, kBlock, 0, s>>>(d, p);
+        k_scan_add<<<gt, kBlock, 0, s>>>(d, p);
+        if (p.tile) launch_row_tiles(d, p, s);
+        k_scatter<<<gw, kBlock, 0, s>>>(d, p);
+    }
     k_rank_permute<<<gw, kBlock, 0, s>>>(d, p);
     if (with_list) launch_list(d, p, s);
     k_post_build<<<p.nbox < 1024 ? p.nbox : 1024, kBlock, 0, s>>>(d, p, with_list ? 1 : 0);
@@ -2867,8 +2952,10 @@ void launch_dutc(const Dev& d, const Params& p, uint32_t seq, hipStream_t s) {
 void launch_energy_reduce(const Dev& d, const Params& p, bool record, int thermo, bool tl, hipStream_t s) {
     const int nparts = tl ? p.maxcell : p.maxslot / kWave * p.tpk;  // a box has at most one row tile per cell
     const int nseg = (nparts + kRedSeg - 1) / kRedSeg;
-    k_energy_segments<<<dim3(nseg, p.nbox), kBlock, 0, s>>>(d, p, tl ? 1 : 0);
-    k_energy_reduce<<<p.nbox < 1024 ? p.nbox : 1024, kBlock, 0, s>>>(d, p, record ? 1 : 0, thermo, tl ? 1 : 0);
+    // at most kRedSeg partials per box: one launch instead of two
+    if (nseg > 1) k_energy_segments<<<dim3(nseg, p.nbox), kBlock, 0, s>>>(d, p, tl ? 1 : 0);
+    k_energy_reduce<<<p.nbox < 1024 ? p.nbox : 1024, kBlock, 0, s>>>(d, p, record ? 1 : 0, thermo, tl ? 1 : 0,
+                                                                    nseg > 1 ? 0 : 1);
 }
 void launch_ke_partial(const Dev& d, const Params& p, hipStream_t s) {
     k_ke_partial<<<grid_for_waves(p.nwave), kBlock, 0, s>>>(d, p);
