@@ -288,7 +288,7 @@ typedef struct {
  * MD_EINVAL: bad box index, side not finite or <= 0, rho_gas not finite or
  * < 0, fewer than 1 or more than 1024 subcells on an axis, info NULL.
  * MD_ESTATE without a state; MD_ENUMERIC for a position outside [-L, 2L).
- * Work buffers (about 17 bytes per subcell) are allocated on the first call and
+ * Work buffers (about 24 bytes per subcell) are allocated on the first call and
  * grown when needed.  Synchronizing. */
 md_status md_bubbles(md_ctx *ctx, int32_t box, double side, double rho_gas, uint8_t *counts,
                      int32_t *labels, int64_t *roots, int64_t *sizes, int64_t cap,

@@ -516,7 +516,9 @@ void free_all(md_ctx* c) {
     dfree(c->bw.lab);
     dfree(c->bw.size);
     dfree(c->bw.roots);
-    dfree(c->bw.flag);
+    dfree(c->bw.segcnt);
+    dfree(c->bw.segoff);
+    dfree(c->bw.misc);
     c->bw_alloc = 0;
     if (c->st_h) (void)hipHostFree(c->st_h);
     c->st_h = nullptr;
@@ -1355,37 +1357,35 @@ md_status md_bubbles(md_ctx* c, int32_t box, double side, double rho_gas, uint8_
         dfree(c->bw.lab);
         dfree(c->bw.size);
         dfree(c->bw.roots);
-        dfree(c->bw.flag);
+        dfree(c->bw.segcnt);
+        dfree(c->bw.segoff);
+        dfree(c->bw.misc);
         c->bw_alloc = 0;
+        const int64_t nseg = (nsub + kNaSeg - 1) / kNaSeg;
         if ((s = dalloc(c, &c->bw.cnt, nsub)) != MD_OK || (s = dalloc(c, &c->bw.par, nsub)) != MD_OK ||
             (s = dalloc(c, &c->bw.lab, nsub)) != MD_OK || (s = dalloc(c, &c->bw.size, nsub)) != MD_OK ||
-            (s = dalloc(c, &c->bw.roots, nsub)) != MD_OK || (s = dalloc(c, &c->bw.flag, 2)) != MD_OK)
+            (s = dalloc(c, &c->bw.roots, nsub)) != MD_OK || (s = dalloc(c, &c->bw.segcnt, nseg)) != MD_OK ||
+            (s = dalloc(c, &c->bw.segoff, nseg)) != MD_OK || (s = dalloc(c, &c->bw.misc, 1)) != MD_OK)
             return s;
         c->bw_alloc = nsub;
     }
-    HIPCHK(c, hipMemsetAsync(c->bw.cnt, 0, sizeof(uint32_t) * nsub, c->stream));
-    HIPCHK(c, hipMemsetAsync(c->bw.flag, 0, sizeof(int32_t) * 2, c->stream));
     launch_bubbles(c->D, box, c->geom[box].npart, sg, c->bw, counts, c->stream);
     LAUNCHCHK(c);
     if (labels)
         HIPCHK(c, hipMemcpyAsync(labels, c->bw.lab, sizeof(int32_t) * nsub, hipMemcpyDeviceToDevice, c->stream));
-    int32_t flag[2] = {0, 0};
-    HIPCHK(c, hipMemcpyAsync(flag, c->bw.flag, sizeof flag, hipMemcpyDeviceToHost, c->stream));
+    NaMisc m{};
+    HIPCHK(c, hipMemcpyAsync(&m, c->bw.misc, sizeof m, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    if (flag[0]) return fail(c, MD_ENUMERIC, "box %d: a position is not finite or lies outside [-L, 2L)", box);
-    std::vector<int2> rs((size_t)flag[1]);
-    if (flag[1] > 0) {
-        HIPCHK(c, hipMemcpy(rs.data(), c->bw.roots, sizeof(int2) * rs.size(), hipMemcpyDeviceToHost));
-        std::sort(rs.begin(), rs.end(), [](const int2& a, const int2& b) { return a.x < b.x; });
-    }
-    int64_t ngas = 0, largest = 0;
-    for (const int2& r : rs) {
-        ngas += r.y;
-        largest = std::max<int64_t>(largest, r.y);
-    }
-    for (int64_t k = 0; k < cap && k < (int64_t)rs.size(); ++k) {
-        roots[k] = rs[k].x;
-        sizes[k] = rs[k].y;
+    if (m.bad) return fail(c, MD_ENUMERIC, "box %d: a position is not finite or lies outside [-L, 2L)", box);
+    const int64_t k = std::min<int64_t>(cap, m.nroots);
+    if (k > 0) {
+        std::vector<int2> rs((size_t)k);
+        HIPCHK(c, hipMemcpyAsync(rs.data(), c->bw.roots, sizeof(int2) * k, hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        for (int64_t j = 0; j < k; ++j) {
+            roots[j] = rs[j].x;
+            sizes[j] = rs[j].y;
+        }
     }
     *info = md_bubble_info{};
     for (int a = 0; a < 3; ++a) {
@@ -1393,9 +1393,9 @@ md_status md_bubbles(md_ctx* c, int32_t box, double side, double rho_gas, uint8_
         info->side[a] = L[a] / sg.n[a];
     }
     info->threshold = sg.thr;
-    info->ngas = ngas;
-    info->nbubbles = (int64_t)rs.size();
-    info->largest = largest;
+    info->ngas = (int64_t)m.ngas;
+    info->nbubbles = m.nroots;
+    info->largest = m.largest;
     return MD_OK;
 }
 
@@ -1492,15 +1492,14 @@ md_status md_get_neighbors(md_ctx* c, int64_t* key_ptr, int32_t* partners, int64
     if (!key_ptr) return fail(c, MD_EINVAL, "key_ptr must be a device array [n + 1]");
     launch_list_counts(c->D, c->P, key_ptr + 1, c->nwave, c->stream);
     LAUNCHCHK(c);
-    std::vector<int64_t> kp(c->ntotal + 1, 0);
-    HIPCHK(c, hipMemcpyAsync(kp.data() + 1, key_ptr + 1, sizeof(int64_t) * c->ntotal, hipMemcpyDeviceToHost,
-                             c->stream));
+    launch_list_ptr(c->D, c->ntotal, key_ptr, c->stream);
+    LAUNCHCHK(c);
+    int64_t all = 0;
+    HIPCHK(c, hipMemcpyAsync(&all, key_ptr + c->ntotal, sizeof all, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    for (int64_t i = 0; i < c->ntotal; ++i) kp[i + 1] += kp[i];
-    HIPCHK(c, hipMemcpy(key_ptr, kp.data(), sizeof(int64_t) * kp.size(), hipMemcpyHostToDevice));
-    if (total) *total = kp[c->ntotal];
-    if (kp[c->ntotal] > cap) return fail(c, MD_EINVAL, "partners capacity %lld < %lld entries", (long long)cap,
-                                         (long long)kp[c->ntotal]);
+    if (total) *total = all;
+    if (all > cap)
+        return fail(c, MD_EINVAL, "partners capacity %lld < %lld entries", (long long)cap, (long long)all);
     if (!partners) return fail(c, MD_EINVAL, "partners must be a device array");
     launch_list_export(c->D, c->P, key_ptr, partners, c->nwave, c->stream);
     LAUNCHCHK(c);

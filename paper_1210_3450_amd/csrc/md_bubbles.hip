@@ -14,12 +14,11 @@
 //                always point to a smaller index, so a bubble's final root is
 //                its smallest subcell index
 //   k_sub_label  label = root (path halving on the way), sizes by atomics
-//   k_sub_roots  compacts (root, size) pairs; the host sorts them by root
+//   k_na_seg*    ordered compaction of the roots: counts per segment, a one-block scan,
+//                write-out in subcell order, so the bubbles arrive sorted
 //
-// md_bubbles_noalloc runs the same count / flag / hook / label kernels on a
-// fixed device array instead of allocated buffers and replaces the last step by
-// an ordered compaction (root counts per segment, one-block scan, write-out in
-// subcell order), so the bubbles arrive sorted without a host-side buffer.
+// md_bubbles_noalloc runs the same kernels on a fixed device array instead of
+// allocated buffers.
 //
 // Union-find on the GPU after the published lock-free scheme of linking a root
 // to a smaller root with compare-and-swap and compressing paths with plain
@@ -128,14 +127,25 @@ __global__ __launch_bounds__(kBlock) void k_sub_label(SubGrid sg, int32_t* __res
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_sub_roots(SubGrid sg, const int32_t* __restrict__ lab,
-                                                      const int32_t* __restrict__ size, int2* __restrict__ out,
-                                                      int32_t* __restrict__ count) {
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < sg.nsub; i += gridDim.x * kBlock) {
-        if (lab[i] != i) continue;
-        const int32_t k = atomicAdd(count, 1);  // < nsub: at most one entry per subcell
-        out[k] = make_int2(i, size[i]);
+// Exclusive scan across a block; *total gets the block sum.
+__device__ __forceinline__ int seg_scan(int v, int* total) {
+    __shared__ int ws[kBlock / kWave];
+    const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int incl = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int t = __shfl_up(incl, o);
+        if (l >= o) incl += t;
     }
+    if (l == 63) ws[w] = incl;
+    __syncthreads();
+    int off = 0, tot = 0;
+    for (int k = 0; k < kBlock / kWave; ++k) {
+        if (k < w) off += ws[k];
+        tot += ws[k];
+    }
+    __syncthreads();
+    *total = tot;
+    return off + incl - v;
 }
 
 // ---------------------------------------------------------------- fixed scratch
@@ -158,7 +168,6 @@ constexpr size_t kNaSegOff = kNaSegCnt + 4 * (size_t)kNaSegs;
 constexpr size_t kNaMisc = kNaSegOff + 4 * (size_t)kNaSegs;
 constexpr size_t kNaBytes = kNaMisc + sizeof(NaMisc);
 static_assert(kNaMaxSub % kNaSeg == 0, "whole segments");
-static_assert(kNaSegs <= kBlock * 4, "one block scans the segment counts");
 
 static __device__ __align__(256) unsigned char scratch[kNaBytes];
 
@@ -190,8 +199,10 @@ BubbleWork bubbles_scratch_work(unsigned char* base) {
     w.par = reinterpret_cast<int32_t*>(base + kNaPar);
     w.lab = reinterpret_cast<int32_t*>(base + kNaLab);
     w.size = reinterpret_cast<int32_t*>(base + kNaSize);
-    w.roots = nullptr;  // the ordered compaction writes root / rsize instead
-    w.flag = reinterpret_cast<int32_t*>(base + kNaMisc);  // NaMisc::bad
+    w.roots = nullptr;  // root / rsize instead
+    w.segcnt = reinterpret_cast<int32_t*>(base + kNaSegCnt);
+    w.segoff = reinterpret_cast<int32_t*>(base + kNaSegOff);
+    w.misc = reinterpret_cast<NaMisc*>(base + kNaMisc);
     return w;
 }
 
@@ -207,7 +218,6 @@ __global__ __launch_bounds__(kBlock) void k_na_clear(uint32_t* __restrict__ cnt,
 __global__ __launch_bounds__(kBlock) void k_na_segcount(SubGrid sg, const int32_t* __restrict__ lab,
                                                         const int32_t* __restrict__ size,
                                                         int32_t* __restrict__ segcnt, NaMisc* misc) {
-    __shared__ int red[kBlock];
     const int s = blockIdx.x;
     const int i0 = s * kNaSeg, i1 = min(i0 + kNaSeg, sg.nsub);
     int nr = 0, ng = 0, big = 0;
@@ -219,54 +229,40 @@ __global__ __launch_bounds__(kBlock) void k_na_segcount(SubGrid sg, const int32_
             big = max(big, size[i]);
         }
     }
-    red[threadIdx.x] = nr;
-    __syncthreads();
-    for (int o = kBlock / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
+    int tot;
+    seg_scan(nr, &tot);
+    if (threadIdx.x == 0) segcnt[s] = tot;
+    for (int o = 32; o > 0; o >>= 1) {  // one atomic per wavefront
+        ng += __shfl_xor(ng, o);
+        big = max(big, __shfl_xor(big, o));
     }
-    if (threadIdx.x == 0) segcnt[s] = red[0];
-    if (ng) atomicAdd(&misc->ngas, (unsigned long long)ng);
-    if (big) atomicMax(&misc->largest, big);
+    if ((threadIdx.x & 63) == 0) {
+        if (ng) atomicAdd(&misc->ngas, (unsigned long long)ng);
+        if (big) atomicMax(&misc->largest, big);
+    }
 }
 
 // One block: exclusive scan of the segment counts; the total is the bubble count.
 __global__ __launch_bounds__(kBlock) void k_na_segscan(int32_t nseg, const int32_t* __restrict__ segcnt,
                                                        int32_t* __restrict__ segoff, NaMisc* misc) {
-    __shared__ int part[kBlock];
-    constexpr int kPer = 4;  // segments per thread (nseg <= kBlock * kPer)
-    int v[kPer], tot = 0;
-    for (int k = 0; k < kPer; ++k) {
-        const int j = threadIdx.x * kPer + k;
-        v[k] = j < nseg ? segcnt[j] : 0;
-        tot += v[k];
-    }
-    part[threadIdx.x] = tot;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int t = 0; t < kBlock; ++t) {
-            const int x = part[t];
-            part[t] = run;
-            run += x;
-        }
-        misc->nroots = run;
-    }
-    __syncthreads();
-    int run = part[threadIdx.x];
-    for (int k = 0; k < kPer; ++k) {
-        const int j = threadIdx.x * kPer + k;
-        if (j < nseg) segoff[j] = run;
-        run += v[k];
+    const int per = (nseg + kBlock - 1) / kBlock, j0 = min((int)threadIdx.x * per, nseg), j1 = min(j0 + per, nseg);
+    int tot = 0, all;
+    for (int j = j0; j < j1; ++j) tot += segcnt[j];
+    int run = seg_scan(tot, &all);
+    if (threadIdx.x == 0) misc->nroots = all;
+    for (int j = j0; j < j1; ++j) {
+        segoff[j] = run;
+        run += segcnt[j];
     }
 }
 
 // Roots of each segment in ascending subcell order at the segment's offset.
+// PAIR: as (root, size) pairs, else as two int64 arrays.
+template <bool PAIR>
 __global__ __launch_bounds__(kBlock) void k_na_segwrite(SubGrid sg, const int32_t* __restrict__ lab,
                                                         const int32_t* __restrict__ size,
-                                                        const int32_t* __restrict__ segoff,
+                                                        const int32_t* __restrict__ segoff, int2* __restrict__ pairs,
                                                         int64_t* __restrict__ root, int64_t* __restrict__ rsize) {
-    __shared__ int part[kBlock];
     constexpr int kPer = kNaSeg / kBlock;  // consecutive subcells per thread
     const int s = blockIdx.x;
     const int i0 = s * kNaSeg + threadIdx.x * kPer;
@@ -275,23 +271,17 @@ __global__ __launch_bounds__(kBlock) void k_na_segwrite(SubGrid sg, const int32_
         const int i = i0 + k;
         n += (i < sg.nsub && lab[i] == i) ? 1 : 0;
     }
-    part[threadIdx.x] = n;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int t = 0; t < kBlock; ++t) {
-            const int x = part[t];
-            part[t] = run;
-            run += x;
-        }
-    }
-    __syncthreads();
-    int at = segoff[s] + part[threadIdx.x];
+    int tot;
+    int at = segoff[s] + seg_scan(n, &tot);
     for (int k = 0; k < kPer; ++k) {
         const int i = i0 + k;
         if (i < sg.nsub && lab[i] == i) {
-            root[at] = i;
-            rsize[at] = size[i];
+            if (PAIR) {
+                pairs[at] = make_int2(i, size[i]);
+            } else {
+                root[at] = i;
+                rsize[at] = size[i];
+            }
             ++at;
         }
     }
@@ -302,31 +292,32 @@ static int grid_for(int64_t n) {
     return (int)(b < 1 ? 1 : (b > 16384 ? 16384 : b));
 }
 
-void launch_bubbles(const Dev& d, int32_t b, int32_t npart, const SubGrid& sg, const BubbleWork& w, uint8_t* bytes,
-                    hipStream_t s) {
-    k_sub_count<<<grid_for(npart), kBlock, 0, s>>>(d, b, sg, w.cnt, w.flag);
+static int bubble_steps(const Dev& d, int32_t b, int32_t npart, const SubGrid& sg, const BubbleWork& w, uint8_t* bytes,
+                        hipStream_t s) {
+    const int nseg = (sg.nsub + kNaSeg - 1) / kNaSeg;
+    k_na_clear<<<grid_for(sg.nsub), kBlock, 0, s>>>(w.cnt, sg.nsub, w.misc);
+    k_sub_count<<<grid_for(npart), kBlock, 0, s>>>(d, b, sg, w.cnt, &w.misc->bad);
     k_sub_flags<<<grid_for(sg.nsub), kBlock, 0, s>>>(sg, w.cnt, bytes, w.par, w.size);
     k_sub_hook<<<grid_for(sg.nsub), kBlock, 0, s>>>(sg, w.par);
     k_sub_label<<<grid_for(sg.nsub), kBlock, 0, s>>>(sg, w.par, w.lab, w.size);
-    k_sub_roots<<<grid_for(sg.nsub), kBlock, 0, s>>>(sg, w.lab, w.size, w.roots, w.flag + 1);
+    k_na_segcount<<<nseg, kBlock, 0, s>>>(sg, w.lab, w.size, w.segcnt, w.misc);
+    k_na_segscan<<<1, kBlock, 0, s>>>(nseg, w.segcnt, w.segoff, w.misc);
+    return nseg;
+}
+
+void launch_bubbles(const Dev& d, int32_t b, int32_t npart, const SubGrid& sg, const BubbleWork& w, uint8_t* bytes,
+                    hipStream_t s) {
+    const int nseg = bubble_steps(d, b, npart, sg, w, bytes, s);
+    k_na_segwrite<true><<<nseg, kBlock, 0, s>>>(sg, w.lab, w.size, w.segoff, w.roots, nullptr, nullptr);
 }
 
 void launch_bubbles_scratch(const Dev& d, int32_t b, int32_t npart, const SubGrid& sg, unsigned char* base,
                             uint8_t* bytes, hipStream_t s) {
     const BubbleWork w = bubbles_scratch_work(base);
-    NaMisc* misc = reinterpret_cast<NaMisc*>(base + kNaMisc);
-    int32_t* segcnt = reinterpret_cast<int32_t*>(base + kNaSegCnt);
-    int32_t* segoff = reinterpret_cast<int32_t*>(base + kNaSegOff);
-    const int nseg = (sg.nsub + kNaSeg - 1) / kNaSeg;
-    k_na_clear<<<grid_for(sg.nsub), kBlock, 0, s>>>(w.cnt, sg.nsub, misc);
-    k_sub_count<<<grid_for(npart), kBlock, 0, s>>>(d, b, sg, w.cnt, &misc->bad);
-    k_sub_flags<<<grid_for(sg.nsub), kBlock, 0, s>>>(sg, w.cnt, bytes, w.par, w.size);
-    k_sub_hook<<<grid_for(sg.nsub), kBlock, 0, s>>>(sg, w.par);
-    k_sub_label<<<grid_for(sg.nsub), kBlock, 0, s>>>(sg, w.par, w.lab, w.size);
-    k_na_segcount<<<nseg, kBlock, 0, s>>>(sg, w.lab, w.size, segcnt, misc);
-    k_na_segscan<<<1, kBlock, 0, s>>>(nseg, segcnt, segoff, misc);
-    k_na_segwrite<<<nseg, kBlock, 0, s>>>(sg, w.lab, w.size, segoff, reinterpret_cast<int64_t*>(base + kNaRoot),
-                                          reinterpret_cast<int64_t*>(base + kNaRsize));
+    const int nseg = bubble_steps(d, b, npart, sg, w, bytes, s);
+    k_na_segwrite<false><<<nseg, kBlock, 0, s>>>(sg, w.lab, w.size, w.segoff, nullptr,
+                                                 reinterpret_cast<int64_t*>(base + kNaRoot),
+                                                 reinterpret_cast<int64_t*>(base + kNaRsize));
 }
 
 void bubbles_scratch_results(unsigned char* base, int64_t** root, int64_t** rsize, int32_t** lab, NaMisc** misc) {

@@ -242,15 +242,26 @@ struct SubGrid {
     int32_t nsub;
 };
 
-// Device work buffers of the bubble analysis, nsub entries each (flag: 2 ints,
-// [0] bad position, [1] root count; cleared by the caller).
+constexpr int32_t kNaSeg = 2048;              // subcells per segment of the ordered compaction
+struct NaMisc {
+    int32_t bad;               // a position was not finite or outside [-L, 2L)
+    int32_t nroots;            // bubbles found
+    unsigned long long ngas;   // gas subcells
+    int32_t largest;           // subcells of the largest bubble
+    int32_t pad;
+};
+
+// Device work buffers of the bubble analysis, nsub entries each (per segment of kNaSeg
+// subcells: segcnt, segoff).
 struct BubbleWork {
-    uint32_t* cnt;   // particles per subcell (cleared by the caller)
+    uint32_t* cnt;   // particles per subcell
     int32_t* par;    // union-find parent, -1 for liquid
     int32_t* lab;    // bubble label (smallest subcell index), -1 for liquid
     int32_t* size;   // subcells per bubble, at its root
-    int2* roots;     // (root, size) of each bubble, unordered
-    int32_t* flag;
+    int2* roots;     // (root, size) of each bubble, ascending
+    int32_t* segcnt; // roots per segment
+    int32_t* segoff; // roots before it
+    NaMisc* misc;
 };
 
 void launch_bubbles(const Dev& d, int32_t b, int32_t npart, const SubGrid& sg, const BubbleWork& w, uint8_t* bytes,
@@ -259,15 +270,7 @@ void launch_bubbles(const Dev& d, int32_t b, int32_t npart, const SubGrid& sg, c
 // Allocation-free bubble analysis: every work buffer lives in a fixed device
 // array of the library (md_bubbles.hip), sized for kNaMaxSub subcells.
 constexpr int32_t kNaMaxSub = 1 << 20;        // subcells per call at most
-constexpr int32_t kNaSeg = 2048;              // subcells per segment of the ordered compaction
 constexpr int32_t kNaSegs = kNaMaxSub / kNaSeg;
-struct NaMisc {
-    int32_t bad;               // a position was not finite or outside [-L, 2L)
-    int32_t nroots;            // bubbles found
-    unsigned long long ngas;   // gas subcells
-    int32_t largest;           // subcells of the largest bubble
-    int32_t pad;
-};
 // Takes the array's device address on `device` (which must be current) once and
 // keeps it; later calls return at once.
 hipError_t bubbles_scratch_init(int device);
@@ -287,6 +290,8 @@ void launch_get_forces(const Dev& d, const Params& p, double* force, int32_t nwa
 void launch_get_cells(const Dev& d, const Params& p, int32_t* cells, int32_t nwave, hipStream_t s);
 void launch_list_counts(const Dev& d, const Params& p, int64_t* cnt_by_id, int32_t nwave,
                         hipStream_t s);
+// Lengths by caller id at kp + 1 .. kp + n into the offsets kp[0 .. n]; uses d.perm as scratch.
+void launch_list_ptr(const Dev& d, int64_t n, int64_t* kp, hipStream_t s);
 void launch_list_export(const Dev& d, const Params& p, const int64_t* key_ptr, int32_t* partners,
                         int32_t nwave, hipStream_t s);
 void launch_mark_rebuild(const Dev& d, const Params& p, hipStream_t s);

@@ -349,36 +349,120 @@ __device__ int tile_slot(const int* ps0, const int* plen, uint32_t e, int recb) 
     return ps0[13];  // not reached for an entry the build wrote
 }
 
+// Exclusive scan of the keys' list lengths (key_ptr[i + 1] = length of caller id i) into
+// key_ptr, in place: sums of kScanSeg lengths, their scan by one block, then each segment.
+constexpr int kScanSeg = 4096;
+__global__ __launch_bounds__(kBlock) void k_ptr_sums(const int64_t* __restrict__ len, int64_t n,
+                                                     int64_t* __restrict__ sums) {
+    __shared__ int64_t red[kBlock / kWave];
+    const int64_t i0 = (int64_t)blockIdx.x * kScanSeg;
+    int64_t v = 0;
+    for (int k = threadIdx.x; k < kScanSeg; k += kBlock) v += i0 + k < n ? len[i0 + k] : 0;
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if (lane_id() == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) sums[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+}
+__global__ __launch_bounds__(kBlock) void k_ptr_scan(int64_t* __restrict__ sums, int nseg) {
+    __shared__ int64_t tot[kBlock];
+    const int per = (nseg + kBlock - 1) / kBlock, j0 = min((int)threadIdx.x * per, nseg), j1 = min(j0 + per, nseg);
+    int64_t v = 0;
+    for (int j = j0; j < j1; ++j) v += sums[j];
+    tot[threadIdx.x] = v;
+    __syncthreads();
+    for (int o = 1; o < kBlock; o <<= 1) {
+        const int64_t t = (int)threadIdx.x >= o ? tot[threadIdx.x - o] : 0;
+        __syncthreads();
+        tot[threadIdx.x] += t;
+        __syncthreads();
+    }
+    int64_t run = tot[threadIdx.x] - v;
+    for (int j = j0; j < j1; ++j) {
+        const int64_t t = sums[j];
+        sums[j] = run;
+        run += t;
+    }
+}
+__global__ __launch_bounds__(kBlock) void k_ptr_add(int64_t* __restrict__ ptr, int64_t n,
+                                                    const int64_t* __restrict__ sums) {
+    __shared__ int64_t tot[kBlock / kWave];
+    constexpr int kPer = kScanSeg / kBlock;  // consecutive keys per thread
+    const int64_t i0 = (int64_t)blockIdx.x * kScanSeg + (int64_t)threadIdx.x * kPer;
+    int64_t v[kPer], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        v[k] = i0 + k < n ? ptr[1 + i0 + k] : 0;
+        sum += v[k];
+    }
+    int64_t incl = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int64_t t = __shfl_up(incl, o);
+        if (lane_id() >= o) incl += t;
+    }
+    if (lane_id() == kWave - 1) tot[threadIdx.x >> 6] = incl;
+    __syncthreads();
+    int64_t run = sums[blockIdx.x] + incl - sum;
+    for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) run += tot[w];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        run += v[k];
+        if (i0 + k < n) ptr[1 + i0 + k] = run;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) ptr[0] = 0;
+}
+
+// Partners of every key in caller ids, ascending.  One wavefront per key: lane l holds the
+// partner of entry l (blocks of 64 entries for longer lists); a partner's place is the number
+// of smaller ids among the key's, counted by lane reads, so every id goes to its place with
+// one store.  (An insertion sort by one lane per key in the output array took 300 us of an
+// export of 32,000 keys of 46 partners; with the offsets' scan on the device the whole call,
+// list build included, went from 630 to 290 us.)
 __global__ __launch_bounds__(kBlock) void k_list_export(Dev d, Params p, const int64_t* __restrict__ key_ptr,
                                                         int32_t* __restrict__ partners) {
     const int l = lane_id();
-    for (int w = blockIdx.x * 4 + wave_in_block(); w < p.nwave; w += gridDim.x * 4) {
-        const int b = ld_const(d.wave_box + w);
+    for (int s = blockIdx.x * 4 + wave_in_block(); s < p.nwave * kWave; s += gridDim.x * 4) {
+        const int b = ld_const(d.wave_box + (s >> 6));
         const BoxGeom& g = d.geom[b];
-        const int s = w * kWave + l;
-        if (s - g.slot_off >= g.npart) continue;
-        const int sp = d.st[b].sp;
-        const int32_t* id = d.id[sp];
+        if (s - g.slot_off >= g.npart) continue;  // uniform over the wavefront
+        const int32_t* id = d.id[d.st[b].sp];
         const int64_t base = key_ptr[id[s]];
         const int n = d.cnt[s];
         const uint32_t cc = d.q[d.st[b].sq][s].cc;
-        if (p.tile) {
-            int ps0[27], plen[27];
-            tile_pieces_of(d, g, cc, ps0, plen);
-            for (int e = 0; e < n; ++e)
-                partners[base + e] = id[tile_slot(ps0, plen, d.list[list_addr(s, e, p.tpk, p.rows)], p.recb)];
-        } else {
-            for (int e = 0; e < n; ++e)
-                partners[base + e] = id[entry_slot(d, cc, d.list[list_addr(s, e, p.tpk, p.rows)], g)];
+        // row-tile format: lane pc holds piece pc of the key's tile
+        int ps0 = 0, plen = 0;
+        if (p.tile && l < 27) {
+            const int cx = (int)(cc & 1023), cy = (int)((cc >> 10) & 1023), cz = (int)(cc >> 20);
+            const int4 tr = d.rtile[d.cell_rt[g.cell_off + (cz * g.n[1] + cy) * g.n[0] + cx]];
+            int ox, oy, oz;
+            tile_piece(d, g, cy, cz, tr.z, tr.w, l, ps0, plen, ox, oy, oz);
         }
-        for (int a = 1; a < n; ++a) {  // ascending, insertion sort
-            const int32_t x = partners[base + a];
-            int c = a - 1;
-            while (c >= 0 && partners[base + c] > x) {
-                partners[base + c + 1] = partners[base + c];
-                --c;
+        const int pend = wave_incl_sum(plen);  // staged index after the piece
+        auto partner = [&](int e) -> int32_t {   // every lane calls it; INT_MAX beyond the list
+            const uint32_t en = e < n ? d.list[list_addr(s, e, p.tpk, p.rows)] : 0u;
+            int slot;
+            if (p.tile) {
+                const int idx = (int)(en / (uint32_t)p.recb);
+                slot = 0;
+                int from = 0;
+                for (int pc = 0; pc < 27; ++pc) {
+                    const int end = __builtin_amdgcn_readlane(pend, pc);
+                    if (idx >= from && idx < end) slot = __builtin_amdgcn_readlane(ps0, pc) + idx - from;
+                    from = end;
+                }
+            } else {
+                slot = entry_slot(d, cc, en, g);
             }
-            partners[base + c + 1] = x;
+            return e < n ? id[slot] : 0x7fffffff;
+        };
+        for (int e0 = 0; e0 < n; e0 += kWave) {
+            const int32_t v = partner(e0 + l);
+            int rank = 0;
+            for (int t0 = 0; t0 < n; t0 += kWave) {
+                const int32_t w = t0 == e0 ? v : partner(t0 + l);
+                const int m = min(kWave, n - t0);
+                for (int t = 0; t < m; ++t) rank += __builtin_amdgcn_readlane(w, t) < v ? 1 : 0;
+            }
+            if (e0 + l < n) partners[base + rank] = v;
         }
     }
 }
@@ -2753,7 +2837,15 @@ void launch_list_counts(const Dev& d, const Params& p, int64_t* c, int32_t nwave
 }
 void launch_list_export(const Dev& d, const Params& p, const int64_t* kp, int32_t* partners, int32_t nwave,
                         hipStream_t s) {
-    k_list_export<<<grid_for_waves(nwave), kBlock, 0, s>>>(d, p, kp, partners);
+    const int64_t keys = (int64_t)nwave * kWave;  // a wavefront each, up to 65536 blocks of them
+    k_list_export<<<(int)((keys < 262144 ? keys : 262144) / 4), kBlock, 0, s>>>(d, p, kp, partners);
+}
+void launch_list_ptr(const Dev& d, int64_t n, int64_t* kp, hipStream_t s) {
+    int64_t* sums = reinterpret_cast<int64_t*>(d.perm);  // free between list builds; n / kScanSeg of them
+    const int nseg = (int)((n + kScanSeg - 1) / kScanSeg);
+    k_ptr_sums<<<nseg, kBlock, 0, s>>>(kp + 1, n, sums);
+    k_ptr_scan<<<1, kBlock, 0, s>>>(sums, nseg);
+    k_ptr_add<<<nseg, kBlock, 0, s>>>(kp, n, sums);
 }
 void launch_mark_rebuild(const Dev& d, const Params& p, hipStream_t s) {
     k_mark_rebuild<<<1, kBlock, 0, s>>>(d, p);
