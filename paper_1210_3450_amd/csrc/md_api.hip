@@ -946,10 +946,16 @@ md_status create_impl(const md_params* boxes, int32_t nbox, void* stream, md_ctx
     }
     layout(c);
     int tpk = c->prm.threads_per_key;
-    // default layout (md_autotune measures instead): small systems need more lanes
-    // per key to fill the chip; large ones are bound by partner gathers, where the
-    // FP64 path's 32-byte records gain from two lanes reading adjacent entries
-    if (tpk == 0) tpk = c->ntotal < 262144 ? 4 : (c->prm.precision == MD_PREC_FP64 ? 2 : 1);
+    // Default layout of the gather format (md_autotune measures instead).  Small systems need
+    // more lanes per key to fill the chip: four lanes against two, force pass, FP64 62,500
+    // particles 15.0 / 16.2 us, 131,000 26.6 / 24.8 us; FP32-mixed 131,000 21.2 / 18.2 us (one lane
+    // 17.9), 256,000 37.8 / 31.1 (31.8).  On large ones the FP64 path's 32-byte partner records gain
+    // from two lanes reading adjacent entries (16M: 2455 us with one lane, 2272 with two), the
+    // FP32-mixed path's 12-byte ones do not (1M 98.8 and 108 us).
+    if (tpk == 0) {
+        const bool fp64 = c->prm.precision == MD_PREC_FP64;
+        tpk = c->ntotal < 98304 ? 4 : (c->ntotal < 262144 || fp64 ? 2 : 1);
+    }
     // Row tiles pay off on large boxes only: at 13.8M particles (FCC, density 0.5) their
     // force pass is 11% and the step 3.5% faster than the gather format's, at 4M particles
     // and below the gather format is 7-25% faster per step (the tile cuts cost rebuild time
