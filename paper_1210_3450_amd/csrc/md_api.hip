@@ -643,7 +643,7 @@ md_status enqueue_rebuild(md_ctx* c, bool with_list) {
     return MD_OK;
 }
 
-md_status enqueue_force(md_ctx* c, int mode, bool energy) {
+md_status enqueue_force(md_ctx* c, int mode, int energy) {
     md_status s;
     if (c->timing && (s = timed_event(c, c->ev_force)) != MD_OK) return s;
     launch_force(c->D, c->P, mode, energy, c->stream);
@@ -657,7 +657,7 @@ md_status enqueue_force(md_ctx* c, int mode, bool energy) {
 md_status enqueue_mid_step(md_ctx* c) {
     md_status s;
     if ((s = enqueue_rebuild(c, true)) != MD_OK) return s;
-    if ((s = enqueue_force(c, kForceMid, false)) != MD_OK) return s;
+    if ((s = enqueue_force(c, kForceMid, kEnNone)) != MD_OK) return s;
     launch_dutc(c->D, c->P, 0, c->stream);
     return MD_OK;
 }
@@ -752,7 +752,7 @@ md_status enqueue_ahead(md_ctx* c, int32_t chunk, int32_t done, int32_t energy_e
     if (!opened) {
         if (thermo) {
             launch_ke_partial(c->D, c->P, c->stream);
-            launch_energy_reduce(c->D, c->P, false, 2, false, c->stream);
+            launch_energy_reduce(c->D, c->P, false, 2, false, kEnKe, c->stream);
         }
         launch_kick_drift(c->D, c->P, c->stream);
         launch_dutc(c->D, c->P, opening[1] = next_seq(c), c->stream);
@@ -786,18 +786,19 @@ md_status enqueue_ahead(md_ctx* c, int32_t chunk, int32_t done, int32_t energy_e
         const bool last = k == chunk;
         mark[k] = c->ev_force.size();
         if (thermo) {
-            if ((s = enqueue_force(c, kForceEnd, true)) != MD_OK) return s;
-            launch_energy_reduce(c->D, c->P, energy, last ? 1 : 3, c->P.tile != 0, c->stream);
+            if ((s = enqueue_force(c, kForceEnd, energy ? kEnFull : kEnKe)) != MD_OK) return s;
+            launch_energy_reduce(c->D, c->P, energy, last ? 1 : 3, c->P.tile != 0, energy ? kEnFull : kEnKe,
+                                 c->stream);
             if (last)
                 launch_vscale(c->D, c->P, c->stream);
             else
                 launch_kick_drift(c->D, c->P, c->stream);
         } else if (energy || last) {
-            if ((s = enqueue_force(c, kForceEnd, energy)) != MD_OK) return s;
-            if (energy) launch_energy_reduce(c->D, c->P, true, 0, c->P.tile != 0, c->stream);
+            if ((s = enqueue_force(c, kForceEnd, energy ? kEnFull : kEnNone)) != MD_OK) return s;
+            if (energy) launch_energy_reduce(c->D, c->P, true, 0, c->P.tile != 0, kEnFull, c->stream);
             if (!last) launch_kick_drift(c->D, c->P, c->stream);
         } else {
-            if ((s = enqueue_force(c, kForceMid, false)) != MD_OK) return s;
+            if ((s = enqueue_force(c, kForceMid, kEnNone)) != MD_OK) return s;
         }
         if (!last) launch_dutc(c->D, c->P, opening[k + 1] = next_seq(c), c->stream);
         ++k;
@@ -880,7 +881,7 @@ md_status ensure_list_and_forces(md_ctx* c) {
     if (!c->have_state) return fail(c, MD_ESTATE, "no state: call md_set_state first");
     if (!c->have_list && (s = build_list(c)) != MD_OK) return s;
     if (!c->have_F) {
-        if ((s = enqueue_force(c, kForceOnly, false)) != MD_OK) return s;
+        if ((s = enqueue_force(c, kForceOnly, kEnNone)) != MD_OK) return s;
         LAUNCHCHK(c);
         c->have_F = true;
     }
@@ -1115,7 +1116,7 @@ md_status md_compute_forces(md_ctx* c, double* force) {
     if ((s = check_ctx(c)) != MD_OK) return s;
     if (!c->have_state) return fail(c, MD_ESTATE, "no state: call md_set_state first");
     if (!c->have_list && (s = build_list(c)) != MD_OK) return s;
-    if ((s = enqueue_force(c, kForceOnly, false)) != MD_OK) return s;
+    if ((s = enqueue_force(c, kForceOnly, kEnNone)) != MD_OK) return s;
     c->have_F = true;
     if (force) launch_get_forces(c->D, c->P, force, c->nwave, c->stream);
     LAUNCHCHK(c);
@@ -1151,15 +1152,16 @@ md_status md_step(md_ctx* c, int32_t nsteps, int32_t energy_every) {
             const int32_t gk = done + k;
             if (k == 1 && !opened) {
                 launch_ke_partial(c->D, c->P, c->stream);
-                launch_energy_reduce(c->D, c->P, false, 2, false, c->stream);
+                launch_energy_reduce(c->D, c->P, false, 2, false, kEnKe, c->stream);
                 launch_kick_drift(c->D, c->P, c->stream);
                 launch_dutc(c->D, c->P, 0, c->stream);
             }
             const bool energy = energy_every > 0 && gk % energy_every == 0;
             const bool last = k == chunk;
             if ((s = enqueue_rebuild(c, true)) != MD_OK) return s;
-            if ((s = enqueue_force(c, kForceEnd, true)) != MD_OK) return s;
-            launch_energy_reduce(c->D, c->P, energy, last ? 1 : 3, c->P.tile != 0, c->stream);
+            if ((s = enqueue_force(c, kForceEnd, energy ? kEnFull : kEnKe)) != MD_OK) return s;
+            launch_energy_reduce(c->D, c->P, energy, last ? 1 : 3, c->P.tile != 0, energy ? kEnFull : kEnKe,
+                                 c->stream);
             if (last) {
                 launch_vscale(c->D, c->P, c->stream);
             } else {
@@ -1177,8 +1179,8 @@ md_status md_step(md_ctx* c, int32_t nsteps, int32_t energy_every) {
             const bool last = k == chunk;
             if (energy || last) {
                 if ((s = enqueue_rebuild(c, true)) != MD_OK) return s;
-                if ((s = enqueue_force(c, kForceEnd, energy)) != MD_OK) return s;
-                if (energy) launch_energy_reduce(c->D, c->P, true, 0, c->P.tile != 0, c->stream);
+                if ((s = enqueue_force(c, kForceEnd, energy ? kEnFull : kEnNone)) != MD_OK) return s;
+                if (energy) launch_energy_reduce(c->D, c->P, true, 0, c->P.tile != 0, kEnFull, c->stream);
                 if (!last) {
                     launch_kick_drift(c->D, c->P, c->stream);
                     launch_dutc(c->D, c->P, 0, c->stream);
@@ -1242,9 +1244,9 @@ static md_status energies(md_ctx* c) {
     if ((s = check_ctx(c)) != MD_OK) return s;
     if (!c->have_state) return fail(c, MD_ESTATE, "no state: call md_set_state first");
     if (!c->have_list && (s = build_list(c)) != MD_OK) return s;
-    if ((s = enqueue_force(c, kForceOnly, true)) != MD_OK) return s;
+    if ((s = enqueue_force(c, kForceOnly, kEnFull)) != MD_OK) return s;
     c->have_F = true;
-    launch_energy_reduce(c->D, c->P, false, 0, c->P.tile != 0, c->stream);
+    launch_energy_reduce(c->D, c->P, false, 0, c->P.tile != 0, kEnFull, c->stream);
     LAUNCHCHK(c);
     return sync_states(c);
 }
@@ -1673,8 +1675,8 @@ md_status md_autotune(md_ctx* c, const char* cache_path) {
             launch_mark_rebuild(c->D, c->P, c->stream);
             launch_rebuild_chain(c->D, c->P, true, c->stream);
             HIPCHK(c, hipEventRecord(ev[1], c->stream));
-            launch_force(c->D, c->P, kForceOnly, false, c->stream);  // warm-up
-            for (int r = 0; r < 5; ++r) launch_force(c->D, c->P, kForceOnly, false, c->stream);
+            launch_force(c->D, c->P, kForceOnly, kEnNone, c->stream);  // warm-up
+            for (int r = 0; r < 5; ++r) launch_force(c->D, c->P, kForceOnly, kEnNone, c->stream);
             HIPCHK(c, hipEventRecord(ev[2], c->stream));
             HIPCHK(c, hipEventSynchronize(ev[2]));
             LAUNCHCHK(c);

@@ -231,6 +231,11 @@ enum ForceMode : int {
     kForceEnd = 1,   // v += h F (closing half kick), F stored
     kForceMid = 2    // v += h F twice (close step n, open step n+1), drift q, DUTC max
 };
+// Energy partials a force pass leaves.  A thermostat step that records no sample needs the
+// kinetic energy alone: the pair energy and the virial are some 10 of the 40 instructions of
+// an entry (closing pass of 2M particles at density 0.84, FP32-mixed, all / kinetic: gathers
+// 255 / 226 us, row tiles 262 / 204 us; FP64 1M 240 / 207 and 269 / 215 us).
+enum ForceEnergy : int { kEnNone = 0, kEnKe = 1, kEnFull = 2 };
 
 // Subcell grid of the bubble analysis (md_bubbles.hip): n = floor(L / side)
 // per axis, inv = n / L rounded once on the host, thr = rho_gas * subcell volume.
@@ -300,7 +305,7 @@ void launch_row_tiles(const Dev& d, const Params& p, hipStream_t s);
 // Resident blocks per compute unit of the row-tile force kernel.
 int rowtile_blocks_per_cu(const Params& p);
 void launch_rebuild_chain(const Dev& d, const Params& p, bool with_list, hipStream_t s);
-void launch_force(const Dev& d, const Params& p, int mode, bool energy, hipStream_t s);
+void launch_force(const Dev& d, const Params& p, int mode, int energy, hipStream_t s);
 void launch_kick_drift(const Dev& d, const Params& p, hipStream_t s);
 // seq: number of the drift whose decision the host waits for (one box), or 0.
 void launch_dutc(const Dev& d, const Params& p, uint32_t seq, hipStream_t s);
@@ -309,7 +314,9 @@ void launch_dutc(const Dev& d, const Params& p, uint32_t seq, hipStream_t s);
 // goes to BoxState::vscale for the next kick (or k_vscale).
 // tl: the partials are per row tile (written by the row-tile force kernel), else per
 // list wavefront.
-void launch_energy_reduce(const Dev& d, const Params& p, bool record, int thermo, bool tl, hipStream_t s);
+// energy: kEnFull, or kEnKe where the force pass left kinetic partials only.
+void launch_energy_reduce(const Dev& d, const Params& p, bool record, int thermo, bool tl, int energy,
+                          hipStream_t s);
 void launch_ke_partial(const Dev& d, const Params& p, hipStream_t s);
 void launch_vscale(const Dev& d, const Params& p, hipStream_t s);
 void launch_verify(const Dev& d, const Params& p, hipStream_t s);

@@ -1548,7 +1548,7 @@ __device__ __forceinline__ void stripe_put(unsigned long long* base, int b, int 
 // The end of a force pass for one key: reduce the lanes of a key, then store F,
 // or kick (closing half kick; mid-step: closing and opening kicks, drift and the
 // fixed-point re-encoding), DUTC maximum and energy partials per wavefront.
-template <int PREC, int MODE, int TPK, bool ENERGY, bool HALF>
+template <int PREC, int MODE, int TPK, int ENERGY, bool HALF>
 __device__ __forceinline__ void force_finish(const Dev& d, const Params& p, const BoxGeom& g, int b, int lw, int key,
                                              bool owner, const Pos& qi, uint32_t cc, int sq, int sp, double Fx,
                                              double Fy, double Fz, double pe, double vir, bool f_done = false) {
@@ -1559,7 +1559,7 @@ __device__ __forceinline__ void force_finish(const Dev& d, const Params& p, cons
             Fx += __shfl_xor(Fx, o);
             Fy += __shfl_xor(Fy, o);
             Fz += __shfl_xor(Fz, o);
-            if (ENERGY) {
+            if (ENERGY == kEnFull) {
                 pe += __shfl_xor(pe, o);
                 vir += __shfl_xor(vir, o);
             }
@@ -1627,10 +1627,12 @@ __device__ __forceinline__ void force_finish(const Dev& d, const Params& p, cons
     }
     if (ENERGY) {
         const double ks = wave_sum(ke);
+        if (l == 0) d.ke_part[lw] = ks;
+    }
+    if (ENERGY == kEnFull) {
         const double ps = wave_sum(owner ? pe : 0.0);
         const double vs = wave_sum(owner ? vir : 0.0);
         if (l == 0) {
-            d.ke_part[lw] = ks;
             d.pe_part[lw] = ps;
             d.vir_part[lw] = vs;
         }
@@ -1638,7 +1640,7 @@ __device__ __forceinline__ void force_finish(const Dev& d, const Params& p, cons
 }
 
 // Algorithm 1 on the GPU.  PREC: MD_PREC_FP64 or MD_PREC_FP32_MIXED.
-// MODE: kForceOnly / kForceEnd / kForceMid.  ENERGY: per-wave KE and PE partials.
+// MODE: kForceOnly / kForceEnd / kForceMid.  ENERGY: no, kinetic or all (kEn*) partials per wave.
 // Each lane reads 8 list entries per 16-byte load and keeps 8 partner gathers in
 // flight (Algorithm 1's unrolling for latency hiding, in GPU form).  A list
 // entry names a stencil cell and a rank in it; the wavefront first tabulates, in
@@ -1661,7 +1663,7 @@ __device__ __forceinline__ uint32_t force_rec(const Dev& d, uint32_t cc, int s, 
 // HALF (half list, kForceOnly, one lane per key): the reaction -f d of every pair
 // goes to the partner by an atomic add, and the key's own sum is added likewise;
 // F must be zero before the pass.
-template <int PREC, int MODE, int TPK, bool ENERGY, bool HALF = false>
+template <int PREC, int MODE, int TPK, int ENERGY, bool HALF = false>
 __global__ __launch_bounds__(kBlock) void k_force(Dev d, Params p) {
     if (step_off(d)) return;
     static_assert(!HALF || (MODE == kForceOnly && TPK == 1), "half lists: forces only, one lane per key");
@@ -1862,12 +1864,12 @@ __global__ __launch_bounds__(kBlock) void k_force(Dev d, Params p) {
                         const double x2 = xt * xt, x3 = x2 * xt, x4 = x2 * x2;
                         const double r8 = x4 * (5.0 - 4.0 * t), r14 = x4 * x3 * (8.0 - 7.0 * t);
                         f = in ? 24.0 * r8 - 48.0 * r14 + c2x8 : 0.0;
-                        if (ENERGY) e = x3 * x3 * (7.0 - 6.0 * t) - x3 * (4.0 - 3.0 * t);
+                        if (ENERGY == kEnFull) e = x3 * x3 * (7.0 - 6.0 * t) - x3 * (4.0 - 3.0 * t);
                     } else {
                         const double inv = 1.0 / r2;
                         const double inv3 = inv * inv * inv;
                         f = in ? (24.0 * inv3 - 48.0 * inv3 * inv3) * inv + c2x8 : 0.0;
-                        if (ENERGY) e = inv3 * inv3 - inv3;
+                        if (ENERGY == kEnFull) e = inv3 * inv3 - inv3;
                     }
                     Fx += f * dx;
                     Fy += f * dy;
@@ -1882,7 +1884,7 @@ __global__ __launch_bounds__(kBlock) void k_force(Dev d, Params p) {
                             unsafeAtomicAdd(d.fz + js[k], -(f * dz));
                         }
                     }
-                    if (ENERGY) {
+                    if (ENERGY == kEnFull) {
                         pe += in ? 2.0 * (e + p.c2 * r2 + p.c0) : 0.0;
                         vir += in ? f * r2 : 0.0;
                     }
@@ -1894,7 +1896,7 @@ __global__ __launch_bounds__(kBlock) void k_force(Dev d, Params p) {
             const int32_t* __restrict__ u = d.u[sq];
             const int4 ui = units3(qi, cc, g);  // own coordinate from the record: no extra load
             // lengths stay in fixed-point units: r^2 in units^2, 1/r^2 rescaled once
-            const float rc2u = g.rc2u, lam2inv = g.lam2inv, lam2 = g.lam * g.lam, c2x8 = 8.0f * p.c2f;
+            const float rc2u = g.rc2u, lam2inv = g.lam2inv, c2l = p.c2f * (g.lam * g.lam), c2x8 = 8.0f * p.c2f;
             const float irc2 = p.irc2f;
             // the clamp serves full lists only: a half list's reactions go to partners directly
             const bool clampf = p.clamp != 0 && !HALF;
@@ -1954,9 +1956,9 @@ __global__ __launch_bounds__(kBlock) void k_force(Dev d, Params p) {
                             unsafeAtomicAdd(d.fz + js[k], -(double)fdz * lamd);
                         }
                     }
-                    if (ENERGY) {
+                    if (ENERGY == kEnFull) {
                         const float i3 = inv0 * inv0 * inv0;
-                        pes += in ? 2.0f * (i3 * i3 - i3 + p.c2f * (r2 * lam2) + p.c0f) : 0.0f;
+                        pes += in ? i3 * i3 - i3 + c2l * r2 + p.c0f : 0.0f;  // half the pair energy
                         virs += in ? f * r2 : 0.0f;  // units^2: times lam^2 below
                     }
                 }
@@ -1970,7 +1972,7 @@ __global__ __launch_bounds__(kBlock) void k_force(Dev d, Params p) {
             Fx = ((double)sx - (double)cx) * lam;
             Fy = ((double)sy - (double)cy) * lam;
             Fz = ((double)sz - (double)cz) * lam;
-            pe = (double)pes;
+            pe = 2.0 * (double)pes;
             vir = (double)virs * lam * lam;
         }
     };
@@ -2023,7 +2025,7 @@ __global__ __launch_bounds__(kBlock) void k_force(Dev d, Params p) {
 // CLAMP (the Eq. 1 cutoff, whose f(rc) is 0): a list entry beyond rc is evaluated at
 // rc instead of being masked, 1/r^2 = max(1/r^2, 1/rc^2) (one instruction for a
 // compare and a select); f(rc) rounds to a few 1e-9 in FP32.
-template <int MODE, bool ENERGY, bool CLAMP>
+template <int MODE, int ENERGY, bool CLAMP>
 __global__ __launch_bounds__(kRtBlock) void k_force_t(Dev d, Params p) {
     if (step_off(d)) return;
     constexpr int NW = kRtBlock / kWave;  // wavefronts per block
@@ -2105,7 +2107,7 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t(Dev d, Params p) {
             }
         }
         __syncthreads();
-        const float rc2u = g.rc2u, lam2inv = g.lam2inv, lam2 = g.lam * g.lam, c2x8 = 8.0f * p.c2f;
+        const float rc2u = g.rc2u, lam2inv = g.lam2inv, c2l = p.c2f * (g.lam * g.lam), c2x8 = 8.0f * p.c2f;
         const float irc2 = p.irc2f;  // 1 / rc^2 in length units (FP32)
         const double lam = (double)g.lam;  // units back to lengths (a power of two)
         const char* __restrict__ sb = reinterpret_cast<const char*>(stg);
@@ -2151,9 +2153,9 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t(Dev d, Params p) {
                     bx += f * dx;
                     by += f * dy;
                     bz += f * dz;
-                    if (ENERGY) {
+                    if (ENERGY == kEnFull) {
                         const float i3 = inv0 * inv0 * inv0;
-                        pes += in ? 2.0f * (i3 * i3 - i3 + p.c2f * (r2 * lam2) + p.c0f) : 0.0f;
+                        pes += in ? i3 * i3 - i3 + c2l * r2 + p.c0f : 0.0f;  // half the pair energy
                         virs += in ? f * r2 : 0.0f;  // units^2: times lam^2 below
                     }
                 }
@@ -2211,9 +2213,9 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t(Dev d, Params p) {
                     if (l == 0) stripe_put(d.disp_s, b, t * 4 + wib, mm);
                 }
             }
-            if (ENERGY && active) {
-                e_ke += ke;
-                e_pe += (double)pes;
+            if (ENERGY && active) e_ke += ke;
+            if (ENERGY == kEnFull && active) {
+                e_pe += 2.0 * (double)pes;
                 e_vir += (double)virs * lam * lam;
             }
             kb += kRtBlock;
@@ -2230,7 +2232,8 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t(Dev d, Params p) {
             raw_b = p.rows >= 16 ? ld_stream(l4 + kWave) : make_uint4(0u, 0u, 0u, 0u);
         }
         if (ENERGY) {  // the tile's partials, summed in a fixed order
-            const double ks = wave_sum(e_ke), ps = wave_sum(e_pe), vs = wave_sum(e_vir);
+            const double ks = wave_sum(e_ke), ps = ENERGY == kEnFull ? wave_sum(e_pe) : 0.0,
+                         vs = ENERGY == kEnFull ? wave_sum(e_vir) : 0.0;
             __syncthreads();  // red of the previous tile has been read
             if (l == 0) {
                 red[0][wib] = ks;
@@ -2246,8 +2249,10 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t(Dev d, Params p) {
                     a2 += red[2][w];
                 }
                 d.ke_part[t] = a0;
-                d.pe_part[t] = a1;
-                d.vir_part[t] = a2;
+                if (ENERGY == kEnFull) {
+                    d.pe_part[t] = a1;
+                    d.vir_part[t] = a2;
+                }
             }
         }
         __syncthreads();  // the next tile's staging reuses the LDS
@@ -2266,7 +2271,7 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t(Dev d, Params p) {
 struct D3 {
     double x, y, z;
 };
-template <int MODE, bool ENERGY>
+template <int MODE, int ENERGY>
 __global__ __launch_bounds__(kRtBlock) void k_force_t64(Dev d, Params p) {
     if (step_off(d)) return;
     constexpr int NW = kRtBlock / kWave;
@@ -2377,17 +2382,17 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t64(Dev d, Params p) {
                         const double x2 = xt * xt, x3 = x2 * xt, x4 = x2 * x2;
                         const double r8 = x4 * (5.0 - 4.0 * tt), r14 = x4 * x3 * (8.0 - 7.0 * tt);
                         f = in ? 24.0 * r8 - 48.0 * r14 + c2x8 : 0.0;
-                        if (ENERGY) e = x3 * x3 * (7.0 - 6.0 * tt) - x3 * (4.0 - 3.0 * tt);
+                        if (ENERGY == kEnFull) e = x3 * x3 * (7.0 - 6.0 * tt) - x3 * (4.0 - 3.0 * tt);
                     } else {
                         const double inv = 1.0 / r2;
                         const double inv3 = inv * inv * inv;
                         f = in ? (24.0 * inv3 - 48.0 * inv3 * inv3) * inv + c2x8 : 0.0;
-                        if (ENERGY) e = inv3 * inv3 - inv3;
+                        if (ENERGY == kEnFull) e = inv3 * inv3 - inv3;
                     }
                     Fx += f * dx;
                     Fy += f * dy;
                     Fz += f * dz;
-                    if (ENERGY) {
+                    if (ENERGY == kEnFull) {
                         pe += in ? 2.0 * (e + p.c2 * r2 + p.c0) : 0.0;
                         vir += in ? f * r2 : 0.0;
                     }
@@ -2438,8 +2443,8 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t64(Dev d, Params p) {
                     if (l == 0) stripe_put(d.disp_s, b, t * 4 + wib, mm);
                 }
             }
-            if (ENERGY && active) {
-                e_ke += ke;
+            if (ENERGY && active) e_ke += ke;
+            if (ENERGY == kEnFull && active) {
                 e_pe += pe;
                 e_vir += vir;
             }
@@ -2457,10 +2462,11 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t64(Dev d, Params p) {
             raw_b = p.rows >= 16 ? ld_stream(l4 + kWave) : make_uint4(0u, 0u, 0u, 0u);
         }
         if (ENERGY) {  // the tile's partials, summed in a fixed order
-            const double ks2 = wave_sum(e_ke), ps = wave_sum(e_pe), vs = wave_sum(e_vir);
+            const double ks = wave_sum(e_ke), ps = ENERGY == kEnFull ? wave_sum(e_pe) : 0.0,
+                         vs = ENERGY == kEnFull ? wave_sum(e_vir) : 0.0;
             __syncthreads();
             if (l == 0) {
-                red[0][wib] = ks2;
+                red[0][wib] = ks;
                 red[1][wib] = ps;
                 red[2][wib] = vs;
             }
@@ -2473,8 +2479,10 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t64(Dev d, Params p) {
                     a2 += red[2][w];
                 }
                 d.ke_part[t] = a0;
-                d.pe_part[t] = a1;
-                d.vir_part[t] = a2;
+                if (ENERGY == kEnFull) {
+                    d.pe_part[t] = a1;
+                    d.vir_part[t] = a2;
+                }
             }
         }
         __syncthreads();  // the next tile's staging reuses the LDS
@@ -2607,7 +2615,8 @@ __device__ __forceinline__ void part_range(const Dev& d, const Params& p, const 
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_energy_segments(Dev d, Params p, int tl) {
+// ke_only: the pair partials are those of an earlier step and stay unread.
+__global__ __launch_bounds__(kBlock) void k_energy_segments(Dev d, Params p, int tl, int ke_only) {
     if (step_off(d)) return;
     const int b = blockIdx.y, j = blockIdx.x;
     const BoxGeom& g = d.geom[b];
@@ -2618,6 +2627,7 @@ __global__ __launch_bounds__(kBlock) void k_energy_segments(Dev d, Params p, int
     double k = 0.0, e = 0.0, v = 0.0;
     for (int w = a0 + threadIdx.x; w < a1; w += kBlock) {
         k += d.ke_part[w];
+        if (ke_only) continue;
         e += d.pe_part[w];
         v += d.vir_part[w];
     }
@@ -2631,7 +2641,7 @@ __global__ __launch_bounds__(kBlock) void k_energy_segments(Dev d, Params p, int
 }
 
 __global__ __launch_bounds__(kBlock) void k_energy_reduce(Dev d, Params p, int record, int thermo, int tl,
-                                                            int one) {
+                                                            int one, int ke_only) {
     if (step_off(d)) return;
     for (int b = blockIdx.x; b < p.nbox; b += gridDim.x) {
         const BoxGeom& g = d.geom[b];
@@ -2642,6 +2652,7 @@ __global__ __launch_bounds__(kBlock) void k_energy_reduce(Dev d, Params p, int r
         if (one) {  // every box has one segment: summed here as k_energy_segments sums it
             for (int w = w0 + threadIdx.x; w < w1; w += kBlock) {
                 k += d.ke_part[w];
+                if (ke_only) continue;
                 e += d.pe_part[w];
                 v += d.vir_part[w];
             }
@@ -2678,8 +2689,10 @@ __global__ __launch_bounds__(kBlock) void k_energy_reduce(Dev d, Params p, int r
                 st.vscale = f;
             }
             st.ke = ke_s;
-            st.pe = e;
-            st.vir = 0.5 * v;  // every pair appears in both keys' lists
+            if (!ke_only) {
+                st.pe = e;
+                st.vir = 0.5 * v;  // every pair appears in both keys' lists
+            }
             if (record && st.nseries < kMaxSeries) {
                 const size_t at = (size_t)st.nseries * p.nbox + b;
                 d.series_ke[at] = ke_s;
@@ -2705,11 +2718,7 @@ __global__ __launch_bounds__(kBlock) void k_ke_partial(Dev d, Params p) {
         const double k = s - g.slot_off < g.npart ? 0.5 * p.mass * norm2(d.vx[sp][s], d.vy[sp][s], d.vz[sp][s])
                                                   : 0.0;
         const double ks = wave_sum(k);
-        if (l < p.tpk) {
-            d.ke_part[w * p.tpk + l] = l == 0 ? ks : 0.0;
-            d.pe_part[w * p.tpk + l] = 0.0;
-            d.vir_part[w * p.tpk + l] = 0.0;
-        }
+        if (l < p.tpk) d.ke_part[w * p.tpk + l] = l == 0 ? ks : 0.0;
     }
 }
 
@@ -2915,25 +2924,27 @@ void launch_rebuild_chain(const Dev& d, const Params& p, bool with_list, hipStre
 }
 
 template <int PREC, int TPK>
-static void launch_force_pt(const Dev& d, const Params& p, int mode, bool energy, hipStream_t s) {
+static void launch_force_pt(const Dev& d, const Params& p, int mode, int energy, hipStream_t s) {
     const int nb = (p.nwave * TPK + 3) / 4;
     if (mode == kForceOnly) {
         if (energy)
-            k_force<PREC, kForceOnly, TPK, true><<<nb, kBlock, 0, s>>>(d, p);
+            k_force<PREC, kForceOnly, TPK, kEnFull><<<nb, kBlock, 0, s>>>(d, p);
         else
-            k_force<PREC, kForceOnly, TPK, false><<<nb, kBlock, 0, s>>>(d, p);
+            k_force<PREC, kForceOnly, TPK, kEnNone><<<nb, kBlock, 0, s>>>(d, p);
     } else if (mode == kForceEnd) {
-        if (energy)
-            k_force<PREC, kForceEnd, TPK, true><<<nb, kBlock, 0, s>>>(d, p);
+        if (energy == kEnFull)
+            k_force<PREC, kForceEnd, TPK, kEnFull><<<nb, kBlock, 0, s>>>(d, p);
+        else if (energy == kEnKe)
+            k_force<PREC, kForceEnd, TPK, kEnKe><<<nb, kBlock, 0, s>>>(d, p);
         else
-            k_force<PREC, kForceEnd, TPK, false><<<nb, kBlock, 0, s>>>(d, p);
+            k_force<PREC, kForceEnd, TPK, kEnNone><<<nb, kBlock, 0, s>>>(d, p);
     } else {
-        k_force<PREC, kForceMid, TPK, false><<<nb, kBlock, 0, s>>>(d, p);
+        k_force<PREC, kForceMid, TPK, kEnNone><<<nb, kBlock, 0, s>>>(d, p);
     }
 }
 
 template <int PREC>
-static void launch_force_p(const Dev& d, const Params& p, int mode, bool energy, hipStream_t s) {
+static void launch_force_p(const Dev& d, const Params& p, int mode, int energy, hipStream_t s) {
     switch (p.tpk) {
         case 1: launch_force_pt<PREC, 1>(d, p, mode, energy, s); break;
         case 2: launch_force_pt<PREC, 2>(d, p, mode, energy, s); break;
@@ -2944,13 +2955,13 @@ static void launch_force_p(const Dev& d, const Params& p, int mode, bool energy,
 
 // Half list: clear F, accumulate it with the reactions, then integrate from it.
 template <int PREC>
-static void launch_force_half(const Dev& d, const Params& p, int mode, bool energy, hipStream_t s) {
+static void launch_force_half(const Dev& d, const Params& p, int mode, int energy, hipStream_t s) {
     const int nb = (p.nwave + 3) / 4;
     k_zero_f<<<grid_for_waves(p.nwave), kBlock, 0, s>>>(d, p);
-    if (energy)
-        k_force<PREC, kForceOnly, 1, true, true><<<nb, kBlock, 0, s>>>(d, p);
+    if (energy == kEnFull)
+        k_force<PREC, kForceOnly, 1, kEnFull, true><<<nb, kBlock, 0, s>>>(d, p);
     else
-        k_force<PREC, kForceOnly, 1, false, true><<<nb, kBlock, 0, s>>>(d, p);
+        k_force<PREC, kForceOnly, 1, kEnNone, true><<<nb, kBlock, 0, s>>>(d, p);
     if (mode == kForceEnd) {
         if (energy)
             k_kick_close<true><<<nb, kBlock, 0, s>>>(d, p);
@@ -2962,20 +2973,22 @@ static void launch_force_half(const Dev& d, const Params& p, int mode, bool ener
 }
 
 template <bool CLAMP>
-static void launch_force_rowtile_c(const Dev& d, const Params& p, int mode, bool energy, hipStream_t s) {
+static void launch_force_rowtile_c(const Dev& d, const Params& p, int mode, int energy, hipStream_t s) {
     const size_t lds = (size_t)p.scap * sizeof(U3);
     if (mode == kForceOnly) {
         if (energy)
-            k_force_t<kForceOnly, true, CLAMP><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
+            k_force_t<kForceOnly, kEnFull, CLAMP><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
         else
-            k_force_t<kForceOnly, false, CLAMP><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
+            k_force_t<kForceOnly, kEnNone, CLAMP><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
     } else if (mode == kForceEnd) {
-        if (energy)
-            k_force_t<kForceEnd, true, CLAMP><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
+        if (energy == kEnFull)
+            k_force_t<kForceEnd, kEnFull, CLAMP><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
+        else if (energy == kEnKe)
+            k_force_t<kForceEnd, kEnKe, CLAMP><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
         else
-            k_force_t<kForceEnd, false, CLAMP><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
+            k_force_t<kForceEnd, kEnNone, CLAMP><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
     } else {
-        k_force_t<kForceMid, false, CLAMP><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
+        k_force_t<kForceMid, kEnNone, CLAMP><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
     }
 }
 
@@ -2985,33 +2998,35 @@ int rowtile_blocks_per_cu(const Params& p) {
     int nb = 0;
     hipError_t e;
     if (p.precision == MD_PREC_FP64)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_force_t64<kForceMid, false>, kRtBlock,
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_force_t64<kForceMid, kEnNone>, kRtBlock,
                                                          (size_t)p.scap * sizeof(D3));
     else
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_force_t<kForceMid, false, true>, kRtBlock,
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_force_t<kForceMid, kEnNone, true>, kRtBlock,
                                                          (size_t)p.scap * sizeof(U3));
     if (e != hipSuccess || nb < 1) nb = 1;
     return nb;
 }
 
-static void launch_force_rowtile64(const Dev& d, const Params& p, int mode, bool energy, hipStream_t s) {
+static void launch_force_rowtile64(const Dev& d, const Params& p, int mode, int energy, hipStream_t s) {
     const size_t lds = (size_t)p.scap * sizeof(D3);
     if (mode == kForceOnly) {
         if (energy)
-            k_force_t64<kForceOnly, true><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
+            k_force_t64<kForceOnly, kEnFull><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
         else
-            k_force_t64<kForceOnly, false><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
+            k_force_t64<kForceOnly, kEnNone><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
     } else if (mode == kForceEnd) {
-        if (energy)
-            k_force_t64<kForceEnd, true><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
+        if (energy == kEnFull)
+            k_force_t64<kForceEnd, kEnFull><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
+        else if (energy == kEnKe)
+            k_force_t64<kForceEnd, kEnKe><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
         else
-            k_force_t64<kForceEnd, false><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
+            k_force_t64<kForceEnd, kEnNone><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
     } else {
-        k_force_t64<kForceMid, false><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
+        k_force_t64<kForceMid, kEnNone><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
     }
 }
 
-static void launch_force_rowtile(const Dev& d, const Params& p, int mode, bool energy, hipStream_t s) {
+static void launch_force_rowtile(const Dev& d, const Params& p, int mode, int energy, hipStream_t s) {
     if (p.precision == MD_PREC_FP64)
         launch_force_rowtile64(d, p, mode, energy, s);
     else if (p.clamp)
@@ -3020,7 +3035,7 @@ static void launch_force_rowtile(const Dev& d, const Params& p, int mode, bool e
         launch_force_rowtile_c<false>(d, p, mode, energy, s);
 }
 
-void launch_force(const Dev& d, const Params& p, int mode, bool energy, hipStream_t s) {
+void launch_force(const Dev& d, const Params& p, int mode, int energy, hipStream_t s) {
     if (p.tile) return launch_force_rowtile(d, p, mode, energy, s);
     if (p.half) {
         if (p.precision == MD_PREC_FP64)
@@ -3041,13 +3056,15 @@ void launch_kick_drift(const Dev& d, const Params& p, hipStream_t s) {
 void launch_dutc(const Dev& d, const Params& p, uint32_t seq, hipStream_t s) {
     k_dutc<<<p.nbox < 1024 ? p.nbox : 1024, kBlock, 0, s>>>(d, p, seq);
 }
-void launch_energy_reduce(const Dev& d, const Params& p, bool record, int thermo, bool tl, hipStream_t s) {
+void launch_energy_reduce(const Dev& d, const Params& p, bool record, int thermo, bool tl, int energy,
+                          hipStream_t s) {
+    const int ke_only = energy == kEnKe ? 1 : 0;
     const int nparts = tl ? p.maxcell : p.maxslot / kWave * p.tpk;  // a box has at most one row tile per cell
     const int nseg = (nparts + kRedSeg - 1) / kRedSeg;
     // at most kRedSeg partials per box: one launch instead of two
-    if (nseg > 1) k_energy_segments<<<dim3(nseg, p.nbox), kBlock, 0, s>>>(d, p, tl ? 1 : 0);
+    if (nseg > 1) k_energy_segments<<<dim3(nseg, p.nbox), kBlock, 0, s>>>(d, p, tl ? 1 : 0, ke_only);
     k_energy_reduce<<<p.nbox < 1024 ? p.nbox : 1024, kBlock, 0, s>>>(d, p, record ? 1 : 0, thermo, tl ? 1 : 0,
-                                                                    nseg > 1 ? 0 : 1);
+                                                                    nseg > 1 ? 0 : 1, ke_only);
 }
 void launch_ke_partial(const Dev& d, const Params& p, hipStream_t s) {
     k_ke_partial<<<grid_for_waves(p.nwave), kBlock, 0, s>>>(d, p);
