@@ -79,18 +79,18 @@ typedef enum {
 #define MD_F_GRAPH 2u              /* replay md_step chunks as captured HIP graphs (ensembles, and one
                                       box with MD_REBUILD_EVERY_STEP; other one-box runs enqueue a list
                                       build only where a step needs one and gain nothing from graphs) */
-#define MD_F_TILE_ON 4u            /* row tiles (threads_per_key 0 or 1; the FP32-mixed default for a
-                                      largest box of 2^23 particles or more): each row of cells is
-                                      cut into runs of cells whose partners (the 9 neighbouring rows,
-                                      one cell wider each side) a block stages in LDS once (fixed-point
-                                      records for FP32-mixed, FP64 positions for FP64); list entries
-                                      name staged records and the force pass reads every partner from
-                                      LDS.  A context whose cells are too crowded for the staging
-                                      capacity (about 2400 particles around one cell) switches to the
-                                      gather format by itself. */
+#define MD_F_TILE_ON 4u            /* row tiles (threads_per_key 0 or 1; the default for a largest box
+                                      of 3 * 2^18 particles or more, FP64 3 * 2^19, whose cells hold
+                                      4 to 36, FP64 30, on average): pairs of rows of
+                                      cells are cut into slices whose partners (the neighbouring
+                                      rows, one cell wider each side) a block stages in LDS once
+                                      (fixed-point records for FP32-mixed, FP64 positions for FP64);
+                                      list entries name staged records and the force pass reads every
+                                      partner from LDS.  A context whose cells are too crowded for the
+                                      staging capacity (2048 particles in a slice of one cell per row
+                                      and its neighbours) switches to the gather format by itself. */
 #define MD_F_TILE_OFF 8u           /* the gather format instead of row tiles (every partner read from
-                                      global memory by cell and rank; the default for FP64 and for
-                                      smaller FP32-mixed boxes) */
+                                      global memory by cell and rank; the default for other boxes) */
 #define MD_F_FAST_RCP 16u          /* FP64 path: 1/r^2 from the hardware reciprocal, with the
                                       correction of Sec. III.C applied to r^-6, r^-8, r^-12 and
                                       r^-14 (r^-2n ~ xt^n ((n + 1) - n xt r^2)) instead of a division */

@@ -25,7 +25,9 @@ using namespace mdg;
 namespace {
 
 constexpr int kChunk = 200;      // steps enqueued between status checks
-constexpr int64_t kTileMinN = 1 << 23;  // FP32-mixed boxes from this size take row tiles by default
+// Boxes that take row tiles by default (FP64, FP32-mixed): particles, and particles per cell.
+constexpr int64_t kTileMinN[2] = {3 << 19, 3 << 18};
+constexpr double kTileMinCell = 4.0, kTileMaxCell[2] = {30.0, 36.0};
 constexpr int kGraphSteps = 8;   // continuing steps per captured graph
 
 // Message of the last failed md_create / md_batch_create (no context exists then).
@@ -45,6 +47,7 @@ struct md_ctx {
     std::vector<BoxGeom> geom;
     int64_t ntotal = 0;
     int32_t nslot = 0, nwave = 0, ntile = 0, nrows = 0;
+    int64_t ntilemax = 0;          // row tiles at most: one per beam and x
     bool tile_fallback = false;    // a row tile overflowed its staging capacity: gather format from then on
     bool prefer_gather = false;    // gather format over row tiles: by size at creation, or md_autotune's choice
     double cell_scale = 0.0;       // > 0: cell side bound chosen by md_autotune (else the boxes' own)
@@ -219,7 +222,7 @@ void layout(md_ctx* c) {
     const double rl = c->prm.rc + c->prm.skin, side = rl * cell_scale_of(c);
     c->geom.assign(c->nbox, BoxGeom{});
     int32_t slot = 0, tile = 0, rows = 0;
-    int64_t id = 0;
+    int64_t id = 0, tiles = 0;
     for (int b = 0; b < c->nbox; ++b) {
         BoxGeom& g = c->geom[b];
         const md_params& p = c->boxes[b];
@@ -264,8 +267,12 @@ void layout(md_ctx* c) {
         g.id_off = (int32_t)id;
         id += p.n;
         g.row_off = rows;
-        rows += g.n[1] * g.n[2];
+        g.nby = (g.n[1] + kBy - 1) / kBy;
+        const int32_t nbeam = g.nby * ((g.n[2] + kBz - 1) / kBz);
+        rows += nbeam;
+        tiles += (int64_t)nbeam * g.n[0];
     }
+    c->ntilemax = tiles;
     c->nrows = rows;
     c->nslot = slot;
     c->nwave = slot / kWave;
@@ -296,7 +303,7 @@ md_status upload_geometry(md_ctx* c) {
         const BoxGeom& g = c->geom[b];
         for (int w = 0; w < g.nslot / kWave; ++w) wb[g.slot_off / kWave + w] = b;
         for (int t = 0; t < g.ntile; ++t) tb[g.tile_off + t] = b;
-        for (int r = 0; r < g.n[1] * g.n[2]; ++r) rb[g.row_off + r] = b;
+        for (int r = 0; r < g.nby * ((g.n[2] + kBz - 1) / kBz); ++r) rb[g.row_off + r] = b;
     }
     std::vector<double4> dsh(27 * c->nbox);
     for (int b = 0; b < c->nbox; ++b) {
@@ -344,13 +351,13 @@ md_status alloc_cells(md_ctx* c) {
     const size_t ncellpad = (size_t)c->ntile * kTile;
     // energy partials: per list wavefront, or per row tile (at most one per cell)
     const size_t nparts = std::max((size_t)c->nwave * 8, ncellpad);
-    if ((s = dalloc(c, &c->D.rtile, ncellpad)) != MD_OK) return s;
+    if ((s = dalloc(c, &c->D.rtile, c->ntilemax)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.row_box, c->nrows)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.row_nt, c->nrows)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.row_t0, c->nrows)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.cell_rt, ncellpad)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.rt_tmp, ncellpad)) != MD_OK) return s;
-    if ((s = dalloc(c, &c->D.rt_delta, ncellpad * 27)) != MD_OK) return s;
+    if ((s = dalloc(c, &c->D.rt_delta, c->ntilemax * kPieces)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.ke_part, nparts)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.pe_part, nparts)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.vir_part, nparts)) != MD_OK) return s;
@@ -957,17 +964,26 @@ md_status create_impl(const md_params* boxes, int32_t nbox, void* stream, md_ctx
         const bool fp64 = c->prm.precision == MD_PREC_FP64;
         tpk = c->ntotal < 98304 ? 4 : (c->ntotal < 262144 || fp64 ? 2 : 1);
     }
-    // Row tiles pay off on large boxes only: at 13.8M particles (FCC, density 0.5) their
-    // force pass is 11% and the step 3.5% faster than the gather format's, at 4M particles
-    // and below the gather format is 7-25% faster per step (the tile cuts cost rebuild time
-    // and the gather pass's partners still hit in L2).  So the FP32-mixed default takes
-    // them for a largest box of kTileMinN particles or more (md_autotune measures instead).
-    int64_t nmax = 0;
-    for (const md_params& bp : c->boxes) nmax = std::max(nmax, bp.n);
-    const bool mixed = c->prm.precision == MD_PREC_FP32_MIXED;
-    const bool tiles = !(c->prm.flags & (MD_F_TILE_OFF | MD_F_HALF_LIST)) &&
-                       ((c->prm.flags & MD_F_TILE_ON) || (mixed && nmax >= kTileMinN));
-    if (c->prm.threads_per_key == 0 && tiles) tpk = 1;
+    // Row tiles: their force pass is faster from about 100,000 particles on, but cutting the tiles
+    // costs four launches and a table per rebuild.  Whole steps, gathers / tiles (us): FP32-mixed 442,000
+    // particles 79.6 / 83.5, 1,049,000 143 / 131, 2,126,000 at density 0.7 with cutoff 3.0 461 / 407,
+    // 6,912,000 804 / 711; FP64 1,049,000 190 / 190, 2,126,000 645 / 626, 4,000,000 592 / 558, 6,912,000
+    // 1130 / 986.  So they are the default for a largest box of kTileMinN particles or more
+    // (md_autotune measures instead), where its cells hold kTileMinCell to kTileMaxCell on
+    // average: with fewer the copies of a slice outweigh its pairs (2M particles, one lane per key /
+    // tiles: 2.2 to a cell FP64 250 / 277, FP32-mixed 231 / 241; 4.5 to a cell 267 / 253, 230 / 205), with
+    // more its region is mostly margin, and many are near the staging capacity (two lanes / tiles:
+    // 31 to a cell FP64 734 / 735, FP32-mixed 493 / 465; 37 to a cell 897 / 1025, 632 / 626; 48 1175 / 1520,
+    // 832 / 861).
+    int big = 0;
+    for (int b = 1; b < c->nbox; ++b)
+        if (c->boxes[b].n > c->boxes[big].n) big = b;
+    const double percell = (double)c->boxes[big].n / c->geom[big].ncell;
+    const bool may = !(c->prm.flags & (MD_F_TILE_OFF | MD_F_HALF_LIST)) && c->prm.threads_per_key <= 1;
+    const bool pays = c->boxes[big].n >= kTileMinN[c->prm.precision] && percell >= kTileMinCell &&
+                      percell <= kTileMaxCell[c->prm.precision];
+    const bool tiles = may && ((c->prm.flags & MD_F_TILE_ON) || pays);
+    if (tiles) tpk = 1;
     c->prefer_gather = !tiles;
     if (c->prm.flags & MD_F_HALF_LIST) tpk = 1;
     c->P.tpk = tpk;

@@ -30,12 +30,13 @@
 //             partner's index in its key's staged row tile (below): the LDS byte
 //             offset of its 12-byte record.
 //   cells     per box ncell counters and starts, box ranges aligned to 1024-cell tiles.
-//   row tiles (FP32-mixed path) each row of cells (fixed cy, cz) is cut into runs of
-//             consecutive cells [xa, xb) holding at most kt keys whose staged partner
-//             region fits scap records.  The region is the 9 rows (cy+dy, cz+dz),
-//             dy, dz in {-1,0,1}, over the unwrapped cells xa-1 .. xb; a row's run is
-//             one contiguous range of slots, plus one wrapped cell at either x end
-//             ("pieces": row r = (dz+1)*3 + (dy+1), side 0 = cell x = -1, 1 = the
+//   row tiles rows of cells are taken kBy x kBz at a time ("beams": rows (cy, cz) with cy in
+//             [y0, y0 + by), cz in [z0, z0 + bz), fewer at the box's end), and a beam is cut
+//             along x into runs of consecutive cells [xa, xb) holding at most kt keys whose
+//             staged partner region fits scap records.  The region is the rows
+//             y0 - 1 .. y0 + by, z0 - 1 .. z0 + bz over the unwrapped cells xa-1 .. xb; a row's
+//             run is one contiguous range of slots, plus one wrapped cell at either x end
+//             ("pieces": row r = (dz+1)*(kBy+2) + (dy+1), side 0 = cell x = -1, 1 = the
 //             run inside [0, n), 2 = cell x = n).  Staged index order: piece by piece,
 //             slots in order, so every cell's members are consecutive.
 #pragma once
@@ -67,8 +68,12 @@ constexpr int kNeedStripes = 256;        // slots per box for the longest list o
 constexpr int kNeedStride = 16;          // 64 bytes between slots
 constexpr int kTileWMax = 64;            // cells per row tile at most
 constexpr int kScapMax = 5461;           // staged records per row tile at most (16-bit entries of 12 * index)
+constexpr int kBy = 2, kBz = 1;          // rows of cells per beam
+constexpr int kBeamRows = kBy * kBz;
+constexpr int kPieces = (kBy + 2) * (kBz + 2) * 3;  // pieces of a staged region: one lane each
+static_assert(kPieces <= 64, "one lane per piece");
 constexpr int kRtBlock = 256;            // threads per block of the row-tile force kernel (keys per tile)
-constexpr int kStageCap = 2432;          // staged records per row tile (28.5 KB of LDS)
+constexpr int kStageCap = 2048;          // staged records per row tile (24 KB of LDS, FP64 48 KB)
 constexpr int kRedSeg = 2048;            // energy partials per first-level segment
 
 // Position record of one slot.  cc and cnt ride in the 8 bytes a double4
@@ -102,7 +107,8 @@ struct BoxGeom {
     int32_t npart;
     int32_t nslot;
     int32_t id_off;    // first caller index of this box
-    int32_t row_off;   // first global row of cells (row = cz * ny + cy within the box)
+    int32_t row_off;   // first global beam (beam = (cz / kBz) * nby + cy / kBy within the box)
+    int32_t nby;       // beams along y: ceil(ny / kBy)
     // division by d = n[0], n[1], n[0] * n[1] (k = 0, 1, 2) for 0 <= x < 2^30 as
     // (x * dmul[k]) >> (32 + dshr[k]), with dmul = floor(2^(30 + l) / d) + 1 and
     // dshr = l - 2, l = ceil(log2 d): exact over that range, since the multiplier's
@@ -148,7 +154,7 @@ struct Params {
     int32_t recb;       // bytes per staged record: 12 (FP32-mixed fixed point), 24 (FP64 x, y, z)
     int32_t tgrid;      // blocks of the row-tile force kernel: one resident round (each loops over tiles)
     int32_t clamp;      // Eq. 1 cutoff (f(rc) = 0): FP32-mixed forces clamp 1/r^2 at 1/rc^2 instead of masking
-    int32_t nrows;      // rows of cells over all boxes
+    int32_t nrows;      // beams over all boxes
     int32_t fastrcp;    // FP64 forces from the hardware reciprocal with the correction of r^-8, r^-14
     int32_t half;       // half list (each pair once, forward stencil cells), partner forces by atomics
     int32_t maxslot;    // slots of the largest box
@@ -186,16 +192,16 @@ struct Dev {
     int32_t* tile_sum;
     int32_t* tile_pref;
     int32_t* need_s;     // [nbox][kNeedStripes] striped maximum list length of the running build, stride kNeedStride
-    int4* rtile;         // row tiles: (box, row cz * ny + cy, xa, xb), in global row order
-    int32_t* row_box;    // box of each global row
-    int32_t* row_nt;     // row tiles per row
-    int32_t* row_t0;     // first row tile of each row (exclusive scan of row_nt)
+    int4* rtile;         // row tiles: (box, y0 | z0 << 16, xa, xb), in global beam order
+    int32_t* row_box;    // box of each global beam
+    int32_t* row_nt;     // row tiles per beam
+    int32_t* row_t0;     // first row tile of each beam (exclusive scan of row_nt)
     int32_t* ntiles;     // [0] row tiles in all; then the post-build kernel's counters at stride kPostStride:
                          // groups done, blocks done per group (the last to count resets each)
     int32_t* box_t0;     // [nbox + 1] first row tile of each box, then the total
     int32_t* cell_rt;    // row tile of each cell
-    int32_t* rt_tmp;     // per cell: xa | xb << 16 of the row's k-th tile at (row's first cell + k)
-    int32_t* rt_delta;   // [tile][27]: staged index minus first slot of each piece of the tile
+    int32_t* rt_tmp;     // xa | xb << 16 of the beam's k-th tile at (first cell of its first row + k)
+    int32_t* rt_delta;   // [tile][kPieces]: staged index minus first slot of each piece of the tile
     unsigned long long* vmax_s;  // [nbox][kStripes] striped max |v|^2 (bits), stride kStripeStride
     unsigned long long* disp_s;  // [nbox][kStripes] striped max |q - q_build|^2 (bits)
     double* ke_part;     // per list wave

@@ -325,28 +325,28 @@ __device__ __forceinline__ int entry_slot(const Dev& d, uint32_t cc, uint32_t e,
     return d.cell_start[stencil_cell(cc, (int)(e >> kOffBits), g, &img)] + (int)(e & (kMaxCellCount - 1));
 }
 
-__device__ __forceinline__ void tile_piece(const Dev& d, const BoxGeom& g, int cy, int cz, int xa, int xb, int p,
+__device__ __forceinline__ void tile_piece(const Dev& d, const BoxGeom& g, int y0, int z0, int xa, int xb, int p,
                                            int& s0, int& len, int& ox, int& oy, int& oz);
 
-// First slots and lengths of the 27 pieces staged for the row tile of the key whose
+// First slots and lengths of the pieces staged for the row tile of the key whose
 // cell is cc (diagnostics: decoding of row-tile entries).
 __device__ void tile_pieces_of(const Dev& d, const BoxGeom& g, uint32_t cc, int* ps0, int* plen) {
     const int cx = (int)(cc & 1023), cy = (int)((cc >> 10) & 1023), cz = (int)(cc >> 20);
     const int4 tr = d.rtile[d.cell_rt[g.cell_off + (cz * g.n[1] + cy) * g.n[0] + cx]];
-    for (int pc = 0; pc < 27; ++pc) {
+    for (int pc = 0; pc < kPieces; ++pc) {
         int ox, oy, oz;
-        tile_piece(d, g, cy, cz, tr.z, tr.w, pc, ps0[pc], plen[pc], ox, oy, oz);
+        tile_piece(d, g, tr.y & 0xffff, tr.y >> 16, tr.z, tr.w, pc, ps0[pc], plen[pc], ox, oy, oz);
     }
 }
 
 // Slot behind a row-tile entry (recb * staged index), given the tile's pieces.
 __device__ int tile_slot(const int* ps0, const int* plen, uint32_t e, int recb) {
     int idx = (int)(e / (uint32_t)recb);
-    for (int pc = 0; pc < 27; ++pc) {
+    for (int pc = 0; pc < kPieces; ++pc) {
         if (idx < plen[pc]) return ps0[pc] + idx;
         idx -= plen[pc];
     }
-    return ps0[13];  // not reached for an entry the build wrote
+    return ps0[0];  // not reached for an entry the build wrote
 }
 
 // Exclusive scan of the keys' list lengths (key_ptr[i + 1] = length of caller id i) into
@@ -430,11 +430,11 @@ __global__ __launch_bounds__(kBlock) void k_list_export(Dev d, Params p, const i
         const uint32_t cc = d.q[d.st[b].sq][s].cc;
         // row-tile format: lane pc holds piece pc of the key's tile
         int ps0 = 0, plen = 0;
-        if (p.tile && l < 27) {
+        if (p.tile && l < kPieces) {
             const int cx = (int)(cc & 1023), cy = (int)((cc >> 10) & 1023), cz = (int)(cc >> 20);
             const int4 tr = d.rtile[d.cell_rt[g.cell_off + (cz * g.n[1] + cy) * g.n[0] + cx]];
             int ox, oy, oz;
-            tile_piece(d, g, cy, cz, tr.z, tr.w, l, ps0, plen, ox, oy, oz);
+            tile_piece(d, g, tr.y & 0xffff, tr.y >> 16, tr.z, tr.w, l, ps0, plen, ox, oy, oz);
         }
         const int pend = wave_incl_sum(plen);  // staged index after the piece
         auto partner = [&](int e) -> int32_t {   // every lane calls it; INT_MAX beyond the list
@@ -444,7 +444,7 @@ __global__ __launch_bounds__(kBlock) void k_list_export(Dev d, Params p, const i
                 const int idx = (int)(en / (uint32_t)p.recb);
                 slot = 0;
                 int from = 0;
-                for (int pc = 0; pc < 27; ++pc) {
+                for (int pc = 0; pc < kPieces; ++pc) {
                     const int end = __builtin_amdgcn_readlane(pend, pc);
                     if (idx >= from && idx < end) slot = __builtin_amdgcn_readlane(ps0, pc) + idx - from;
                     from = end;
@@ -814,25 +814,26 @@ __global__ __launch_bounds__(kBlock) void k_rank_permute(Dev d, Params p) {
 
 __device__ __forceinline__ int wrap_idx(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
 
-// Piece p = r * 3 + side (r = (dz+1)*3 + (dy+1)) of the staged partner region of the
-// row tile with home cells [xa, xb) of row (cy, cz): its first slot, its length (0 if
-// the piece is absent) and the image terms its fixed-point records take on, so that
-// every staged record is in the unwrapped frame of the home row.
+// Piece p = r * 3 + side (r = (dz+1)*(kBy+2) + (dy+1)) of the staged partner region of the
+// row tile with home cells [xa, xb) of the beam that starts at row (y0, z0): its first slot, its
+// length (0 if the piece is absent) and the image terms its fixed-point records take on, so that
+// every staged record is in the unwrapped frame of the home rows.
 //   side 0: unwrapped cell x = -1, i.e. cell n-1 one box length down (only if xa == 0)
 //   side 1: cells max(xa-1, 0) .. min(xb, n-1), one contiguous run of slots
 //   side 2: unwrapped cell x = n, i.e. cell 0 one box length up (only if xb == n)
-__device__ __forceinline__ void tile_piece(const Dev& d, const BoxGeom& g, int cy, int cz, int xa, int xb, int p,
+__device__ __forceinline__ void tile_piece(const Dev& d, const BoxGeom& g, int y0, int z0, int xa, int xb, int p,
                                            int& s0, int& len, int& ox, int& oy, int& oz) {
-    const int r = (p * 11) >> 5, side = p - 3 * r;  // p / 3 for p < 27
-    const int rz = (r * 11) >> 5, ry = r - 3 * rz;
+    const int r = (p * 43) >> 7, side = p - 3 * r;  // p / 3 for p < 64
+    const int rz = r / (kBy + 2), ry = r - (kBy + 2) * rz;
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-    const int y = cy + ry - 1, z = cz + rz - 1;
+    const int y = y0 + ry - 1, z = z0 + rz - 1;
     s0 = 0;
     len = 0;
     // image terms modulo 2^32: a cell index that wrapped below 0 takes -n * uoff, above n-1 +n * uoff
     ox = side == 0 ? -g.nuoff[0] : (side == 2 ? g.nuoff[0] : 0);
     oy = y < 0 ? -g.nuoff[1] : (y >= ny ? g.nuoff[1] : 0);
     oz = z < 0 ? -g.nuoff[2] : (z >= nz ? g.nuoff[2] : 0);
+    if (y > ny || z > nz) return;  // beyond the neighbours of a beam cut short by the box's end
     int x0, x1;
     if (side == 0) {
         if (xa > 0) return;
@@ -852,17 +853,17 @@ __device__ __forceinline__ void tile_piece(const Dev& d, const BoxGeom& g, int c
 // Periodic image of piece p of a row tile's staged region, per axis in {-1, 0, 1}:
 // -1 where the piece's cells wrapped below 0 (their positions are taken minus L),
 // +1 above n - 1 (plus L).  The same cases as tile_piece's fixed-point terms.
-__device__ __forceinline__ void tile_piece_img(const BoxGeom& g, int cy, int cz, int p, int& rx, int& ry, int& rz) {
-    const int r = (p * 11) >> 5, side = p - 3 * r;
-    const int rzz = (r * 11) >> 5, ryy = r - 3 * rzz;
-    const int y = cy + ryy - 1, z = cz + rzz - 1;
+__device__ __forceinline__ void tile_piece_img(const BoxGeom& g, int y0, int z0, int p, int& rx, int& ry, int& rz) {
+    const int r = (p * 43) >> 7, side = p - 3 * r;
+    const int rzz = r / (kBy + 2), ryy = r - (kBy + 2) * rzz;
+    const int y = y0 + ryy - 1, z = z0 + rzz - 1;
     rx = side == 0 ? -1 : (side == 2 ? 1 : 0);
     ry = y < 0 ? -1 : (y >= g.n[1] ? 1 : 0);
     rz = z < 0 ? -1 : (z >= g.n[2] ? 1 : 0);
 }
 
-// Cuts every row of cells into row tiles, greedily from x = 0: a tile grows by the
-// next cell while its keys stay within kt, its staged region within scap records and
+// Cuts every beam into row tiles, greedily from x = 0: a tile grows by the
+// next slice of cells while its keys stay within kt, its staged region within scap records and
 // its width within kTileWMax cells.  One wavefront per row.  The column sums of the
 // 3 x 3 rows around it (cells x = -1 .. n, unwrapped) and the row's own counts go to
 // LDS as prefix sums; every lane then finds, for the cells x it holds, where a tile
@@ -902,24 +903,27 @@ __global__ __launch_bounds__(kBlock) void k_row_tiles(Dev d, Params p) {
         const int b = ld_const(d.row_box + row);
         const BoxGeom g = ld_geom(d.geom + b);
         const int lr = row - g.row_off, nx = g.n[0], ny = g.n[1], nz = g.n[2];
-        const int cy = lr % ny, cz = lr / ny;
-        // the 9 row starts, then the counts of 4 x positions per lane in flight at once
-        int rs[9];
-#pragma unroll
-        for (int r = 0; r < 9; ++r)
-            rs[r] = g.cell_off + (wrap_idx(cz + r / 3 - 1, nz) * ny + wrap_idx(cy + r % 3 - 1, ny)) * nx;
-        constexpr int kXu = 4;
+        const int z0 = lr / g.nby * kBz, y0 = (lr - lr / g.nby * g.nby) * kBy;
+        const int by = min(kBy, ny - y0), bz = min(kBz, nz - z0);
+        constexpr int kXu = 4;  // x positions per lane in flight at once
         for (int x0 = l - 1; x0 <= nx; x0 += kWave * kXu) {
             int sum[kXu], own[kXu];
 #pragma unroll
             for (int u = 0; u < kXu; ++u) {
                 const int x = x0 + u * kWave, xw = wrap_idx(min(x, nx), nx);
                 sum[u] = 0;
+                own[u] = 0;
                 if (x <= nx) {
-#pragma unroll
-                    for (int r = 0; r < 9; ++r) sum[u] += d.cell_cnt[rs[r] + xw];
+                    for (int rz = 0; rz < bz + 2; ++rz) {
+                        const int zc = wrap_idx(z0 + rz - 1, nz) * ny;
+                        for (int ry = 0; ry < by + 2; ++ry) {
+                            const int m = d.cell_cnt[g.cell_off + (zc + wrap_idx(y0 + ry - 1, ny)) * nx + xw];
+                            sum[u] += m;
+                            // the beam's own rows
+                            if (x >= 0 && x < nx && ry >= 1 && ry <= by && rz >= 1 && rz <= bz) own[u] += m;
+                        }
+                    }
                 }
-                own[u] = x >= 0 && x < nx ? d.cell_cnt[rs[4] + x] : 0;  // r = 4: the row itself
             }
 #pragma unroll
             for (int u = 0; u < kXu; ++u) {
@@ -947,7 +951,7 @@ __global__ __launch_bounds__(kBlock) void k_row_tiles(Dev d, Params p) {
         }
         wave_sync();
         if (l == 0) {
-            const int base = g.cell_off + lr * nx;  // the row's cells hold its tiles in rt_tmp
+            const int base = g.cell_off + (z0 * ny + y0) * nx;  // the first row's cells hold the tiles in rt_tmp
             int nt = 0, xa = 0, big = 0;
             while (xa < nx) {
                 const int xb = nxt[xa];
@@ -957,7 +961,7 @@ __global__ __launch_bounds__(kBlock) void k_row_tiles(Dev d, Params p) {
                 xa = xb;
             }
             d.row_nt[row] = nt;
-            if (big > p.scap) {  // only a one-cell tile can exceed it; the step stops here
+            if (big > p.scap) {  // only a one-slice tile can exceed it; the step stops here
                 atomicOr(&d.st[b].err, 4);
                 atomicOr(d.halt, 1);
             }
@@ -1015,13 +1019,17 @@ __global__ __launch_bounds__(kBlock) void k_row_write(Dev d, Params p) {
     for (int row = blockIdx.x * 4 + wave_in_block(); row < p.nrows; row += gridDim.x * 4) {
         const int b = ld_const(d.row_box + row);
         const BoxGeom g = ld_geom(d.geom + b);
-        const int lr = row - g.row_off, base = g.cell_off + lr * g.n[0];
+        const int lr = row - g.row_off, z0 = lr / g.nby * kBz, y0 = (lr - lr / g.nby * g.nby) * kBy;
+        const int base = g.cell_off + (z0 * g.n[1] + y0) * g.n[0];
+        const int by = min(kBy, g.n[1] - y0), bz = min(kBz, g.n[2] - z0);
         const int nt = d.row_nt[row], t0 = d.row_t0[row];
         for (int k = l; k < nt; k += kWave) {
             const int v = d.rt_tmp[base + k];
             const int xa = v & 0xffff, xb = v >> 16;
-            d.rtile[t0 + k] = make_int4(b, lr, xa, xb);
-            for (int x = xa; x < xb; ++x) d.cell_rt[base + x] = t0 + k;
+            d.rtile[t0 + k] = make_int4(b, y0 | (z0 << 16), xa, xb);
+            for (int z = 0; z < bz; ++z)
+                for (int y = 0; y < by; ++y)
+                    for (int x = xa; x < xb; ++x) d.cell_rt[base + (z * g.n[1] + y) * g.n[0] + x] = t0 + k;
         }
     }
 }
@@ -1037,12 +1045,11 @@ __global__ __launch_bounds__(kBlock) void k_row_delta(Dev d, Params p) {
         const int4 tr = d.rtile[t];
         const int b = __builtin_amdgcn_readfirstlane(tr.x);
         const BoxGeom g = ld_geom(d.geom + b);
-        const int lr = __builtin_amdgcn_readfirstlane(tr.y);
+        const int yz = __builtin_amdgcn_readfirstlane(tr.y);
         int ps0 = 0, plen = 0, ox, oy, oz;
-        const int lz = gdiv(g, lr, 1);
-        if (l < 27) tile_piece(d, g, lr - lz * g.n[1], lz, tr.z, tr.w, l, ps0, plen, ox, oy, oz);
+        if (l < kPieces) tile_piece(d, g, yz & 0xffff, yz >> 16, tr.z, tr.w, l, ps0, plen, ox, oy, oz);
         const int pbase = wave_incl_sum(plen) - plen;
-        if (l < 27) d.rt_delta[t * 27 + l] = pbase - ps0;
+        if (l < kPieces) d.rt_delta[(size_t)t * kPieces + l] = pbase - ps0;
     }
 }
 
@@ -1401,15 +1408,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6, 8))) 
         int pre = incl - cnt;
         // entry of candidate ci of the lane's stencil cell s: ekey + ci (gather format:
         // s << 11 plus its rank; row-tile format: its index in the staged region of the
-        // home cell's row tile, whose piece p = r * 3 + side holds unwrapped cells in order)
+        // home cell's row tile, whose pieces hold unwrapped cells in order)
         int ekey = (s_of_l << kOffBits) - pre;
         if constexpr (TL) {
             // staged index of the stencil cell's first member: its first slot plus the
             // (staged index - first slot) of the piece of the home cell's row tile holding it
-            const int r = s_of_l / 3, x = cx + s_of_l % 3 - 1;
+            const int x = cx + s_of_l % 3 - 1;
+            const int r = (cz % kBz + s_of_l / 9) * (kBy + 2) + cy % kBy + (s_of_l / 3) % 3;
             const int pc = r * 3 + (x < 0 ? 0 : (x >= g.n[0] ? 2 : 1));
             const int rt = ld_const(d.cell_rt + c);
-            ekey = (l < 27 ? start + d.rt_delta[rt * 27 + pc] : 0) - pre;
+            ekey = (l < 27 ? start + d.rt_delta[(size_t)rt * kPieces + pc] : 0) - pre;
         }
         const int total = __builtin_amdgcn_readlane(incl, 26);
         const bool wrap = __ballot(img != 0) != 0ull;  // uniform: this cell touches the box boundary
@@ -1646,7 +1654,7 @@ __device__ __forceinline__ void force_finish(const Dev& d, const Params& p, cons
 // entry names a stencil cell and a rank in it; the wavefront first tabulates, in
 // LDS, the 27 stencil cells of each distinct cell its keys live in: FP64 keeps
 // the start slot and the periodic image code, FP32-mixed the start slot and the
-// fixed-point stencil offset (one 16-byte record).  The cutoff test is a select,
+// fixed-point stencil offset.  The cutoff test is a select,
 // not a branch (as Algorithm 1's mask w), and only a lane's last, partial chunk
 // of entries pays for an end-of-list check.
 constexpr int kHomeMax = 12;  // distinct key cells per wavefront served from LDS
@@ -2009,30 +2017,110 @@ __global__ __launch_bounds__(kBlock) void k_force(Dev d, Params p) {
                                                 pe, vir, f_done);
 }
 
-// FP32-mixed pair forces from a row tile staged in LDS (row-tile list format, one
-// lane per key).  A block takes a row tile: wavefront 0 works out the 27 pieces of
-// its staged region, the block copies them from the fixed-point array into LDS as
-// 16-byte records (coalesced runs of slots; the pieces' image terms added, so every
-// record is in the unwrapped frame of the home row), then each lane walks one key's
-// list, whose entries are the records' LDS byte offsets.  A pair separation is one
-// integer subtraction per axis (exact, modulo 2^32) and one conversion to FP32; the
-// arithmetic after that, and the summation order, are those of the gather kernel,
-// so both give the same forces bit for bit.  The integration (kicks, drift,
-// fixed-point re-encoding, DUTC maximum) follows in the same pass; energy partials
-// are summed per tile in a fixed order.  A tile whose region exceeds scap is
-// skipped (its build has stopped the step; the host switches to the gather format
-// and goes on from that build).
+// A row tile as its block's wavefronts see it: the pieces of its staged region that are not
+// empty (a per-wavefront table in LDS: slot minus staged index, image terms; and the first
+// staged index of piece o in lane o), and its keys, one run of slots per row of the beam.
+struct TileTab {
+    int4 pc[kPieces];
+    int st[kPieces];
+};
+struct Tile {
+    int S;              // staged records
+    int np;             // pieces
+    int cstart;         // lane o: first staged index of piece o
+    int K;              // keys
+    int ka[kBeamRows];  // per row: slot minus key index,
+    int kf[kBeamRows];  // and the keys before the next row
+};
+// Every wavefront works the tile out itself (lane p holds piece p): no barrier.  FP64: the image
+// terms as box lengths, -1, 0 or 1, else in fixed-point units.
+template <bool FP64>
+__device__ __forceinline__ Tile tile_open(const Dev& d, const BoxGeom& g, int yz, int xa, int xb, TileTab& tab) {
+    const int l = lane_id();
+    const int y0 = yz & 0xffff, z0 = yz >> 16;
+    Tile t;
+    int ps0 = 0, plen = 0, ox = 0, oy = 0, oz = 0;
+    if (l < kPieces) {
+        tile_piece(d, g, y0, z0, xa, xb, l, ps0, plen, ox, oy, oz);
+        if (FP64) tile_piece_img(g, y0, z0, l, ox, oy, oz);
+    }
+    const int incl = wave_incl_sum(plen);
+    t.S = __builtin_amdgcn_readlane(incl, kWave - 1);
+    const unsigned long long ne = __builtin_amdgcn_ballot_w64(plen > 0);
+    t.np = __popcll(ne);
+    const int o = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(ne >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)ne, 0u));
+    if (plen > 0) {
+        tab.pc[o] = make_int4(ps0 - (incl - plen), ox, oy, oz);
+        tab.st[o] = incl - plen;
+    }
+    t.K = 0;
+#pragma unroll
+    for (int r = 0; r < kBeamRows; ++r) {
+        const int y = y0 + r % kBy, z = z0 + r / kBy;
+        int n = 0, a = 0;
+        if (y < g.n[1] && z < g.n[2]) {
+            const int rowc = g.cell_off + (z * g.n[1] + y) * g.n[0];
+            a = ld_const(d.cell_start + rowc + xa);
+            n = ld_const(d.cell_start + rowc + xb - 1) + ld_const(d.cell_cnt + rowc + xb - 1) - a;
+        }
+        t.ka[r] = a - t.K;
+        t.K += n;
+        t.kf[r] = t.K;
+    }
+    wave_lds_sync();
+    t.cstart = tab.st[min(l, max(t.np, 1) - 1)];
+    return t;
+}
+// Slot of key k of the tile.
+__device__ __forceinline__ int tile_key(const Tile& t, int k) {
+    int a = t.ka[0];
+#pragma unroll
+    for (int r = 1; r < kBeamRows; ++r) a = k >= t.kf[r - 1] ? t.ka[r] : a;
+    return a + k;
+}
+// The table's record of staged index c * 64 + lane: the piece of the chunk's first record by a
+// ballot, then one comparison per piece that starts inside the chunk (about one).
+__device__ __forceinline__ int4 tile_rec(const Tile& t, const TileTab& tab, int c) {
+    const int l = lane_id(), i = c * kWave + l;
+    const int p0 = __popcll(__builtin_amdgcn_ballot_w64(l < t.np && t.cstart <= c * kWave)) - 1;
+    int pp = p0;
+    for (int q = p0 + 1; q < t.np; ++q) {
+        const int nx = __builtin_amdgcn_readlane(t.cstart, q);
+        if (nx >= c * kWave + kWave) break;
+        pp += i >= nx ? 1 : 0;
+    }
+    return tab.pc[pp];
+}
+
+// FP32-mixed pair forces from a row tile staged in LDS (row-tile list format, one lane per
+// key).  A block takes a row tile: its wavefronts work out the pieces of the staged region
+// (tile_open), copy them from the fixed-point array into LDS as 12-byte records in chunks of 64
+// (coalesced runs of slots; the pieces' image terms added, so every record is in the unwrapped
+// frame of the home rows), then each lane walks one key's list, whose entries are the records'
+// LDS byte offsets.  A pair separation is one integer subtraction per axis (exact, modulo 2^32)
+// and one conversion to FP32; the arithmetic after that, and the summation order, are those of
+// the gather kernel, so both give the same forces bit for bit.  The integration (kicks, drift,
+// fixed-point re-encoding, DUTC maximum) follows in the same pass; energy partials are summed
+// per tile in a fixed order.  A tile whose region exceeds scap is skipped (its build has stopped
+// the step; the host switches to the gather format and goes on from that build).
 // CLAMP (the Eq. 1 cutoff, whose f(rc) is 0): a list entry beyond rc is evaluated at
 // rc instead of being masked, 1/r^2 = max(1/r^2, 1/rc^2) (one instruction for a
 // compare and a select); f(rc) rounds to a few 1e-9 in FP32.
+// Bound by the pair arithmetic (a gather pass is bound by one lane-load per clock and CU).  Tiles
+// two rows high stage 12 rows for the keys of two, where single rows staged 9 for one: a third
+// fewer records per key, and tiles long enough to fill 256 lanes.  Mid-step pass (us), gathers /
+// single rows / these: 1M particles 98 / 97.5 / 80.6, 16M 1408 / 1159 / 1095, 2M with cutoff 3.0
+// 326 / 292 / 258.  2 x 2 rows: 16M 1209; 3 x 1: 1201; 512 threads and 2720 records: 1241; 1920
+// records: 1117.  Four wavefronts per SIMD also where the energies would take 138 registers: the
+// closing pass of 2M particles with all energies 306 -> 262 us, in spite of 10 spills.
 template <int MODE, int ENERGY, bool CLAMP>
-__global__ __launch_bounds__(kRtBlock) void k_force_t(Dev d, Params p) {
+__global__ __launch_bounds__(kRtBlock, 4) void k_force_t(Dev d, Params p) {
     if (step_off(d)) return;
     constexpr int NW = kRtBlock / kWave;  // wavefronts per block
     constexpr int U = 8;       // entries per 16-byte list chunk
-    constexpr int kPc = 27;    // pieces of a staged region
     constexpr int kCopy = 4;   // copy chunks per wavefront in flight
     extern __shared__ U3 stg[];  // p.scap records of 12 bytes
+    __shared__ __align__(16) TileTab tabs[NW];
     __shared__ double red[3][NW];
     const int l = lane_id(), wib = wave_in_block();
     const int ntl = ld_const(d.ntiles);
@@ -2044,66 +2132,47 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t(Dev d, Params p) {
         const int4 tr = d.rtile[t];
         const int b = __builtin_amdgcn_readfirstlane(tr.x);
         const BoxGeom g = ld_geom(d.geom + b);
-        const int lr = __builtin_amdgcn_readfirstlane(tr.y), xa = __builtin_amdgcn_readfirstlane(tr.z),
+        const int yz = __builtin_amdgcn_readfirstlane(tr.y), xa = __builtin_amdgcn_readfirstlane(tr.z),
                   xb = __builtin_amdgcn_readfirstlane(tr.w);
-        const int cz = gdiv(g, lr, 1), cy = lr - cz * g.n[1];
         const int sq = ld_const(&d.st[b].sq), sp = ld_const(&d.st[b].sp);
-        // every wavefront works out the pieces itself (lane p holds piece p): no barrier
-        int ps0 = 0, plen = 0, pox = 0, poy = 0, poz = 0;
-        if (l < kPc) tile_piece(d, g, cy, cz, xa, xb, l, ps0, plen, pox, poy, poz);
-        const int pincl = wave_incl_sum(plen);
-        const int S = __builtin_amdgcn_readlane(pincl, kPc - 1);
-        // keys: the home cells [xa, xb) of the home row (inside piece 13)
-        const int rowc = g.cell_off + (cz * g.n[1] + cy) * g.n[0];
-        const int k0 = ld_const(d.cell_start + rowc + xa);
-        const int k1 = ld_const(d.cell_start + rowc + xb - 1) + ld_const(d.cell_cnt + rowc + xb - 1);
-        if (S > p.scap) continue;  // uniform over the block; nothing staged yet
+        TileTab& tab = tabs[wib];
+        const Tile tl = tile_open<false>(d, g, yz, xa, xb, tab);
+        if (tl.S > p.scap || tl.K == 0) {  // uniform over the block; nothing staged yet
+            if (ENERGY && threadIdx.x == 0) d.ke_part[t] = d.pe_part[t] = d.vir_part[t] = 0.0;
+            continue;
+        }
         // this thread's first key: its record, velocity and first two list chunks, fetched
         // while the block stages (a list holds at least 8 entries per lane, 16 when rows >= 16)
-        int kb = k0;
-        int key = kb + (int)threadIdx.x;
-        bool active = key < k1;
-        int ks = active ? key : k0;
-        Pos qi = d.q[sq][ks];
-        double v0x = ld_stream(d.vx[sp] + ks), v0y = ld_stream(d.vy[sp] + ks), v0z = ld_stream(d.vz[sp] + ks);
-        const uint4* __restrict__ l4 = reinterpret_cast<const uint4*>(d.list) + (size_t)(ks >> 6) * p.rows * 8 + (ks & 63);
+        int kb = 0;
+        bool active = (int)threadIdx.x < tl.K;
+        int key = tile_key(tl, active ? (int)threadIdx.x : 0);
+        Pos qi = d.q[sq][key];
+        double v0x = ld_stream(d.vx[sp] + key), v0y = ld_stream(d.vy[sp] + key), v0z = ld_stream(d.vz[sp] + key);
+        const uint4* __restrict__ l4 =
+            reinterpret_cast<const uint4*>(d.list) + (size_t)(key >> 6) * p.rows * 8 + (key & 63);
         uint4 raw_a = ld_stream(l4);
         uint4 raw_b = p.rows >= 16 ? ld_stream(l4 + kWave) : make_uint4(0u, 0u, 0u, 0u);
-        // stage: 64-record chunk c of the pieces goes to wavefront c % NW; the chunk's
-        // piece is the number of pieces whose chunks all lie before it.  Per piece p
-        // (first chunk cs): record c * 64 + l of the pieces' chunk space comes from slot
-        // src_p + c * 64 + l and goes to dst_p + c * 64 + l while c * 64 + l < end_p.
-        {
-            const int pch = (plen + kWave - 1) >> 6;  // 64-record copy chunks of piece l
-            const int chincl = wave_incl_sum(pch);
-            const int NC = __builtin_amdgcn_readlane(chincl, kPc - 1);
-            const int cs = chincl - pch;
-            const int src = ps0 - kWave * cs, dst = (pincl - plen) - kWave * cs, end = plen + kWave * cs;
+        {  // stage: 64-record chunk c of the region goes to wavefront c % NW
             const int32_t* __restrict__ u = d.u[sq];
-            for (int c0 = wib; c0 < NC; c0 += NW * kCopy) {
+            for (int c0 = wib; c0 * kWave < tl.S; c0 += NW * kCopy) {
                 U3 v[kCopy];
-                int at[kCopy], ox[kCopy], oy[kCopy], oz[kCopy];
+                int4 rec[kCopy];
 #pragma unroll
                 for (int k = 0; k < kCopy; ++k) {
-                    const int c = c0 + NW * k;
-                    at[k] = -1;
-                    if (c < NC) {  // uniform
-                        const int pc = __popcll(__ballot(l < kPc && chincl <= c));
-                        const int i = c * kWave + l;
-                        ox[k] = __builtin_amdgcn_readlane(pox, pc);
-                        oy[k] = __builtin_amdgcn_readlane(poy, pc);
-                        oz[k] = __builtin_amdgcn_readlane(poz, pc);
-                        if (i < __builtin_amdgcn_readlane(end, pc)) {
-                            v[k] = *reinterpret_cast<const U3*>(u + 3 * (__builtin_amdgcn_readlane(src, pc) + i));
-                            at[k] = __builtin_amdgcn_readlane(dst, pc) + i;
-                        }
+                    const int c = c0 + NW * k, i = c * kWave + l;
+                    if (c * kWave < tl.S) {  // uniform
+                        rec[k] = tile_rec(tl, tab, c);
+                        if (i < tl.S) v[k] = *reinterpret_cast<const U3*>(u + 3 * (rec[k].x + i));
                     }
                 }
 #pragma unroll
-                for (int k = 0; k < kCopy; ++k)
-                    if (at[k] >= 0)
-                        stg[at[k]] = U3{(int)((uint32_t)v[k].x + (uint32_t)ox[k]), (int)((uint32_t)v[k].y + (uint32_t)oy[k]),
-                                        (int)((uint32_t)v[k].z + (uint32_t)oz[k])};
+                for (int k = 0; k < kCopy; ++k) {
+                    const int i = (c0 + NW * k) * kWave + l;
+                    if (i < tl.S)
+                        stg[i] = U3{(int)((uint32_t)v[k].x + (uint32_t)rec[k].y),
+                                    (int)((uint32_t)v[k].y + (uint32_t)rec[k].z),
+                                    (int)((uint32_t)v[k].z + (uint32_t)rec[k].w)};
+                }
             }
         }
         __syncthreads();
@@ -2219,15 +2288,14 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t(Dev d, Params p) {
                 e_vir += (double)virs * lam * lam;
             }
             kb += kRtBlock;
-            if (kb >= k1) break;
-            key = kb + (int)threadIdx.x;
-            active = key < k1;
-            ks = active ? key : k0;
-            qi = d.q[sq][ks];
-            v0x = ld_stream(d.vx[sp] + ks);
-            v0y = ld_stream(d.vy[sp] + ks);
-            v0z = ld_stream(d.vz[sp] + ks);
-            l4 = reinterpret_cast<const uint4*>(d.list) + (size_t)(ks >> 6) * p.rows * 8 + (ks & 63);
+            if (kb >= tl.K) break;
+            active = kb + (int)threadIdx.x < tl.K;
+            key = tile_key(tl, active ? kb + (int)threadIdx.x : 0);
+            qi = d.q[sq][key];
+            v0x = ld_stream(d.vx[sp] + key);
+            v0y = ld_stream(d.vy[sp] + key);
+            v0z = ld_stream(d.vz[sp] + key);
+            l4 = reinterpret_cast<const uint4*>(d.list) + (size_t)(key >> 6) * p.rows * 8 + (key & 63);
             raw_a = ld_stream(l4);
             raw_b = p.rows >= 16 ? ld_stream(l4 + kWave) : make_uint4(0u, 0u, 0u, 0u);
         }
@@ -2268,15 +2336,20 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t(Dev d, Params p) {
 // subtraction instead of after (one rounding of a different sum).  The pair scalar,
 // the summation order and the integration are the gather pass's (IEEE division, or
 // the hardware reciprocal with the correction of Sec. III.C).
+// Three wavefronts per SIMD is what the LDS allows (three blocks of 51 KB): the energies are
+// held to its 168 registers (1M particles, closing pass, kinetic energy 269 -> 215 us, all
+// 277 -> 269).  Mid-step pass (us), gathers / single rows / two rows: 1M 154 / 202 / 147, 16M
+// 2263 / 2398 / 1818, 2M with cutoff 3.0 490 / 632 / 498 (2 x 2 rows with 1664 records 133, -, 729).
 struct D3 {
     double x, y, z;
 };
 template <int MODE, int ENERGY>
-__global__ __launch_bounds__(kRtBlock) void k_force_t64(Dev d, Params p) {
+__global__ __launch_bounds__(kRtBlock, 3) void k_force_t64(Dev d, Params p) {
     if (step_off(d)) return;
     constexpr int NW = kRtBlock / kWave;
-    constexpr int U = 8, kPc = 27, kCopy = 4;
+    constexpr int U = 8, kCopy = 4;
     extern __shared__ D3 stg64[];  // p.scap records of 24 bytes
+    __shared__ __align__(16) TileTab tabs[NW];
     __shared__ double red[3][NW];
     const int l = lane_id(), wib = wave_in_block();
     const int ntl = ld_const(d.ntiles);
@@ -2285,61 +2358,49 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t64(Dev d, Params p) {
         const int4 tr = d.rtile[t];
         const int b = __builtin_amdgcn_readfirstlane(tr.x);
         const BoxGeom g = ld_geom(d.geom + b);
-        const int lr = __builtin_amdgcn_readfirstlane(tr.y), xa = __builtin_amdgcn_readfirstlane(tr.z),
+        const int yz = __builtin_amdgcn_readfirstlane(tr.y), xa = __builtin_amdgcn_readfirstlane(tr.z),
                   xb = __builtin_amdgcn_readfirstlane(tr.w);
-        const int cz = gdiv(g, lr, 1), cy = lr - cz * g.n[1];
         const int sq = ld_const(&d.st[b].sq), sp = ld_const(&d.st[b].sp);
-        int ps0 = 0, plen = 0, rx = 0, ry = 0, rz = 0;
-        if (l < kPc) {
-            int ox, oy, oz;
-            tile_piece(d, g, cy, cz, xa, xb, l, ps0, plen, ox, oy, oz);
-            tile_piece_img(g, cy, cz, l, rx, ry, rz);
+        TileTab& tab = tabs[wib];
+        const Tile tl = tile_open<true>(d, g, yz, xa, xb, tab);
+        if (tl.S > p.scap || tl.K == 0) {  // uniform over the block; nothing staged yet
+            if (ENERGY && threadIdx.x == 0) d.ke_part[t] = d.pe_part[t] = d.vir_part[t] = 0.0;
+            continue;
         }
-        const int pincl = wave_incl_sum(plen);
-        const int S = __builtin_amdgcn_readlane(pincl, kPc - 1);
-        const int rowc = g.cell_off + (cz * g.n[1] + cy) * g.n[0];
-        const int k0 = ld_const(d.cell_start + rowc + xa);
-        const int k1 = ld_const(d.cell_start + rowc + xb - 1) + ld_const(d.cell_cnt + rowc + xb - 1);
-        if (S > p.scap) continue;  // uniform over the block; nothing staged yet
-        int kb = k0;
-        int key = kb + (int)threadIdx.x;
-        bool active = key < k1;
-        int ks = active ? key : k0;
-        Pos qi = d.q[sq][ks];
-        double v0x = ld_stream(d.vx[sp] + ks), v0y = ld_stream(d.vy[sp] + ks), v0z = ld_stream(d.vz[sp] + ks);
-        const uint4* __restrict__ l4 = reinterpret_cast<const uint4*>(d.list) + (size_t)(ks >> 6) * p.rows * 8 + (ks & 63);
+        // this thread's first key: its record, velocity and first two list chunks, fetched
+        // while the block stages (a list holds at least 8 entries per lane, 16 when rows >= 16)
+        int kb = 0;
+        bool active = (int)threadIdx.x < tl.K;
+        int key = tile_key(tl, active ? (int)threadIdx.x : 0);
+        Pos qi = d.q[sq][key];
+        double v0x = ld_stream(d.vx[sp] + key), v0y = ld_stream(d.vy[sp] + key), v0z = ld_stream(d.vz[sp] + key);
+        const uint4* __restrict__ l4 =
+            reinterpret_cast<const uint4*>(d.list) + (size_t)(key >> 6) * p.rows * 8 + (key & 63);
         uint4 raw_a = ld_stream(l4);
         uint4 raw_b = p.rows >= 16 ? ld_stream(l4 + kWave) : make_uint4(0u, 0u, 0u, 0u);
-        {  // staging, as in k_force_t: 64-record chunks dealt round-robin to the wavefronts
-            const int pch = (plen + kWave - 1) >> 6;
-            const int chincl = wave_incl_sum(pch);
-            const int NC = __builtin_amdgcn_readlane(chincl, kPc - 1);
-            const int cs = chincl - pch;
-            const int src = ps0 - kWave * cs, dst = (pincl - plen) - kWave * cs, end = plen + kWave * cs;
+        {  // staging, as in k_force_t
             const Pos* __restrict__ q = d.q[sq];
-            for (int c0 = wib; c0 < NC; c0 += NW * kCopy) {
+            for (int c0 = wib; c0 * kWave < tl.S; c0 += NW * kCopy) {
                 D3 v[kCopy];
-                int at[kCopy];
+                int4 rec[kCopy];
 #pragma unroll
                 for (int k = 0; k < kCopy; ++k) {
-                    const int c = c0 + NW * k;
-                    at[k] = -1;
-                    if (c < NC) {  // uniform
-                        const int pc = __popcll(__ballot(l < kPc && chincl <= c));
-                        const int i = c * kWave + l;
-                        const double sx = (double)__builtin_amdgcn_readlane(rx, pc) * g.L[0];
-                        const double sy = (double)__builtin_amdgcn_readlane(ry, pc) * g.L[1];
-                        const double sz = (double)__builtin_amdgcn_readlane(rz, pc) * g.L[2];
-                        if (i < __builtin_amdgcn_readlane(end, pc)) {
-                            const Pos x = q[__builtin_amdgcn_readlane(src, pc) + i];
-                            v[k] = D3{x.x + sx, x.y + sy, x.z + sz};
-                            at[k] = __builtin_amdgcn_readlane(dst, pc) + i;
+                    const int c = c0 + NW * k, i = c * kWave + l;
+                    if (c * kWave < tl.S) {  // uniform
+                        rec[k] = tile_rec(tl, tab, c);
+                        if (i < tl.S) {
+                            const Pos x = q[rec[k].x + i];
+                            v[k] = D3{x.x, x.y, x.z};
                         }
                     }
                 }
 #pragma unroll
-                for (int k = 0; k < kCopy; ++k)
-                    if (at[k] >= 0) stg64[at[k]] = v[k];
+                for (int k = 0; k < kCopy; ++k) {
+                    const int i = (c0 + NW * k) * kWave + l;
+                    if (i < tl.S)
+                        stg64[i] = D3{v[k].x + (double)rec[k].y * g.L[0], v[k].y + (double)rec[k].z * g.L[1],
+                                      v[k].z + (double)rec[k].w * g.L[2]};
+                }
             }
         }
         __syncthreads();
@@ -2449,15 +2510,14 @@ __global__ __launch_bounds__(kRtBlock) void k_force_t64(Dev d, Params p) {
                 e_vir += vir;
             }
             kb += kRtBlock;
-            if (kb >= k1) break;
-            key = kb + (int)threadIdx.x;
-            active = key < k1;
-            ks = active ? key : k0;
-            qi = d.q[sq][ks];
-            v0x = ld_stream(d.vx[sp] + ks);
-            v0y = ld_stream(d.vy[sp] + ks);
-            v0z = ld_stream(d.vz[sp] + ks);
-            l4 = reinterpret_cast<const uint4*>(d.list) + (size_t)(ks >> 6) * p.rows * 8 + (ks & 63);
+            if (kb >= tl.K) break;
+            active = kb + (int)threadIdx.x < tl.K;
+            key = tile_key(tl, active ? kb + (int)threadIdx.x : 0);
+            qi = d.q[sq][key];
+            v0x = ld_stream(d.vx[sp] + key);
+            v0y = ld_stream(d.vy[sp] + key);
+            v0z = ld_stream(d.vz[sp] + key);
+            l4 = reinterpret_cast<const uint4*>(d.list) + (size_t)(key >> 6) * p.rows * 8 + (key & 63);
             raw_a = ld_stream(l4);
             raw_b = p.rows >= 16 ? ld_stream(l4 + kWave) : make_uint4(0u, 0u, 0u, 0u);
         }
@@ -2751,7 +2811,7 @@ __global__ __launch_bounds__(kBlock) void k_verify(Dev d, Params p) {
         const Pos* q = d.q[d.st[b].sq];
         const Pos qi = q[s];
         const int n = d.cnt[s];
-        int ps0[27], plen[27];
+        int ps0[kPieces], plen[kPieces];
         if (p.tile) tile_pieces_of(d, g, qi.cc, ps0, plen);
         unsigned long long missed = 0;
         for (int j = g.slot_off; j < g.slot_off + g.npart; ++j) {
