@@ -342,7 +342,7 @@ md_status alloc_cells(md_ctx* c) {
     dfree(c->D.row_t0);
     dfree(c->D.cell_rt);
     dfree(c->D.rt_tmp);
-    dfree(c->D.rt_delta);
+    dfree(c->D.rt_rec);
     dfree(c->D.ke_part);
     dfree(c->D.pe_part);
     dfree(c->D.vir_part);
@@ -357,7 +357,7 @@ md_status alloc_cells(md_ctx* c) {
     if ((s = dalloc(c, &c->D.row_t0, c->nrows)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.cell_rt, ncellpad)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.rt_tmp, ncellpad)) != MD_OK) return s;
-    if ((s = dalloc(c, &c->D.rt_delta, c->ntilemax * kPieces)) != MD_OK) return s;
+    if ((s = dalloc(c, &c->D.rt_rec, c->ntilemax * kTileRec)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.ke_part, nparts)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.pe_part, nparts)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.vir_part, nparts)) != MD_OK) return s;
@@ -459,7 +459,7 @@ void params_refresh(md_ctx* c) {
         int cus = 256;
         if (hipGetDeviceProperties(&prop, c->device) == hipSuccess && prop.multiProcessorCount > 0)
             cus = prop.multiProcessorCount;
-        P.tgrid = cus * rowtile_blocks_per_cu(P);
+        P.tgrid = std::max(8, cus * rowtile_blocks_per_cu(P));
     }
     P.fastrcp = (p.flags & MD_F_FAST_RCP) ? 1 : 0;
 }
@@ -503,7 +503,7 @@ void free_all(md_ctx* c) {
     dfree(D.box_t0);
     dfree(D.cell_rt);
     dfree(D.rt_tmp);
-    dfree(D.rt_delta);
+    dfree(D.rt_rec);
     dfree(D.vmax_s);
     dfree(D.disp_s);
     dfree(D.ke_part);

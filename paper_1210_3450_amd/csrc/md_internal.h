@@ -70,8 +70,11 @@ constexpr int kTileWMax = 64;            // cells per row tile at most
 constexpr int kScapMax = 5461;           // staged records per row tile at most (16-bit entries of 12 * index)
 constexpr int kBy = 2, kBz = 1;          // rows of cells per beam
 constexpr int kBeamRows = kBy * kBz;
+constexpr int kTileRun = 512;            // consecutive tiles per XCD and turn, at most
 constexpr int kPieces = (kBy + 2) * (kBz + 2) * 3;  // pieces of a staged region: one lane each
 static_assert(kPieces <= 64, "one lane per piece");
+static_assert(kPieces + 1 + kBeamRows <= 64, "one lane per word of a record");
+constexpr int kTileRec = kPieces + 1 + kBeamRows;   // words of a row tile's record
 constexpr int kRtBlock = 256;            // threads per block of the row-tile force kernel (keys per tile)
 constexpr int kStageCap = 2048;          // staged records per row tile (24 KB of LDS, FP64 48 KB)
 constexpr int kRedSeg = 2048;            // energy partials per first-level segment
@@ -201,7 +204,7 @@ struct Dev {
     int32_t* box_t0;     // [nbox + 1] first row tile of each box, then the total
     int32_t* cell_rt;    // row tile of each cell
     int32_t* rt_tmp;     // xa | xb << 16 of the beam's k-th tile at (first cell of its first row + k)
-    int32_t* rt_delta;   // [tile][kPieces]: staged index minus first slot of each piece of the tile
+    int2* rt_rec;        // [tile][kTileRec]: the tile's record (see k_row_rec)
     unsigned long long* vmax_s;  // [nbox][kStripes] striped max |v|^2 (bits), stride kStripeStride
     unsigned long long* disp_s;  // [nbox][kStripes] striped max |q - q_build|^2 (bits)
     double* ke_part;     // per list wave

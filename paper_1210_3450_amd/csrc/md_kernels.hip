@@ -1034,10 +1034,13 @@ __global__ __launch_bounds__(kBlock) void k_row_write(Dev d, Params p) {
     }
 }
 
-// Per row tile and piece p: staged index of the piece's first record minus its first
-// slot, so that the list build turns a stencil cell's first slot into its staged
-// index with one addition.  One wavefront per tile, lane p per piece.
-__global__ __launch_bounds__(kBlock) void k_row_delta(Dev d, Params p) {
+// The record of each row tile (kTileRec words of 8 bytes): per piece its first slot, and its first
+// staged index | its length << 16 (the list build turns a stencil cell's first slot into its staged
+// index with them); then the box and the first row, and the first slot and the count of the keys of each row.  One load gives a wavefront of the force pass all of it, one tile ahead:
+// working it out there was a chain of four dependent loads before the first copy (mid-step pass 32M
+// particles FP32-mixed 2173 -> 2107 us, FP64 3218 -> 3076; 1M FP64 120 -> 115).
+// One wavefront per tile, lane p per word.  (A region too large for 16 bits is far beyond scap.)
+__global__ __launch_bounds__(kBlock) void k_row_rec(Dev d, Params p) {
     if (!ld_const(d.any) || halted(d)) return;
     const int l = lane_id();
     const int ntl = ld_const(d.ntiles);
@@ -1046,10 +1049,23 @@ __global__ __launch_bounds__(kBlock) void k_row_delta(Dev d, Params p) {
         const int b = __builtin_amdgcn_readfirstlane(tr.x);
         const BoxGeom g = ld_geom(d.geom + b);
         const int yz = __builtin_amdgcn_readfirstlane(tr.y);
+        const int y0 = yz & 0xffff, z0 = yz >> 16;
         int ps0 = 0, plen = 0, ox, oy, oz;
-        if (l < kPieces) tile_piece(d, g, yz & 0xffff, yz >> 16, tr.z, tr.w, l, ps0, plen, ox, oy, oz);
+        if (l < kPieces) tile_piece(d, g, y0, z0, tr.z, tr.w, l, ps0, plen, ox, oy, oz);
+        plen = min(plen, 0x7fff);
         const int pbase = wave_incl_sum(plen) - plen;
-        if (l < kPieces) d.rt_delta[(size_t)t * kPieces + l] = pbase - ps0;
+        int2 r = make_int2(ps0, min(pbase, 0xffff) | plen << 16);
+        if (l == kPieces) r = make_int2(b, yz);
+        if (l > kPieces) {
+            const int k = l - (kPieces + 1), y = y0 + k % kBy, z = z0 + k / kBy;
+            r = make_int2(0, 0);
+            if (k < kBeamRows && y < g.n[1] && z < g.n[2]) {
+                const int rowc = g.cell_off + (z * g.n[1] + y) * g.n[0];
+                r.x = d.cell_start[rowc + tr.z];
+                r.y = d.cell_start[rowc + tr.w - 1] + d.cell_cnt[rowc + tr.w - 1] - r.x;
+            }
+        }
+        if (l < kTileRec) d.rt_rec[(size_t)t * kTileRec + l] = r;
     }
 }
 
@@ -1417,7 +1433,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6, 8))) 
             const int r = (cz % kBz + s_of_l / 9) * (kBy + 2) + cy % kBy + (s_of_l / 3) % 3;
             const int pc = r * 3 + (x < 0 ? 0 : (x >= g.n[0] ? 2 : 1));
             const int rt = ld_const(d.cell_rt + c);
-            ekey = (l < 27 ? start + d.rt_delta[(size_t)rt * kPieces + pc] : 0) - pre;
+            const int2 w = d.rt_rec[(size_t)rt * kTileRec + pc];
+            ekey = (l < 27 ? start + (w.y & 0xffff) - w.x : 0) - pre;
         }
         const int total = __builtin_amdgcn_readlane(incl, 26);
         const bool wrap = __ballot(img != 0) != 0ull;  // uniform: this cell touches the box boundary
@@ -2037,6 +2054,7 @@ struct TileTab {
     int st[kPieces];
 };
 struct Tile {
+    int b, yz;          // box, first row y0 | z0 << 16
     int S;              // staged records
     int np;             // pieces
     int cstart;         // lane o: first staged index of piece o
@@ -2044,17 +2062,35 @@ struct Tile {
     int ka[kBeamRows];  // per row: slot minus key index,
     int kf[kBeamRows];  // and the keys before the next row
 };
-// Every wavefront works the tile out itself (lane p holds piece p): no barrier.  FP64: the image
-// terms as box lengths, -1, 0 or 1, else in fixed-point units.
-template <bool FP64>
-__device__ __forceinline__ Tile tile_open(const Dev& d, const BoxGeom& g, int yz, int xa, int xb, TileTab& tab) {
-    const int l = lane_id();
-    const int y0 = yz & 0xffff, z0 = yz >> 16;
+__device__ __forceinline__ int2 tile_load(const Dev& d, int t) {
+    return d.rt_rec[(size_t)t * kTileRec + min(lane_id(), kTileRec - 1)];
+}
+// What the record r (lane l: word l) says; the image terms are the force pass's own.
+__device__ __forceinline__ Tile tile_head(const int2& r) {
     Tile t;
-    int ps0 = 0, plen = 0, ox = 0, oy = 0, oz = 0;
-    if (l < kPieces) {
-        tile_piece(d, g, y0, z0, xa, xb, l, ps0, plen, ox, oy, oz);
-        if (FP64) tile_piece_img(g, y0, z0, l, ox, oy, oz);
+    t.b = __builtin_amdgcn_readlane(r.x, kPieces);
+    t.yz = __builtin_amdgcn_readlane(r.y, kPieces);
+    t.K = 0;
+#pragma unroll
+    for (int k = 0; k < kBeamRows; ++k) {
+        t.ka[k] = __builtin_amdgcn_readlane(r.x, kPieces + 1 + k) - t.K;
+        t.K += __builtin_amdgcn_readlane(r.y, kPieces + 1 + k);
+        t.kf[k] = t.K;
+    }
+    return t;
+}
+// Every wavefront builds the table of pieces itself (lane p holds piece p): no barrier.  FP64: the
+// image terms as box lengths, -1, 0 or 1, else in fixed-point units.
+template <bool FP64>
+__device__ __forceinline__ void tile_open(Tile& t, const int2& r, const BoxGeom& g, TileTab& tab) {
+    const int l = lane_id();
+    const int plen = l < kPieces ? (int)((uint32_t)r.y >> 16) : 0;
+    int ox, oy, oz;
+    tile_piece_img(g, t.yz & 0xffff, t.yz >> 16, l, ox, oy, oz);
+    if (!FP64) {
+        ox *= g.nuoff[0];
+        oy *= g.nuoff[1];
+        oz *= g.nuoff[2];
     }
     const int incl = wave_incl_sum(plen);
     t.S = __builtin_amdgcn_readlane(incl, kWave - 1);
@@ -2062,26 +2098,11 @@ __device__ __forceinline__ Tile tile_open(const Dev& d, const BoxGeom& g, int yz
     t.np = __popcll(ne);
     const int o = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(ne >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)ne, 0u));
     if (plen > 0) {
-        tab.pc[o] = make_int4(ps0 - (incl - plen), ox, oy, oz);
+        tab.pc[o] = make_int4(r.x - (incl - plen), ox, oy, oz);
         tab.st[o] = incl - plen;
-    }
-    t.K = 0;
-#pragma unroll
-    for (int r = 0; r < kBeamRows; ++r) {
-        const int y = y0 + r % kBy, z = z0 + r / kBy;
-        int n = 0, a = 0;
-        if (y < g.n[1] && z < g.n[2]) {
-            const int rowc = g.cell_off + (z * g.n[1] + y) * g.n[0];
-            a = ld_const(d.cell_start + rowc + xa);
-            n = ld_const(d.cell_start + rowc + xb - 1) + ld_const(d.cell_cnt + rowc + xb - 1) - a;
-        }
-        t.ka[r] = a - t.K;
-        t.K += n;
-        t.kf[r] = t.K;
     }
     wave_lds_sync();
     t.cstart = tab.st[min(l, max(t.np, 1) - 1)];
-    return t;
 }
 // Slot of key k of the tile.
 __device__ __forceinline__ int tile_key(const Tile& t, int k) {
@@ -2103,6 +2124,35 @@ __device__ __forceinline__ int4 tile_rec(const Tile& t, const TileTab& tab, int 
     }
     return tab.pc[pp];
 }
+
+// Order in which the blocks of a row-tile pass take the tiles: each XCD (blocks b % 8) walks
+// runs of at most kTileRun consecutive tiles, so the rows that neighbouring tiles stage are still
+// in its L2, and the XCDs take turns at the runs, so that no XCD is left with the dense part
+// of a box.  Against block k taking tiles k, k + grid, ..., mid-step pass: 1M particles 79.7 -> 72.7
+// us (FP64 144 -> 130); at 16M and 32M, whose tiles in flight span a plane either way, no change.
+struct TileWalk {
+    int run, step, j, base, ntl;
+    __device__ __forceinline__ TileWalk(int ntl_) : ntl(ntl_) {
+        const int rounds = max((ntl + 8 * kTileRun - 1) / (8 * kTileRun), 1);
+        run = (ntl + 8 * rounds - 1) / (8 * rounds);
+        step = ((int)gridDim.x + 7 - ((int)blockIdx.x & 7)) >> 3;  // blocks on this XCD
+        j = (int)blockIdx.x >> 3;
+        base = ((int)blockIdx.x & 7) * run;
+        settle();
+    }
+    __device__ __forceinline__ void settle() {
+        while (j >= run && base < ntl) {
+            j -= run;
+            base += 8 * run;
+        }
+    }
+    __device__ __forceinline__ bool done() const { return base + j >= ntl; }
+    __device__ __forceinline__ int tile() const { return base + j; }
+    __device__ __forceinline__ void next() {
+        j += step;
+        settle();
+    }
+};
 
 // FP32-mixed pair forces from a row tile staged in LDS (row-tile list format, one lane per
 // key).  A block takes a row tile: its wavefronts work out the pieces of the staged region
@@ -2136,19 +2186,25 @@ __global__ __launch_bounds__(kRtBlock, 4) void k_force_t(Dev d, Params p) {
     __shared__ double red[3][NW];
     const int l = lane_id(), wib = wave_in_block();
     const int ntl = ld_const(d.ntiles);
-    for (int t = xcd_block(blockIdx.x, gridDim.x); t < ntl; t += gridDim.x) {
+    TileWalk tw(ntl);
+    if (tw.done()) return;
+    int2 rec_n = tile_load(d, tw.tile());
+    while (!tw.done()) {
+        const int t = tw.tile();
         // Staging runs at a raised wavefront priority, the pair loop at the normal one: a
         // block that starts a tile gets its loads issued ahead of the arithmetic of the
         // CU's other blocks, so their pair loops cover its memory latency.
         __builtin_amdgcn_s_setprio(2);
-        const int4 tr = d.rtile[t];
-        const int b = __builtin_amdgcn_readfirstlane(tr.x);
+        const int2 rec_t = rec_n;
+        Tile tl = tile_head(rec_t);
+        const int b = tl.b;
         const BoxGeom g = ld_geom(d.geom + b);
-        const int yz = __builtin_amdgcn_readfirstlane(tr.y), xa = __builtin_amdgcn_readfirstlane(tr.z),
-                  xb = __builtin_amdgcn_readfirstlane(tr.w);
         const int sq = ld_const(&d.st[b].sq), sp = ld_const(&d.st[b].sp);
         TileTab& tab = tabs[wib];
-        const Tile tl = tile_open<false>(d, g, yz, xa, xb, tab);
+        tile_open<false>(tl, rec_t, g, tab);
+        tw.next();
+        // the next tile's record, a pair loop ahead of its use
+        rec_n = tile_load(d, tw.done() ? t : tw.tile());
         if (tl.S > p.scap || tl.K == 0) {  // uniform over the block; nothing staged yet
             if (ENERGY && threadIdx.x == 0) d.ke_part[t] = d.pe_part[t] = d.vir_part[t] = 0.0;
             continue;
@@ -2365,16 +2421,22 @@ __global__ __launch_bounds__(kRtBlock, 3) void k_force_t64(Dev d, Params p) {
     __shared__ double red[3][NW];
     const int l = lane_id(), wib = wave_in_block();
     const int ntl = ld_const(d.ntiles);
-    for (int t = xcd_block(blockIdx.x, gridDim.x); t < ntl; t += gridDim.x) {
+    TileWalk tw(ntl);
+    if (tw.done()) return;
+    int2 rec_n = tile_load(d, tw.tile());
+    while (!tw.done()) {
+        const int t = tw.tile();
         __builtin_amdgcn_s_setprio(2);  // staging ahead of pair loops, as in k_force_t
-        const int4 tr = d.rtile[t];
-        const int b = __builtin_amdgcn_readfirstlane(tr.x);
+        const int2 rec_t = rec_n;
+        Tile tl = tile_head(rec_t);
+        const int b = tl.b;
         const BoxGeom g = ld_geom(d.geom + b);
-        const int yz = __builtin_amdgcn_readfirstlane(tr.y), xa = __builtin_amdgcn_readfirstlane(tr.z),
-                  xb = __builtin_amdgcn_readfirstlane(tr.w);
         const int sq = ld_const(&d.st[b].sq), sp = ld_const(&d.st[b].sp);
         TileTab& tab = tabs[wib];
-        const Tile tl = tile_open<true>(d, g, yz, xa, xb, tab);
+        tile_open<true>(tl, rec_t, g, tab);
+        tw.next();
+        // the next tile's record, a pair loop ahead of its use
+        rec_n = tile_load(d, tw.done() ? t : tw.tile());
         if (tl.S > p.scap || tl.K == 0) {  // uniform over the block; nothing staged yet
             if (ENERGY && threadIdx.x == 0) d.ke_part[t] = d.pe_part[t] = d.vir_part[t] = 0.0;
             continue;
@@ -2972,7 +3034,7 @@ void launch_row_tiles(const Dev& d, const Params& p, hipStream_t s) {
     k_row_tiles<<<gr, kBlock, 0, s>>>(d, p);
     k_row_scan<<<1, kBlock, 0, s>>>(d, p);
     k_row_write<<<gr, kBlock, 0, s>>>(d, p);
-    k_row_delta<<<4096, kBlock, 0, s>>>(d, p);
+    k_row_rec<<<4096, kBlock, 0, s>>>(d, p);
 }
 
 void launch_rebuild_chain(const Dev& d, const Params& p, bool with_list, hipStream_t s) {
