@@ -80,8 +80,8 @@ typedef enum {
                                       box with MD_REBUILD_EVERY_STEP; other one-box runs enqueue a list
                                       build only where a step needs one and gain nothing from graphs) */
 #define MD_F_TILE_ON 4u            /* row tiles (threads_per_key 0 or 1; the default for a largest box
-                                      of 3 * 2^18 particles or more, FP64 3 * 2^19, whose cells hold
-                                      4 to 36, FP64 30, on average): pairs of rows of
+                                      of 2^18 particles or more whose cells hold 4 to 36, FP64 30, on
+                                      average): pairs of rows of
                                       cells are cut into slices whose partners (the neighbouring
                                       rows, one cell wider each side) a block stages in LDS once
                                       (fixed-point records for FP32-mixed, FP64 positions for FP64);

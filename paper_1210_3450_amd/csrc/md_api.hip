@@ -25,8 +25,8 @@ using namespace mdg;
 namespace {
 
 constexpr int kChunk = 200;      // steps enqueued between status checks
-// Boxes that take row tiles by default (FP64, FP32-mixed): particles, and particles per cell.
-constexpr int64_t kTileMinN[2] = {3 << 19, 3 << 18};
+// Boxes that take row tiles by default: particles, and particles per cell (at most: FP64, FP32-mixed).
+constexpr int64_t kTileMinN = 1 << 18;
 constexpr double kTileMinCell = 4.0, kTileMaxCell[2] = {30.0, 36.0};
 constexpr int kGraphSteps = 8;   // continuing steps per captured graph
 
@@ -450,10 +450,8 @@ void params_refresh(md_ctx* c) {
         P.maxcell = std::max(P.maxcell, g.ncell);
     }
     P.redcap = (std::max(P.maxslot / kWave * 8, P.maxcell) + kRedSeg - 1) / kRedSeg;
-    // Row-tile force kernel: one resident round of blocks, each looping over the tiles
-    // (block k takes tiles k, k + grid, ...).  With the XCD-aware order each XCD then
-    // sweeps the same band of rows plane after plane, so the rows it stages stay in its
-    // L2; a grid of one block per tile measured 16% slower at 32M particles.
+    // Row-tile force kernel: one resident round of blocks, each looping over the tiles (TileWalk);
+    // a grid of one block per tile measured 16% slower at 32M particles.
     if (P.tgrid <= 0) {
         hipDeviceProp_t prop;
         int cus = 256;
@@ -965,22 +963,21 @@ md_status create_impl(const md_params* boxes, int32_t nbox, void* stream, md_ctx
         tpk = c->ntotal < 98304 ? 4 : (c->ntotal < 262144 || fp64 ? 2 : 1);
     }
     // Row tiles: their force pass is faster from about 100,000 particles on, but cutting the tiles
-    // costs four launches and a table per rebuild.  Whole steps, gathers / tiles (us): FP32-mixed 442,000
-    // particles 79.6 / 83.5, 1,049,000 143 / 131, 2,126,000 at density 0.7 with cutoff 3.0 461 / 407,
-    // 6,912,000 804 / 711; FP64 1,049,000 190 / 190, 2,126,000 645 / 626, 4,000,000 592 / 558, 6,912,000
-    // 1130 / 986.  So they are the default for a largest box of kTileMinN particles or more
-    // (md_autotune measures instead), where its cells hold kTileMinCell to kTileMaxCell on
-    // average: with fewer the copies of a slice outweigh its pairs (2M particles, one lane per key /
-    // tiles: 2.2 to a cell FP64 250 / 277, FP32-mixed 231 / 241; 4.5 to a cell 267 / 253, 230 / 205), with
-    // more its region is mostly margin, and many are near the staging capacity (two lanes / tiles:
-    // 31 to a cell FP64 734 / 735, FP32-mixed 493 / 465; 37 to a cell 897 / 1025, 632 / 626; 48 1175 / 1520,
-    // 832 / 861).
+    // costs four launches and a table per rebuild, and a single evaluation some 20 us more.  Whole
+    // steps, gathers / tiles (us): FP64 187,000 particles 48.1 / 48.5, 256,000 59.0 / 55.3, 442,000 98.3 /
+    // 92.0, 1,049,000 187 / 161; FP32-mixed 39.3 / 39.7, 49.0 / 45.4, 79.7 / 74.1, 144 / 130.  So they are the
+    // default for a largest box of kTileMinN particles or more (md_autotune measures instead), where
+    // its cells hold kTileMinCell to kTileMaxCell on average: with fewer the copies of a slice
+    // outweigh its pairs in the first builds of a run (2M particles at 2.2 to a cell, lists, forces and
+    // energies of new positions FP64 1467 / 1788, FP32-mixed 1273 / 1430, steps 262 / 243, 220 / 215), with
+    // more its region is mostly margin, and many are near the staging capacity (steps, 37 to a cell
+    // 895 / 931, 687 / 615; 48 1120 / 1320, 852 / 810).
     int big = 0;
     for (int b = 1; b < c->nbox; ++b)
         if (c->boxes[b].n > c->boxes[big].n) big = b;
     const double percell = (double)c->boxes[big].n / c->geom[big].ncell;
     const bool may = !(c->prm.flags & (MD_F_TILE_OFF | MD_F_HALF_LIST)) && c->prm.threads_per_key <= 1;
-    const bool pays = c->boxes[big].n >= kTileMinN[c->prm.precision] && percell >= kTileMinCell &&
+    const bool pays = c->boxes[big].n >= kTileMinN && percell >= kTileMinCell &&
                       percell <= kTileMaxCell[c->prm.precision];
     const bool tiles = may && ((c->prm.flags & MD_F_TILE_ON) || pays);
     if (tiles) tpk = 1;

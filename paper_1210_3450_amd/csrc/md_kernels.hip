@@ -1036,9 +1036,10 @@ __global__ __launch_bounds__(kBlock) void k_row_write(Dev d, Params p) {
 
 // The record of each row tile (kTileRec words of 8 bytes): per piece its first slot, and its first
 // staged index | its length << 16 (the list build turns a stencil cell's first slot into its staged
-// index with them); then the box and the first row, and the first slot and the count of the keys of each row.  One load gives a wavefront of the force pass all of it, one tile ahead:
-// working it out there was a chain of four dependent loads before the first copy (mid-step pass 32M
-// particles FP32-mixed 2173 -> 2107 us, FP64 3218 -> 3076; 1M FP64 120 -> 115).
+// index with them); then the box and the first row, and the first slot and the count of the keys
+// of each row.  One load gives a wavefront of the force pass all of it, one tile ahead: working it
+// out there was a chain of four dependent loads before the first copy (mid-step pass 32M particles
+// FP32-mixed 2173 -> 2107 us, FP64 3218 -> 3076; 1M FP64 120 -> 115).
 // One wavefront per tile, lane p per word.  (A region too large for 16 bits is far beyond scap.)
 __global__ __launch_bounds__(kBlock) void k_row_rec(Dev d, Params p) {
     if (!ld_const(d.any) || halted(d)) return;
@@ -2404,10 +2405,12 @@ __global__ __launch_bounds__(kRtBlock, 4) void k_force_t(Dev d, Params p) {
 // subtraction instead of after (one rounding of a different sum).  The pair scalar,
 // the summation order and the integration are the gather pass's (IEEE division, or
 // the hardware reciprocal with the correction of Sec. III.C).
-// Three wavefronts per SIMD is what the LDS allows (three blocks of 51 KB): the energies are
-// held to its 168 registers (1M particles, closing pass, kinetic energy 269 -> 215 us, all
-// 277 -> 269).  Mid-step pass (us), gathers / single rows / two rows: 1M 154 / 202 / 147, 16M
-// 2263 / 2398 / 1818, 2M with cutoff 3.0 490 / 632 / 498 (2 x 2 rows with 1664 records 133, -, 729).
+// Three wavefronts per SIMD is what the LDS allows (three blocks of 51 KB), so the energies are
+// held to 168 registers.  Bound by FP64 arithmetic, some 30 instructions an entry at a quarter of
+// the FP32 rate (55% of the pass) and the staging that three blocks do not hide.  Mid-step pass
+// (us), gathers / single rows / two rows / with the reciprocal, the records read ahead and the tile
+// order of TileWalk: 1M particles 154 / 202 / 147 / 115, 16M 2263 / 2398 / 1818 / 1611, 2M with cutoff 3.0
+// 490 / 632 / 498 / 410 (2 x 2 rows with 1664 records, before those: 1M 133, 2M with 3.0 729).
 struct D3 {
     double x, y, z;
 };
@@ -2415,7 +2418,10 @@ template <int MODE, int ENERGY>
 __global__ __launch_bounds__(kRtBlock, 3) void k_force_t64(Dev d, Params p) {
     if (step_off(d)) return;
     constexpr int NW = kRtBlock / kWave;
-    constexpr int U = 8, kCopy = 4;
+    constexpr int U = 8;
+    // copy chunks in flight: with the energies two, or the registers spill (closing pass of 1M
+    // particles, kinetic energy 134 -> 114 us, all 187 -> 153)
+    constexpr int kCopy = ENERGY ? 2 : 4;
     extern __shared__ D3 stg64[];  // p.scap records of 24 bytes
     __shared__ __align__(16) TileTab tabs[NW];
     __shared__ double red[3][NW];
