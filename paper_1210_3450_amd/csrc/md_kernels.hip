@@ -1638,9 +1638,13 @@ __device__ __forceinline__ void force_finish(const Dev& d, const Params& p, cons
         }
     } else {  // kForceMid
         if (owner) {
-            double vx = kick(kick(ld_stream(d.vx[sp] + key), p.h, Fx), p.h, Fx);
-            double vy = kick(kick(ld_stream(d.vy[sp] + key), p.h, Fy), p.h, Fy);
-            double vz = kick(kick(ld_stream(d.vz[sp] + key), p.h, Fz), p.h, Fz);
+            double vx = kick(ld_stream(d.vx[sp] + key), p.h, Fx);
+            double vy = kick(ld_stream(d.vy[sp] + key), p.h, Fy);
+            double vz = kick(ld_stream(d.vz[sp] + key), p.h, Fz);
+            if (ENERGY) ke = 0.5 * p.mass * norm2(vx, vy, vz);
+            vx = kick(vx, p.h, Fx);
+            vy = kick(vy, p.h, Fy);
+            vz = kick(vz, p.h, Fz);
             st_stream(d.vx[sp] + key, vx);
             st_stream(d.vy[sp] + key, vy);
             st_stream(d.vz[sp] + key, vz);
@@ -2326,9 +2330,11 @@ __global__ __launch_bounds__(kRtBlock, 4) void k_force_t(Dev d, Params p) {
                     d.fz[key] = Fz;
                     if (ENERGY) ke = 0.5 * p.mass * norm2(vx, vy, vz);
                 } else {  // kForceMid: close step n, open step n+1, drift, re-encode
-                    const double vx = kick(kick(v0x, p.h, Fx), p.h, Fx);
-                    const double vy = kick(kick(v0y, p.h, Fy), p.h, Fy);
-                    const double vz = kick(kick(v0z, p.h, Fz), p.h, Fz);
+                    double vx = kick(v0x, p.h, Fx), vy = kick(v0y, p.h, Fy), vz = kick(v0z, p.h, Fz);
+                    if (ENERGY) ke = 0.5 * p.mass * norm2(vx, vy, vz);
+                    vx = kick(vx, p.h, Fx);
+                    vy = kick(vy, p.h, Fy);
+                    vz = kick(vz, p.h, Fz);
                     st_stream(d.vx[sp] + key, vx);
                     st_stream(d.vy[sp] + key, vy);
                     st_stream(d.vz[sp] + key, vz);
@@ -2560,9 +2566,11 @@ __global__ __launch_bounds__(kRtBlock, 3) void k_force_t64(Dev d, Params p) {
                     d.fz[key] = Fz;
                     if (ENERGY) ke = 0.5 * p.mass * norm2(vx, vy, vz);
                 } else {  // kForceMid: close step n, open step n+1, drift
-                    const double vx = kick(kick(v0x, p.h, Fx), p.h, Fx);
-                    const double vy = kick(kick(v0y, p.h, Fy), p.h, Fy);
-                    const double vz = kick(kick(v0z, p.h, Fz), p.h, Fz);
+                    double vx = kick(v0x, p.h, Fx), vy = kick(v0y, p.h, Fy), vz = kick(v0z, p.h, Fz);
+                    if (ENERGY) ke = 0.5 * p.mass * norm2(vx, vy, vz);
+                    vx = kick(vx, p.h, Fx);
+                    vy = kick(vy, p.h, Fy);
+                    vz = kick(vz, p.h, Fz);
                     st_stream(d.vx[sp] + key, vx);
                     st_stream(d.vy[sp] + key, vy);
                     st_stream(d.vz[sp] + key, vz);
@@ -3078,6 +3086,8 @@ static void launch_force_pt(const Dev& d, const Params& p, int mode, int energy,
             k_force<PREC, kForceEnd, TPK, kEnKe><<<nb, kBlock, 0, s>>>(d, p);
         else
             k_force<PREC, kForceEnd, TPK, kEnNone><<<nb, kBlock, 0, s>>>(d, p);
+    } else if (energy == kEnFull) {
+        k_force<PREC, kForceMid, TPK, kEnFull><<<nb, kBlock, 0, s>>>(d, p);
     } else {
         k_force<PREC, kForceMid, TPK, kEnNone><<<nb, kBlock, 0, s>>>(d, p);
     }
@@ -3127,6 +3137,8 @@ static void launch_force_rowtile_c(const Dev& d, const Params& p, int mode, int 
             k_force_t<kForceEnd, kEnKe, CLAMP><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
         else
             k_force_t<kForceEnd, kEnNone, CLAMP><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
+    } else if (energy == kEnFull) {
+        k_force_t<kForceMid, kEnFull, CLAMP><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
     } else {
         k_force_t<kForceMid, kEnNone, CLAMP><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
     }
@@ -3161,6 +3173,8 @@ static void launch_force_rowtile64(const Dev& d, const Params& p, int mode, int 
             k_force_t64<kForceEnd, kEnKe><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
         else
             k_force_t64<kForceEnd, kEnNone><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
+    } else if (energy == kEnFull) {
+        k_force_t64<kForceMid, kEnFull><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
     } else {
         k_force_t64<kForceMid, kEnNone><<<p.tgrid, kRtBlock, lds, s>>>(d, p);
     }
