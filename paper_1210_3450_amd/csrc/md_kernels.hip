@@ -2412,9 +2412,8 @@ __global__ __launch_bounds__(kRtBlock, 4) void k_force_t(Dev d, Params p) {
 // the summation order and the integration are the gather pass's (IEEE division, or
 // the hardware reciprocal with the correction of Sec. III.C).
 // Three wavefronts per SIMD is what the LDS allows (three blocks of 51 KB), so the energies are
-// held to 168 registers.  Bound by FP64 arithmetic, some 30 instructions an entry at a quarter of
-// the FP32 rate (55% of the pass) and the staging that three blocks do not hide.  Mid-step pass
-// (us), gathers / single rows / two rows / with the reciprocal, the records read ahead and the tile
+// held to 168 registers.  Bound by vector issue (some 30 instructions an entry, 59% of the SIMD
+// cycles) and the staging that three blocks do not hide.  Mid-step pass (us), gathers / single rows / two rows / with the reciprocal, the records read ahead and the tile
 // order of TileWalk: 1M particles 154 / 202 / 147 / 115, 16M 2263 / 2398 / 1818 / 1611, 2M with cutoff 3.0
 // 490 / 632 / 498 / 410 (2 x 2 rows with 1664 records, before those: 1M 133, 2M with 3.0 729).
 struct D3 {
