@@ -243,7 +243,7 @@ enum ForceMode : int {
 // Energy partials a force pass leaves.  A thermostat step that records no sample needs the
 // kinetic energy alone: the pair energy and the virial are some 10 of the 40 instructions of
 // an entry (closing pass of 2M particles at density 0.84, FP32-mixed, all / kinetic: gathers
-// 255 / 226 us, row tiles 262 / 204 us; FP64 1M 240 / 207 and 269 / 215 us).
+// 255 / 226 us, row tiles 262 / 204 us; FP64 1M at 0.5, row tiles 153 / 114 us).
 enum ForceEnergy : int { kEnNone = 0, kEnKe = 1, kEnFull = 2 };
 
 // Subcell grid of the bubble analysis (md_bubbles.hip): n = floor(L / side)
