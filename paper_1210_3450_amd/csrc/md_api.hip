@@ -445,7 +445,9 @@ void params_refresh(md_ctx* c) {
     P.nrows = c->nrows;
     P.maxslot = 0;
     P.maxcell = 0;
+    P.ncell = 0;
     for (const BoxGeom& g : c->geom) {
+        P.ncell += g.ncell;
         P.maxslot = std::max(P.maxslot, g.nslot);
         P.maxcell = std::max(P.maxcell, g.ncell);
     }

@@ -162,6 +162,7 @@ struct Params {
     int32_t half;       // half list (each pair once, forward stencil cells), partner forces by atomics
     int32_t maxslot;    // slots of the largest box
     int32_t maxcell;    // cells of the largest box
+    int32_t ncell;      // cells over all boxes
     int32_t redcap;     // first-level energy sums per box (enough for 8 lanes per key)
 };
 

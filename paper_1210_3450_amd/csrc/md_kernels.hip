@@ -1109,10 +1109,11 @@ __device__ __forceinline__ int nb_axis(int c, int o, int n, int& r) {
 // done again by slow_key with the plain FP64 minimum-image definition, so every set is the
 // one that definition gives, bit for bit.
 constexpr int kListG = 6;     // candidate chunks per pass
-constexpr int kMarkBytes = kListG * kWave;  // candidate window of a pass
 constexpr int kStage = 2560;  // staged list entries per wavefront.  With the room behind it, marks and cell
                               // table 26 KB per block: 6 blocks per CU, as many as the registers allow
-constexpr int kStageAll = kStage + kListG * kWave;
+// Boxes of nearly empty cells (launch_list): the candidates of a cell fit one or two chunks.
+constexpr int kThinG = 2;
+constexpr int kThinStage = 1024;
 
 // Centre of cell c along an axis of cells of side cs.
 __device__ __forceinline__ double cell_mid(int c, double cs) { return ((double)c + 0.5) * cs; }
@@ -1177,20 +1178,17 @@ __device__ __forceinline__ const ListArgs& list_args() {
 // entries leave in whole 16-byte chunks afterwards.  A key with more than cap partners
 // runs on into the places of the keys after it, and the last one into the room behind
 // kStage (a pass starts at most cap entries in and adds at most G * 64): its build is
-// thrown away (k_list sets halt), so nothing needs to be checked per chunk.  Otherwise
-// (a capacity beyond the buffer) every key takes the slow way and stores its entries to the
-// list directly, up to cap.
+// thrown away (k_list sets halt), so nothing needs to be checked per chunk.  Otherwise every
+// entry goes to its place in the list at once, up to cap.
 // A candidate's stencil cell: `tab` holds the non-empty stencil cells in candidate order
 // (slot of candidate ci: x + ci; its entry: y + ci; image code z).  Lane o < ncell knows the
 // first candidate `pre` of the o-th of them; all but the first mark the candidate before it in
 // a byte window of the pass (`mark`, G * 64 bytes), so that the marks before a candidate
 // (a ballot and mbcnt per chunk, on the count of the chunks before) number its cell.
-template <bool HALF, bool TL>
+template <bool HALF, bool TL, int G, bool STAGED>
 __device__ __forceinline__ int list_group(const Dev& d, const Params& p, const Pos* __restrict__ q, int cs0, int kb,
                                           int mb, int total, int pre, int ncell, bool wrap, const BoxGeom& g, int hx,
-                                          int hy, int hz, bool staged, uint16_t* stage, uint8_t* mark,
-                                          const int4* tab) {
-    constexpr int G = kListG;
+                                          int hy, int hz, uint16_t* stage, uint8_t* mark, const int4* tab) {
     const int l = lane_id();
     const int cap = p.cap;
     const float inf = __int_as_float(0x7f800000);
@@ -1220,7 +1218,7 @@ __device__ __forceinline__ int list_group(const Dev& d, const Params& p, const P
         const int open0 = open, n_prev = n_own;
         // the window's marks: cleared as words, then a byte each
         uint32_t* mw = reinterpret_cast<uint32_t*>(mark);
-        mw[l] = 0u;
+        if (G * kWave / 4 >= kWave || l < G * kWave / 4) mw[l] = 0u;
         if (l < G * kWave / 4 - kWave) mw[kWave + l] = 0u;
         wave_lds_sync();
         if (l > 0 && l < ncell && pre > c0 && pre <= c0 + G * kWave) mark[pre - 1 - c0] = 1;
@@ -1251,20 +1249,19 @@ __device__ __forceinline__ int list_group(const Dev& d, const Params& p, const P
                 const int pos = (int)__builtin_amdgcn_mbcnt_hi(
                     (unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, (uint32_t)cnt));
                 const uint16_t e = (uint16_t)entry(t.y, ci);
-                if (in && staged) stage[at0 + pos] = e;
-                if (in && !staged && pos < cap) d.list[list_addr(cs0 + kb + a, pos, p.tpk, p.rows)] = e;
+                if (STAGED) {
+                    if (in) stage[at0 + pos] = e;
+                } else if (in && pos < cap) {
+                    d.list[list_addr(cs0 + kb + a, pos, p.tpk, p.rows)] = e;
+                }
                 cnt += __popcll(mask);
             }
             if (l == a) n_own = cnt;
         };
-        if (!staged) {  // uniform
-            for (int a = 0; a < mb; ++a) slow_key(a);
-            continue;
-        }
         // every chunk's loads first, then the conversions: one memory latency per pass
         double qx[G], qy[G], qz[G];
         float cx[G], cy[G], cz[G], cn[G];
-        uint32_t ent[G / 2];  // two 16-bit entries each
+        uint32_t ent[(G + 1) / 2];  // two 16-bit entries each
         int m[G];
 #pragma unroll
         for (int k = 0; k < G; ++k) m[k] = mark[k * kWave + l];
@@ -1309,7 +1306,8 @@ __device__ __forceinline__ int list_group(const Dev& d, const Params& p, const P
         auto key_loop = [&](auto n_c, auto self0_c) {
             constexpr int N = decltype(n_c)::value;
             constexpr bool SELF0 = decltype(self0_c)::value;
-            const int st0 = (int)(lds_addr(stage) >> 1);
+            const int st0 = STAGED ? (int)(lds_addr(stage) >> 1) : 0;
+            const int tsh = STAGED ? 0 : __builtin_ctz((unsigned)p.tpk);
             for (int a = 0; a < mb; ++a) {
                 const float Kx = readlane_f(kx, a), Ky = readlane_f(ky, a), Kz = readlane_f(kz, a);
                 const float lo = readlane_f(tlo, a), hi = readlane_f(thi, a);
@@ -1319,8 +1317,10 @@ __device__ __forceinline__ int list_group(const Dev& d, const Params& p, const P
 #pragma unroll
                 for (int k = 0; k < N; ++k)
                     s[k] = __builtin_fmaf(Kx, cx[k], __builtin_fmaf(Ky, cy[k], __builtin_fmaf(Kz, cz[k], cn[k])));
-                const int at0 = keep_scalar(st0 + a * cap + min(done, cap));
-                int at = at0;  // the next staged entry (LDS address in entries)
+                // the next entry: STAGED its place in LDS (address in entries), else its number
+                const int at0 = STAGED ? keep_scalar(st0 + a * cap + min(done, cap)) : done;
+                int at = at0;
+                uint16_t* __restrict__ kp = STAGED ? nullptr : d.list + list_addr(cs0 + kb + a, 0, p.tpk, p.rows);
                 unsigned long long bord = 0ull;
 #pragma unroll
                 for (int k = 0; k < N; ++k) {
@@ -1332,10 +1332,18 @@ __device__ __forceinline__ int list_group(const Dev& d, const Params& p, const P
                         HALF ? low & __builtin_amdgcn_ballot_w64(k * kWave + l > own + a)
                              : low & ~((SELF0 ? k == 0 : k == sk) ? sb : 0ull);
                     bord |= __builtin_amdgcn_ballot_w64(s[k] < hi) & ~low;
-                    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
-                                                                   __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
-                    if (__builtin_amdgcn_inverse_ballot_w64(mask))
-                        *(lds_u16*)(size_t)((pos + (uint32_t)at) << 1) = (uint16_t)(k & 1 ? ent[k / 2] >> 16 : ent[k / 2]);
+                    const uint16_t e = (uint16_t)(k & 1 ? ent[k / 2] >> 16 : ent[k / 2]);
+                    if (STAGED) {
+                        const uint32_t pos = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
+                                                                       __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+                        if (__builtin_amdgcn_inverse_ballot_w64(mask)) *(lds_u16*)(size_t)((pos + (uint32_t)at) << 1) = e;
+                    } else {
+                        const uint32_t pos = __builtin_amdgcn_mbcnt_hi(
+                            (unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, (uint32_t)at));
+                        const uint32_t mm = pos >> tsh;  // list_addr's offset of entry pos
+                        if (__builtin_amdgcn_inverse_ballot_w64(mask) && (int)pos < cap)
+                            kp[((mm & ~7u) << 6) + ((pos & (uint32_t)(p.tpk - 1)) << 3) + (mm & 7u)] = e;
+                    }
                     at = keep_scalar(at + __popcll(mask));
                 }
                 if (bord) again |= 1ull << a;
@@ -1344,7 +1352,13 @@ __device__ __forceinline__ int list_group(const Dev& d, const Params& p, const P
         };
         if (!HALF && own0 && sk > 0) {
             key_loop(std::integral_constant<int, G>{}, std::false_type{});
+        } else if constexpr (G == 2) {
+            if (nch == 1)
+                key_loop(std::integral_constant<int, 1>{}, std::true_type{});
+            else
+                key_loop(std::integral_constant<int, 2>{}, std::true_type{});
         } else {
+            static_assert(G == 6, "chunk counts below");
             switch (nch) {
                 case 1: key_loop(std::integral_constant<int, 1>{}, std::true_type{}); break;
                 case 2: key_loop(std::integral_constant<int, 2>{}, std::true_type{}); break;
@@ -1354,27 +1368,33 @@ __device__ __forceinline__ int list_group(const Dev& d, const Params& p, const P
                 default: key_loop(std::integral_constant<int, 6>{}, std::true_type{}); break;
             }
         }
+        // entries stored to the list land before the lanes that store them anew
+        if (!STAGED && again) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
         for (; again; again &= again - 1ull) slow_key(__ffsll((long long)again) - 1);
     }
     return n_own;
 }
 
-// Six wavefronts per SIMD: no vector register is spilled.  Seven (72 VGPRs, 18 spilled) take
-// 9-10% longer from 2M particles on.  What bounds it is vector issue: measured on jittered
+// Six wavefronts per SIMD, eight with two chunks: no vector register is spilled.  Seven (72 VGPRs, 18
+// spilled) take 9-10% longer from 2M particles on.  What bounds it is vector issue: measured on jittered
 // FCC boxes, list build before (seven FP64 instructions per test, one address for the longest
 // list of a tile) and now: 100k particles at density 0.6 101 -> 43 us, 1M at 0.5 415 -> 220 us,
 // 2M at 0.7 with cutoff 3.0 1150 -> 980 us, 16M 3000 -> 2800 us.
 // TL: the row-tile entry format (one lane per key, full list); otherwise the gather format.
+// G: candidate chunks per pass; STAGE: list entries the staging buffer holds, 0: entries are stored
+// directly (launch_list chooses).
 //
 // A cell's keys are taken in groups of gk (what the staging buffer holds at the list's
-// capacity); in a cell of more than 64 members a group holds gk64, a power of two, so that
+// capacity, or a chunk); in a cell of more than 64 members a group holds gk64, a power of two, so that
 // its keys lie in one 64-candidate chunk.  With `parts` > 1 that many wavefronts share a cell,
 // part i taking groups i, i + parts, ... (launch_list).
-template <bool HALF, bool TL>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_list(ListArgs args) {
+template <bool HALF, bool TL, int G, int STAGE>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(G == kThinG ? 8 : 6, 8))) void k_list(
+    ListArgs args) {
     if (!ld_const(args.d.any) || halted(args.d)) return;  // no box rebuilds this step, or a build overflowed
-    __shared__ __align__(16) uint16_t stage_all[kBlock / kWave][kStageAll];
-    __shared__ __align__(16) uint8_t mark_all[kBlock / kWave][kMarkBytes];
+    constexpr bool STAGED = STAGE > 0;
+    __shared__ __align__(16) uint16_t stage_all[kBlock / kWave][STAGED ? STAGE + G * kWave : 1];
+    __shared__ __align__(16) uint8_t mark_all[kBlock / kWave][G * kWave];
     __shared__ __align__(16) int4 tab_all[kBlock / kWave][27];
     const int l = lane_id();
     // the wavefront's index in the block, as a scalar: the cell loop and every per-cell
@@ -1450,11 +1470,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6, 8))) 
         int need = 0;
         for (int kb = part * gk; kb < m; kb += A.parts * gk) {
             const int mb = min(gk, m - kb);
-            const bool staged = mb * cap <= kStage;  // uniform; false only if one key's list outgrows the buffer
-            const int n_own = list_group<HALF, TL>(d, p, q, cs0, kb, mb, total, pre, ncell, wrap, g, cx, cy, cz, staged,
-                                                   stage, mark, tab);
+            const int n_own = list_group<HALF, TL, G, STAGED>(d, p, q, cs0, kb, mb, total, pre, ncell, wrap, g, cx, cy,
+                                                              cz, stage, mark, tab);
             wave_lds_sync();
-            if (staged) {
+            if (STAGED) {
                 // write-out: row r = lane t of key a, chunk c of its entries, 16 bytes; the
                 // lanes of a pass hold 2^rsh rows side by side (consecutive keys write consecutive
                 // chunks of the list), 64 >> rsh chunks of each: 8 x 8 where a key has one lane and
@@ -3017,30 +3036,54 @@ static inline int list_grid(const Params& p) {
     const int g = p.ntile * kTile / 32;
     return g < 8192 ? grid_for_waves(p.ntile * kTile, 8192) : (g > 65536 ? 65536 : g);
 }
+template <int G, int STAGE>
+static void launch_list_gs(const Dev& d, const Params& p, int grid, int gk, int gk64, int parts, hipStream_t s) {
+    if (p.half)
+        k_list<true, false, G, STAGE><<<grid, kBlock, 0, s>>>(ListArgs{d, p, gk, gk64, parts});
+    else if (p.tile)
+        k_list<false, true, G, STAGE><<<grid, kBlock, 0, s>>>(ListArgs{d, p, gk, gk64, parts});
+    else
+        k_list<false, false, G, STAGE><<<grid, kBlock, 0, s>>>(ListArgs{d, p, gk, gk64, parts});
+}
+
 static void launch_list(const Dev& d, const Params& p, hipStream_t s) {
-    // keys per group: what the staging buffer holds (one when even that does not fit)
-    int gk = kStage / p.cap;
-    gk = gk < 1 ? 1 : (gk > kWave ? kWave : gk);
+    const int cells = p.nbox == 1 ? p.maxcell : p.ntile * kTile;
+    const int slots = p.nwave * kWave;
     // A small box has too few cells to fill the chip (343 cells at 4000 particles against 6144
     // resident wavefronts), and the time of one cell, not the sum of all, is what its build
     // takes: up to 8 wavefronts share a cell while that leaves no more than 3072 of them
     // (4000 particles 13.3 -> 10, 10,000 at density 0.7 28 -> 20 us; at 100,000 particles
     // two wavefronts per cell were slower, 40 -> 49 us: each repeats the cell's set-up).
-    const int cells = p.nbox == 1 ? p.maxcell : p.ntile * kTile;
     int parts = 3072 / cells;
     parts = parts < 1 ? 1 : (parts > 8 ? 8 : parts);
+    // Every group loads and converts all candidates of its cell again, so long lists, of which the
+    // buffer holds few, are stored directly by groups of a whole chunk instead: from fewer than 7 keys
+    // (4 where wavefronts share a cell) on.  Rebuild chain, 8.6M particles at density 0.84, staged /
+    // direct (us): 36 to a cell (cutoff 3.2, 10 keys fit) 5.1 / 5.9 ms, 58 (6) 8.8 / 8.7, 69 (5) 12.3 /
+    // 10.5, 134 (3) 50.1 / 17.7; 500,000 at 228 to a cell (1) 12.6 / 3.5 ms; 32,000 at 93 (5) 160 / 169 us,
+    // at 148 (3) 376 / 303.
+    const bool direct = kStage / p.cap < (parts > 1 ? 4 : 7);
+    // With fewer than 5 particles to a cell one or two chunks hold all candidates and the registers
+    // of four more cost two wavefronts of each SIMD's eight: 8.6M particles, six chunks / two
+    // (us), 0.4 to a cell 6640 / 5480, 2.2 3140 / 2630, 4.4 2196 / 2102, 5.5 2044 / 2118, 6.6 1952 / 2081.
+    // (Short lists on average do not keep a clump out of the box: then the capacity has grown.)
+    const bool thin = !direct && slots / 5 < p.ncell && p.cap <= 64;
+    // keys per group: what the staging buffer holds
+    int gk = direct ? kWave : (thin ? kThinStage : kStage) / p.cap;
+    gk = gk > kWave ? kWave : gk;
     if (parts > 1) {
-        const int mean = p.nwave * kWave / cells + 1, share = (mean + parts - 1) / parts;
+        const int share = (slots / cells + parts) / parts;
         gk = gk < share ? gk : share;
     }
-    const int gk64 = gk >= 8 ? 8 : (gk >= 4 ? 4 : (gk >= 2 ? 2 : 1));
+    int gk64 = 1;
+    while (2 * gk64 <= gk && (direct || gk64 < 8)) gk64 *= 2;
     const int grid = parts > 1 ? grid_for_waves(p.ntile * kTile * parts) : list_grid(p);
-    if (p.half)
-        k_list<true, false><<<grid, kBlock, 0, s>>>(ListArgs{d, p, gk, gk64, parts});
-    else if (p.tile)
-        k_list<false, true><<<grid, kBlock, 0, s>>>(ListArgs{d, p, gk, gk64, parts});
+    if (direct)
+        launch_list_gs<kListG, 0>(d, p, grid, gk, gk64, parts, s);
+    else if (thin)
+        launch_list_gs<kThinG, kThinStage>(d, p, grid, gk, gk64, parts, s);
     else
-        k_list<false, false><<<grid, kBlock, 0, s>>>(ListArgs{d, p, gk, gk64, parts});
+        launch_list_gs<kListG, kStage>(d, p, grid, gk, gk64, parts, s);
 }
 
 void launch_row_tiles(const Dev& d, const Params& p, hipStream_t s) {

@@ -1,0 +1,85 @@
+"""The list build's three forms (entries staged, entries stored directly, two chunks a pass)
+against the oracle, where they meet: capacities either side of the rule's lines, cells of more
+members than a chunk and than a pass, boxes around five particles to a cell."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1210_3450_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def liquid(cells, side, seed):
+    """A jittered lattice at density about 0.8, cells of `side` and a bit."""
+    r = np.random.Generator(np.random.PCG64(seed))
+    L = np.array([(side + 0.02) * n for n in cells])
+    m = np.floor(L / 1.08).astype(int)
+    g = np.stack(np.meshgrid(*[(np.arange(k) + 0.5) / k for k in m], indexing="ij"), -1).reshape(-1, 3) * L
+    return np.mod(g + r.uniform(-0.1, 0.1, g.shape), L), L
+
+
+def gas(cells, per_cell, seed, side=2.83, clump=(3, 0.9), at=1.0):
+    """`per_cell` particles to a cell on average, spread at random, and a clump (a lattice of
+    clump[0] per side and spacing clump[1]) starting `at` before the corner."""
+    r = np.random.Generator(np.random.PCG64(seed))
+    L = np.array([side * n for n in cells])
+    q = r.uniform(0.0, 1.0, (int(per_cell * np.prod(cells)), 3)) * L
+    k = np.stack(np.meshgrid(*[np.arange(clump[0])] * 3, indexing="ij"), -1).reshape(-1, 3) * clump[1]
+    c = k + r.uniform(-0.05, 0.05, k.shape) + L - at
+    return np.mod(np.concatenate([q, c]), L), L
+
+
+# box, cutoff, list capacity, cell side over list radius: cells of 18 to 200 members in boxes whose cells are shared by
+# wavefronts (few cells: direct below 4 keys in the buffer) or not (below 7)
+CASES = {
+    "shared, 4 keys": (lambda: liquid((4, 4, 3), 4.0, 61), 3.7, 512, 0.0),
+    "shared, 3 keys": (lambda: liquid((4, 4, 3), 4.0, 61), 3.7, 704, 0.0),
+    "shared, 200 to a cell": (lambda: liquid((3, 3, 4), 6.4, 62), 6.1, 0, 0.0),
+    "shared, beyond the buffer": (lambda: liquid((3, 4, 3), 2.8, 63), 2.5, 3000, 0.0),
+    "whole, 7 keys": (lambda: liquid((12, 12, 14), 2.8, 64), 2.5, 320, 0.0),
+    "whole, 6 keys": (lambda: liquid((12, 12, 14), 2.8, 64), 2.5, 400, 0.0),
+    "whole, 70 to a cell": (lambda: liquid((12, 11, 12), 4.4, 65), 4.1, 0, 0.0),
+    "thin, empty cells": (lambda: gas((11, 9, 17), 0.4, 66), 2.5, 0, 0.0),
+    "thin, 3 chunks": (lambda: gas((12, 13, 11), 4.6, 67), 2.5, 64, 0.0),
+    "thin, 90 in a cell": (lambda: gas((7, 7, 6), 3.5, 70, 5.65, (5, 1.25), 5.6), 2.5, 64, 2.0),
+    "not thin": (lambda: gas((12, 13, 11), 5.6, 68), 2.5, 0, 0.0),
+    "thin, shared": (lambda: gas((4, 5, 3), 1.5, 69), 2.5, 0, 0.0),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+@pytest.mark.parametrize("layout", ["tiles", "one lane", "four lanes", "half", "ensemble"])
+def test_sets_equal_the_oracle(name, layout):
+    from paper_1210_3450_amd import binding as B
+    make, rc, cap, scale = CASES[name]
+    q, L = make()
+    n = q.shape[0]
+    flags = {"tiles": B.MD_F_TILE_ON, "half": B.MD_F_HALF_LIST}.get(layout, B.MD_F_TILE_OFF)
+    p = B.make_params(n, L, rc=rc, flags=flags, threads_per_key=4 if layout == "four lanes" else 1, list_cap=cap,
+                      cell_scale=scale)
+    copies = 2 if layout == "ensemble" else 1
+    with B.Context([p] * copies if copies > 1 else p) as c:
+        c.set_state(np.tile(q, (copies, 1)), np.zeros((copies * n, 3)))
+        c.build_neighbors()
+        kp, pl = c.get_neighbors()
+    kp, pl = kp.cpu().numpy(), pl.cpu().numpy()
+    kpr, plr = oracle.neighbors(q, L, rc + 0.3)
+    if layout == "half":  # each pair once, whichever key holds it
+        key = np.repeat(np.arange(n), np.diff(kp))
+        got = np.sort(np.minimum(key, pl).astype(np.int64) * n + np.maximum(key, pl))
+        keyr = np.repeat(np.arange(n), np.diff(kpr))
+        ref = np.sort((keyr.astype(np.int64) * n + plr)[keyr < plr])
+        np.testing.assert_array_equal(got, ref)
+        return
+    for b in range(copies):
+        np.testing.assert_array_equal(kp[b * n:(b + 1) * n + 1] - kp[b * n], kpr)
+        np.testing.assert_array_equal(pl[kp[b * n]:kp[(b + 1) * n]] - b * n, plr)
