@@ -446,7 +446,12 @@ void params_refresh(md_ctx* c) {
     P.maxslot = 0;
     P.maxcell = 0;
     P.ncell = 0;
+    // The list build's FP32 test (k_list) needs the squares of cell diagonals, their 2^-24th parts
+    // and a few times either to be normal FP32 numbers; in other units FP64 decides every pair.
+    P.exact = 0;
     for (const BoxGeom& g : c->geom) {
+        const double diag2 = g.cs[0] * g.cs[0] + g.cs[1] * g.cs[1] + g.cs[2] * g.cs[2];
+        if (!(diag2 > 0x1p-90 && diag2 < 0x1p120)) P.exact = 1;
         P.ncell += g.ncell;
         P.maxslot = std::max(P.maxslot, g.nslot);
         P.maxcell = std::max(P.maxcell, g.ncell);

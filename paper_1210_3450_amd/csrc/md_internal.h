@@ -163,6 +163,7 @@ struct Params {
     int32_t maxslot;    // slots of the largest box
     int32_t maxcell;    // cells of the largest box
     int32_t ncell;      // cells over all boxes
+    int32_t exact;      // list build by the FP64 definition alone (see params_refresh)
     int32_t redcap;     // first-level energy sums per box (enough for 8 lanes per key)
 };
 

@@ -1107,7 +1107,8 @@ __device__ __forceinline__ int nb_axis(int c, int o, int n, int& r) {
 // t_i + eps, eps = 32 R^2 2^-24 (4.5e-5 for cells of side 2.8; the FP32 thresholds' own
 // rounding fits in the difference); a key with a candidate between the two (one in 1300) is
 // done again by slow_key with the plain FP64 minimum-image definition, so every set is the
-// one that definition gives, bit for bit.
+// one that definition gives, bit for bit.  Units whose squared lengths leave FP32's range go
+// through slow_key alone (Params::exact).
 constexpr int kListG = 6;     // candidate chunks per pass
 constexpr int kStage = 2560;  // staged list entries per wavefront.  With the room behind it, marks and cell
                               // table 26 KB per block: 6 blocks per CU, as many as the registers allow
@@ -1258,6 +1259,10 @@ __device__ __forceinline__ int list_group(const Dev& d, const Params& p, const P
             }
             if (l == a) n_own = cnt;
         };
+        if (!STAGED && p.exact) {  // uniform: units the FP32 test cannot hold
+            for (int a = 0; a < mb; ++a) slow_key(a);
+            continue;
+        }
         // every chunk's loads first, then the conversions: one memory latency per pass
         double qx[G], qy[G], qz[G];
         float cx[G], cy[G], cz[G], cn[G];
@@ -1375,8 +1380,9 @@ __device__ __forceinline__ int list_group(const Dev& d, const Params& p, const P
     return n_own;
 }
 
-// Six wavefronts per SIMD, eight with two chunks: no vector register is spilled.  Seven (72 VGPRs, 18
-// spilled) take 9-10% longer from 2M particles on.  What bounds it is vector issue: measured on jittered
+// Six wavefronts per SIMD, eight with two chunks: no vector register is spilled (one where entries
+// are stored directly, half lists and row tiles).  Seven (72 VGPRs, 18 spilled) take 9-10% longer
+// from 2M particles on.  What bounds it is vector issue: measured on jittered
 // FCC boxes, list build before (seven FP64 instructions per test, one address for the longest
 // list of a tile) and now: 100k particles at density 0.6 101 -> 43 us, 1M at 0.5 415 -> 220 us,
 // 2M at 0.7 with cutoff 3.0 1150 -> 980 us, 16M 3000 -> 2800 us.
@@ -3062,7 +3068,7 @@ static void launch_list(const Dev& d, const Params& p, hipStream_t s) {
     // direct (us): 36 to a cell (cutoff 3.2, 10 keys fit) 5.1 / 5.9 ms, 58 (6) 8.8 / 8.7, 69 (5) 12.3 /
     // 10.5, 134 (3) 50.1 / 17.7; 500,000 at 228 to a cell (1) 12.6 / 3.5 ms; 32,000 at 93 (5) 160 / 169 us,
     // at 148 (3) 376 / 303.
-    const bool direct = kStage / p.cap < (parts > 1 ? 4 : 7);
+    const bool direct = p.exact || kStage / p.cap < (parts > 1 ? 4 : 7);
     // With fewer than 5 particles to a cell one or two chunks hold all candidates and the registers
     // of four more cost two wavefronts of each SIMD's eight: 8.6M particles, six chunks / two
     // (us), 0.4 to a cell 6640 / 5480, 2.2 3140 / 2630, 4.4 2196 / 2102, 5.5 2044 / 2118, 6.6 1952 / 2081.

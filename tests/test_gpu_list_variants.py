@@ -83,3 +83,24 @@ def test_sets_equal_the_oracle(name, layout):
     for b in range(copies):
         np.testing.assert_array_equal(kp[b * n:(b + 1) * n + 1] - kp[b * n], kpr)
         np.testing.assert_array_equal(pl[kp[b * n]:kp[(b + 1) * n]] - b * n, plr)
+
+
+@pytest.mark.parametrize("layout", ["tiles", "one lane", "half"])
+@pytest.mark.parametrize("e", [-70, 70])
+def test_units_beyond_fp32(e, layout):
+    """Lengths whose squares FP32 cannot hold (FP64 boxes take any units): every step of the build
+    scales exactly with a power of two, so the sets are those of the same box in plain units."""
+    from paper_1210_3450_amd import binding as B
+    q, L = liquid((4, 5, 4), 2.8, 71)
+    n, s = q.shape[0], 2.0 ** e
+    flags = {"tiles": B.MD_F_TILE_ON, "half": B.MD_F_HALF_LIST}.get(layout, B.MD_F_TILE_OFF)
+    got = []
+    for k in (1.0, s):
+        p = B.make_params(n, L * k, rc=2.5 * k, skin=0.3 * k, flags=flags, threads_per_key=1)
+        with B.Context(p) as c:
+            c.set_state(q * k, np.zeros_like(q))
+            c.build_neighbors()
+            got.append([t.cpu().numpy() for t in c.get_neighbors()])
+    assert got[0][0][-1] > 10 * n
+    for x, y in zip(*got):
+        np.testing.assert_array_equal(x, y)
