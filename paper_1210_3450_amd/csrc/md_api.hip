@@ -730,9 +730,10 @@ bool runs_ahead(const md_ctx* c) {
     return c->nbox == 1 && c->prm.rebuild != MD_REBUILD_EVERY_STEP && !(c->prm.flags & MD_F_VERIFY_LIST);
 }
 
-// Waits for the decision on drift seq: its code (see k_dutc), or 2 when the stream has run
-// dry without one.
+// Waits for the decision on drift seq: its code (see k_dutc).  A stream that runs dry without
+// one is an error: a launch has failed.
 md_status wait_told(md_ctx* c, uint32_t seq, uint32_t* code) {
+    LAUNCHCHK(c);  // here, since the query below leaves an error of its own behind
     const uint32_t* w = c->told_h + (seq & (kToldRing - 1));
     const uint32_t tag = seq << 2;
     for (uint32_t spin = 1;; ++spin) {
@@ -746,7 +747,8 @@ md_status wait_told(md_ctx* c, uint32_t seq, uint32_t* code) {
             if (e != hipErrorNotReady) {
                 HIPCHK(c, e);
                 v = __atomic_load_n(w, __ATOMIC_ACQUIRE);
-                *code = (v & ~3u) == tag ? v & 3u : 2u;
+                if ((v & ~3u) != tag) return fail(c, MD_EHIP, "drift %u ended without a rebuild decision", seq);
+                *code = v & 3u;
                 return MD_OK;
             }
             (void)hipGetLastError();  // "not ready" is no error of ours
@@ -1252,6 +1254,9 @@ md_status md_step(md_ctx* c, int32_t nsteps, int32_t energy_every) {
             opened = true;
             continue;
         }
+        const int32_t drifts = chunk - (opened ? 1 : 0);
+        if (c->st_h[0].nstep - nstep0 != drifts)
+            return fail(c, MD_EHIP, "%d of %d steps ran", c->st_h[0].nstep - nstep0, drifts);
         if (thermo) {  // k_vscale applied the pending factor: the next kick starts from 1
             for (int b = 0; b < c->nbox; ++b) c->st_h[b].vscale = 1.0;
             if ((s = push_states(c)) != MD_OK) return s;
