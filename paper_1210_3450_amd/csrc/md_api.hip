@@ -61,6 +61,7 @@ struct md_ctx {
     uint32_t* told_h = nullptr;  // host address of D.told
     uint32_t seq = 0;            // number of the last drift enqueued with a decision to wait for
     int64_t list_alloc = 0;      // entries allocated in D.list
+    bool cells_laid = false;     // the cell arrays exist and the geometry is uploaded
     bool have_state = false, have_cells = false, have_list = false, have_F = false;
     md_status sticky = MD_OK;
     std::string err;
@@ -392,6 +393,25 @@ md_status alloc_list(md_ctx* c, int32_t cap) {
     return MD_OK;
 }
 
+// The cell arrays and the geometry of the present grid.  What is there goes first, since both
+// together may not fit; after a failure nothing is launched on them until ensure_arrays has
+// laid them again.
+md_status lay_cells(md_ctx* c) {
+    md_status s;
+    c->cells_laid = c->have_cells = c->have_list = c->have_F = false;
+    if ((s = alloc_cells(c)) != MD_OK || (s = upload_geometry(c)) != MD_OK) return s;
+    c->cells_laid = true;
+    return MD_OK;
+}
+
+// The arrays a build works on, laid again after a call that ran out of memory.
+md_status ensure_arrays(md_ctx* c) {
+    md_status s;
+    if (!c->cells_laid && (s = lay_cells(c)) != MD_OK) return s;
+    if (!c->D.list && (s = alloc_list(c, c->P.cap)) != MD_OK) return s;
+    return MD_OK;
+}
+
 // A larger list during stepping: the entries move to the new layout, so the boxes
 // that do not rebuild at the step the overflow stopped keep their lists.
 md_status grow_list_keeping(md_ctx* c, int32_t cap) {
@@ -582,7 +602,6 @@ md_status alloc_all(md_ctx* c) {
     A(D.series_th, (size_t)kMaxSeries * c->nbox);
     A(c->dscratch, (size_t)c->nbox);
 #undef A
-    if ((s = alloc_cells(c)) != MD_OK) return s;
     HIPCHK(c, hipMemsetAsync(D.any, 0, sizeof(int32_t), c->stream));
     HIPCHK(c, hipMemsetAsync(D.halt, 0, sizeof(int32_t), c->stream));
     HIPCHK(c, hipMemsetAsync(D.need_s, 0, sizeof(int32_t) * c->nbox * kNeedStripes * kNeedStride, c->stream));
@@ -873,6 +892,7 @@ void clear_halt(md_ctx* c) { launch_fill_i32(c->D.halt, 0, 1, c->stream); }
 // Full list build for every box, growing the list until it fits.
 md_status build_list(md_ctx* c) {
     md_status s;
+    if ((s = ensure_arrays(c)) != MD_OK) return s;
     for (int attempt = 0; attempt < 8; ++attempt) {
         clear_halt(c);
         launch_mark_rebuild(c->D, c->P, c->stream);
@@ -894,6 +914,7 @@ md_status build_list(md_ctx* c) {
         }
         // grow and rebuild (the overflow stopped the chain before the permuted buffers
         // became current; the rebuild sorts the same slots by cell again)
+        c->have_list = c->have_F = false;
         if ((s = alloc_list(c, need + need / 4 + 8)) != MD_OK) return s;
         c->regrows += 1;
         for (int b = 0; b < c->nbox; ++b) c->st_h[b].need = 0;
@@ -1006,7 +1027,7 @@ md_status create_impl(const md_params* boxes, int32_t nbox, void* stream, md_ctx
     if (c->prm.flags & MD_F_HALF_LIST) tpk = 1;
     c->P.tpk = tpk;
     params_refresh(c);
-    if ((s = alloc_all(c)) != MD_OK || (s = upload_geometry(c)) != MD_OK ||
+    if ((s = alloc_all(c)) != MD_OK || (s = lay_cells(c)) != MD_OK ||
         (s = alloc_list(c, c->prm.list_cap > 0 ? c->prm.list_cap : estimate_cap(c))) != MD_OK) {
         g_create_err = c->err;
         free_all(c);
@@ -1096,10 +1117,7 @@ md_status md_rescale_box(md_ctx* c, double alpha) {
     c->prm.box[2] = c->boxes[0].box[2];
     layout(c);
     params_refresh(c);
-    if ((s = alloc_cells(c)) != MD_OK) return s;
-    if ((s = upload_geometry(c)) != MD_OK) return s;
-    c->have_cells = c->have_list = c->have_F = false;
-    return MD_OK;
+    return lay_cells(c);
 }
 
 md_status md_scale_velocities(md_ctx* c, const double* scale) {
@@ -1120,6 +1138,7 @@ md_status md_build_cells(md_ctx* c) {
     md_status s;
     if ((s = check_ctx(c)) != MD_OK) return s;
     if (!c->have_state) return fail(c, MD_ESTATE, "no state: call md_set_state first");
+    if ((s = ensure_arrays(c)) != MD_OK) return s;
     for (int attempt = 0; attempt < 2; ++attempt) {
         clear_halt(c);
         launch_mark_rebuild(c->D, c->P, c->stream);
@@ -1685,13 +1704,12 @@ md_status md_autotune(md_ctx* c, const char* cache_path) {
         c->cell_scale = k.pct / 100.0;
         c->prefer_gather = !k.tile;
         c->tile_fallback = fallback0;
+        dfree(c->D.list);  // its layout goes with the lanes per key
         c->P.tpk = k.tpk;
         layout(c);
         params_refresh(c);
-        if ((r = alloc_cells(c)) != MD_OK) return r;
-        if ((r = upload_geometry(c)) != MD_OK) return r;
+        if ((r = lay_cells(c)) != MD_OK) return r;
         if ((r = alloc_list(c, c->P.cap)) != MD_OK) return r;
-        c->have_cells = c->have_list = c->have_F = false;
         return build_list(c);
     };
 

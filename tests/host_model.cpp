@@ -6,10 +6,14 @@
 #include "../paper_1210_3450_amd/csrc/md_api.hip"
 
 #include <cstdlib>
+#include <functional>
+#include <map>
 
 namespace {
 struct Model {
-    int allocs = 0, fail_at = -1;  // the fail_at-th allocation from now on fails (0: the next)
+    std::map<const void*, size_t> size;  // live allocations
+    int fail_at = -1;              // the fail_at-th allocation from now on fails (0: the next)
+    bool full = false;             // every allocation fails
     hipError_t last = hipSuccess;
     int busy = 0;                  // stream queries that find the stream busy
     int dutc = 0, drop_dutc = -1;  // launches of k_dutc; the one that is lost
@@ -32,7 +36,10 @@ void need_arrays(const Dev& d, const Params& p, const char* kernel, bool list) {
     bool ok = d.geom && d.st && d.any && d.halt && d.wave_box && d.tile_box && d.q[0] && d.q[1] && d.cnt && d.perm &&
               d.cell_cnt && d.cell_start && d.tile_sum && d.tile_pref && d.ke_part && d.pe_part && d.vir_part && d.red;
     if (p.tile) ok = ok && d.rtile && d.row_box && d.row_nt && d.row_t0 && d.cell_rt && d.rt_tmp && d.rt_rec;
-    if (list) ok = ok && d.list;
+    ok = ok && M.size[d.cell_cnt] >= (size_t)p.ntile * kTile * 4;
+    if (p.tile) ok = ok && M.size[d.cell_rt] >= (size_t)p.ntile * kTile * 4 && M.size[d.row_nt] >= p.nrows * (size_t)4;
+    if (list)
+        ok = ok && d.list && p.rows * p.tpk == p.cap && M.size[d.list] >= (size_t)p.nwave * kWave * p.cap * 2;
     if (ok) return;
     std::fprintf(stderr, "%s launched on an array that is not there\n", kernel);
     std::exit(3);
@@ -43,13 +50,13 @@ bool off(const Dev& d) { return *d.halt || *d.any; }
 // ---- the runtime
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
-    if (M.fail_at >= 0 && M.fail_at-- == 0) return hipErrorOutOfMemory;
-    ++M.allocs;
+    if (M.full || (M.fail_at >= 0 && M.fail_at-- == 0)) return M.last = hipErrorOutOfMemory;
     *p = std::calloc(1, n);
+    M.size[*p] = n;
     return hipSuccess;
 }
 hipError_t hipFree(void* p) {
-    if (p) --M.allocs;
+    M.size.erase(p);
     std::free(p);
     return hipSuccess;
 }
@@ -233,7 +240,7 @@ void plain() {
         M.need = 40;
         md_destroy(c);
     }
-    CHECK(M.allocs == 0);
+    CHECK(M.size.empty());
 }
 
 // A decision that never comes is an error, whichever drift it is and whether or not the launch
@@ -262,12 +269,55 @@ void lost_decision() {
                         md_destroy(c);
                     }
 }
+
+// Memory runs out inside each call that lays arrays anew, at each of its allocations: the call says
+// so, no later call launches on what is missing, and once there is memory again the context goes on.
+void out_of_memory() {
+    const std::function<md_status(md_ctx*)> ops[] = {
+        [](md_ctx* c) { return md_rescale_box(c, 1.3); },
+        [](md_ctx* c) { return md_autotune(c, nullptr); },
+        [](md_ctx* c) { return M.need = 500, md_build_neighbors(c); },
+        [](md_ctx* c) { return M.need = 500, md_step(c, 20, 0); },
+    };
+    const double x = 0.0;
+    std::vector<int64_t> kp(4001);
+    for (uint32_t flags : {0u, (uint32_t)MD_F_TILE_ON, (uint32_t)MD_F_HALF_LIST})
+        for (const auto& op : ops)
+            for (int k = 0, failed = 1; failed; ++k) {
+                M.need = 40;
+                md_ctx* c = open(params(flags));
+                CHECK(md_step(c, 3, 0) == MD_OK);
+                M.fail_at = k;
+                const md_status s = op(c);
+                failed = M.fail_at < 0;  // the k-th allocation was reached
+                CHECK(s == (failed ? MD_ENOMEM : MD_OK));
+                M.fail_at = -1;
+                M.full = failed;  // nothing comes back at first
+                const int32_t done = (int32_t)c->steps;
+                auto only = [&](md_status t) { CHECK(t == MD_OK || t == MD_ENOMEM || t == MD_ESTATE); };
+                only(md_get_neighbors(c, kp.data(), nullptr, 0, nullptr) == MD_EINVAL ? MD_OK : MD_ESTATE);
+                only(md_compute_forces(c, nullptr));
+                only(md_step(c, 0, 0));
+                only(md_energy(c, nullptr, nullptr));
+                only(md_build_cells(c));
+                only(md_build_neighbors(c));
+                only(md_rescale_box(c, 1.0));
+                only(md_autotune(c, nullptr));
+                CHECK(c->sticky == MD_OK && c->steps == done);
+                M.full = false;
+                CHECK(md_step(c, 10, 0) == MD_OK && c->steps == done + 10);
+                CHECK(md_set_state(c, &x, &x) == MD_OK && md_step(c, 10, 0) == MD_OK);
+                md_destroy(c);
+            }
+    CHECK(M.size.empty());
+}
 }  // namespace
 
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "plain") plain();
     else if (what == "lost_decision") lost_decision();
+    else if (what == "out_of_memory") out_of_memory();
     else return std::fprintf(stderr, "unknown scenario\n"), 2;
     return g_fail ? 1 : 0;
 }
