@@ -321,8 +321,9 @@ md_status upload_geometry(md_ctx* c) {
                              c->stream));
     HIPCHK(c, hipMemcpyAsync(c->D.tile_box, tb.data(), sizeof(int32_t) * tb.size(), hipMemcpyHostToDevice,
                              c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->D.row_box, rb.data(), sizeof(int32_t) * rb.size(), hipMemcpyHostToDevice,
-                             c->stream));
+    if (c->D.row_box)  // a context with row tiles
+        HIPCHK(c, hipMemcpyAsync(c->D.row_box, rb.data(), sizeof(int32_t) * rb.size(), hipMemcpyHostToDevice,
+                                 c->stream));
     HIPCHK(c, hipMemcpyAsync(c->D.dshift, dsh.data(), sizeof(double4) * dsh.size(), hipMemcpyHostToDevice,
                              c->stream));
     // the vectors above are pageable: finish the copies before they go away
@@ -350,15 +351,18 @@ md_status alloc_cells(md_ctx* c) {
     dfree(c->D.red);
     md_status s;
     const size_t ncellpad = (size_t)c->ntile * kTile;
-    // energy partials: per list wavefront, or per row tile (at most one per cell)
-    const size_t nparts = std::max((size_t)c->nwave * 8, ncellpad);
-    if ((s = dalloc(c, &c->D.rtile, c->ntilemax)) != MD_OK) return s;
-    if ((s = dalloc(c, &c->D.row_box, c->nrows)) != MD_OK) return s;
-    if ((s = dalloc(c, &c->D.row_nt, c->nrows)) != MD_OK) return s;
-    if ((s = dalloc(c, &c->D.row_t0, c->nrows)) != MD_OK) return s;
-    if ((s = dalloc(c, &c->D.cell_rt, ncellpad)) != MD_OK) return s;
-    if ((s = dalloc(c, &c->D.rt_tmp, ncellpad)) != MD_OK) return s;
-    if ((s = dalloc(c, &c->D.rt_rec, c->ntilemax * kTileRec)) != MD_OK) return s;
+    // energy partials: per list wavefront, or per row tile
+    size_t nparts = (size_t)c->nwave * 8;
+    if (c->P.tile) {  // some 170 bytes per cell, which sparse boxes have many of
+        nparts = std::max(nparts, (size_t)c->ntilemax);
+        if ((s = dalloc(c, &c->D.rtile, c->ntilemax)) != MD_OK) return s;
+        if ((s = dalloc(c, &c->D.row_box, c->nrows)) != MD_OK) return s;
+        if ((s = dalloc(c, &c->D.row_nt, c->nrows)) != MD_OK) return s;
+        if ((s = dalloc(c, &c->D.row_t0, c->nrows)) != MD_OK) return s;
+        if ((s = dalloc(c, &c->D.cell_rt, ncellpad)) != MD_OK) return s;
+        if ((s = dalloc(c, &c->D.rt_tmp, ncellpad)) != MD_OK) return s;
+        if ((s = dalloc(c, &c->D.rt_rec, c->ntilemax * kTileRec)) != MD_OK) return s;
+    }
     if ((s = dalloc(c, &c->D.ke_part, nparts)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.pe_part, nparts)) != MD_OK) return s;
     if ((s = dalloc(c, &c->D.vir_part, nparts)) != MD_OK) return s;

@@ -311,6 +311,26 @@ void out_of_memory() {
             }
     CHECK(M.size.empty());
 }
+
+// Bytes of a sparse box's arrays: a context without row tiles pays nothing for them (39 words a
+// tile), whichever way it came to the gather format, and the autotuner lays them when it needs them.
+void tile_arrays() {
+    auto bytes = [](uint32_t flags) {
+        md_params p = params(flags);
+        p.box[0] = p.box[1] = p.box[2] = 280.0;  // 10^6 cells
+        md_ctx* c = open(p);
+        size_t n = 0;
+        for (const auto& a : M.size) n += a.second;
+        CHECK((c->D.rt_rec != nullptr) == (flags == MD_F_TILE_ON));
+        CHECK(md_step(c, 5, 0) == MD_OK && md_autotune(c, nullptr) == MD_OK && md_step(c, 5, 0) == MD_OK);
+        md_destroy(c);
+        return n;
+    };
+    const size_t tiles = bytes(MD_F_TILE_ON);
+    for (uint32_t flags : {0u, (uint32_t)MD_F_TILE_OFF, (uint32_t)MD_F_HALF_LIST}) {
+        CHECK(bytes(flags) < 16u * 1000000 && tiles > 150u * 1000000);
+    }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -318,6 +338,7 @@ int main(int argc, char** argv) {
     if (what == "plain") plain();
     else if (what == "lost_decision") lost_decision();
     else if (what == "out_of_memory") out_of_memory();
+    else if (what == "tile_arrays") tile_arrays();
     else return std::fprintf(stderr, "unknown scenario\n"), 2;
     return g_fail ? 1 : 0;
 }

@@ -20,7 +20,7 @@ def host_model(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["plain", "lost_decision", "out_of_memory"])
+@pytest.mark.parametrize("scenario", ["plain", "lost_decision", "out_of_memory", "tile_arrays"])
 def test_host_model(host_model, scenario):
     r = subprocess.run([host_model, scenario], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, (r.returncode, r.stderr[-4000:])
