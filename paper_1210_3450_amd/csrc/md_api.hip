@@ -1746,12 +1746,15 @@ md_status md_autotune(md_ctx* c, const char* cache_path) {
         }
         for (hipEvent_t& e : ev) (void)hipEventDestroy(e);
     }
+    // tiles alone allowed and none that fits: the first candidate, which falls back to the gather format
+    const bool timed = best.tpk != 0;
+    if (!timed) best = cands[0];
     if ((s = apply(best)) != MD_OK) return s;
     if ((s = ensure_list_and_forces(c)) != MD_OK) return s;
     if ((s = sync_states(c)) != MD_OK) return s;
     for (int b = 0; b < c->nbox; ++b) c->st_h[b].built = built[b];
     if ((s = push_states(c)) != MD_OK) return s;
-    if (cache_path && !from_cache) {
+    if (cache_path && !from_cache && timed) {
         std::ofstream out(cache_path, std::ios::app);
         if (out) out << key << " " << best.tpk << " " << (best.tile ? 1 : 0) << " " << best.pct << "\n";
     }

@@ -331,6 +331,24 @@ void tile_arrays() {
         CHECK(bytes(flags) < 16u * 1000000 && tiles > 150u * 1000000);
     }
 }
+
+// The autotuner where no row tile fits the staging capacity: with MD_F_TILE_ON the context is the
+// gather format's by itself, and there is no candidate to time.
+void autotune_without_tiles() {
+    const char* cache = "host_model_tune.txt";
+    std::remove(cache);
+    M.tile_overflow = true;
+    for (uint32_t flags : {0u, (uint32_t)MD_F_TILE_ON})
+        for (const char* path : {(const char*)nullptr, cache}) {
+            md_ctx* c = open(params(flags));
+            CHECK(md_step(c, 5, 0) == MD_OK);
+            CHECK(md_autotune(c, path) == MD_OK);
+            CHECK(c->P.tpk >= 1 && c->P.tile == 0);
+            CHECK(md_step(c, 5, 0) == MD_OK && steps(c) == 10);
+            md_destroy(c);
+        }
+    std::remove(cache);
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -339,6 +357,7 @@ int main(int argc, char** argv) {
     else if (what == "lost_decision") lost_decision();
     else if (what == "out_of_memory") out_of_memory();
     else if (what == "tile_arrays") tile_arrays();
+    else if (what == "autotune_without_tiles") autotune_without_tiles();
     else return std::fprintf(stderr, "unknown scenario\n"), 2;
     return g_fail ? 1 : 0;
 }
