@@ -80,15 +80,15 @@ typedef enum {
                                       box with MD_REBUILD_EVERY_STEP; other one-box runs enqueue a list
                                       build only where a step needs one and gain nothing from graphs) */
 #define MD_F_TILE_ON 4u            /* row tiles (threads_per_key 0 or 1; the default for a largest box
-                                      of 2^18 particles or more whose cells hold 4 to 36, FP64 30, on
+                                      of 2^18 particles or more whose cells hold 4 to 75, FP64 30, on
                                       average): pairs of rows of
                                       cells are cut into slices whose partners (the neighbouring
                                       rows, one cell wider each side) a block stages in LDS once
                                       (fixed-point records for FP32-mixed, FP64 positions for FP64);
                                       list entries name staged records and the force pass reads every
                                       partner from LDS.  A context whose cells are too crowded for the
-                                      staging capacity (2048 particles in a slice of one cell per row
-                                      and its neighbours) switches to the gather format by itself. */
+                                      staging capacity (3072 particles, FP64 2720, in a slice of one cell
+                                      per row and its neighbours) switches to the gather format by itself. */
 #define MD_F_TILE_OFF 8u           /* the gather format instead of row tiles (every partner read from
                                       global memory by cell and rank; the default for other boxes) */
 #define MD_F_FAST_RCP 16u          /* FP64 path: 1/r^2 from the hardware reciprocal, with the

@@ -27,7 +27,7 @@ namespace {
 constexpr int kChunk = 200;      // steps enqueued between status checks
 // Boxes that take row tiles by default: particles, and particles per cell (at most: FP64, FP32-mixed).
 constexpr int64_t kTileMinN = 1 << 18;
-constexpr double kTileMinCell = 4.0, kTileMaxCell[2] = {30.0, 36.0};
+constexpr double kTileMinCell = 4.0, kTileMaxCell[2] = {30.0, 75.0};
 constexpr int kGraphSteps = 8;   // continuing steps per captured graph
 
 // Message of the last failed md_create / md_batch_create (no context exists then).
@@ -48,6 +48,7 @@ struct md_ctx {
     int64_t ntotal = 0;
     int32_t nslot = 0, nwave = 0, ntile = 0, nrows = 0;
     int64_t ntilemax = 0;          // row tiles at most: one per beam and x
+    int cus = 0;                   // compute units of the device
     bool tile_fallback = false;    // a row tile overflowed its staging capacity: gather format from then on
     bool prefer_gather = false;    // gather format over row tiles: by size at creation, or md_autotune's choice
     double cell_scale = 0.0;       // > 0: cell side bound chosen by md_autotune (else the boxes' own)
@@ -465,7 +466,15 @@ void params_refresh(md_ctx* c) {
     P.tile = !P.half && P.tpk == 1 && !(p.flags & MD_F_TILE_OFF) && !c->tile_fallback && !c->prefer_gather ? 1 : 0;
     P.recb = p.precision == MD_PREC_FP64 ? 24 : 12;  // FP64 x, y, z or three fixed-point ints
     P.kt = kRtBlock;
-    P.scap = kStageCap;
+    // Staging capacity: a tile holds as many one-cell slices as fit, so in crowded cells a small capacity
+    // leaves lanes without keys.  Steps of 500,000 particles at density 0.84 (us), FP32-mixed 2048 / 3072
+    // records: 25 to a cell 104.6 / 102.4, 32 127.9 / 114.7, 47 196.5 / 170.0 (4096 and three blocks: 175.5),
+    // 63 does not fit / 191.8; FP64 2048 / 2720: 25 to a cell 140.9 / 159.8, 32 182 / 168, 47 326 / 266.
+    double dense = 0.0;
+    for (const BoxGeom& g : c->geom) dense = std::max(dense, (double)g.npart / g.ncell);
+    const int32_t scap = p.precision != MD_PREC_FP64 ? kStageCap32 : (dense > 30.0 ? kStageDense64 : kStageCap64);
+    if (scap != P.scap) P.tgrid = 0;  // another number of resident blocks
+    P.scap = scap;
     P.nrows = c->nrows;
     P.maxslot = 0;
     P.maxcell = 0;
@@ -483,13 +492,13 @@ void params_refresh(md_ctx* c) {
     P.redcap = (std::max(P.maxslot / kWave * 8, P.maxcell) + kRedSeg - 1) / kRedSeg;
     // Row-tile force kernel: one resident round of blocks, each looping over the tiles (TileWalk);
     // a grid of one block per tile measured 16% slower at 32M particles.
-    if (P.tgrid <= 0) {
+    if (c->cus <= 0) {
         hipDeviceProp_t prop;
-        int cus = 256;
+        c->cus = 256;
         if (hipGetDeviceProperties(&prop, c->device) == hipSuccess && prop.multiProcessorCount > 0)
-            cus = prop.multiProcessorCount;
-        P.tgrid = std::max(8, cus * rowtile_blocks_per_cu(P));
+            c->cus = prop.multiProcessorCount;
     }
+    if (P.tgrid <= 0) P.tgrid = std::max(8, c->cus * rowtile_blocks_per_cu(P));
     P.fastrcp = (p.flags & MD_F_FAST_RCP) ? 1 : 0;
 }
 
@@ -1016,8 +1025,10 @@ md_status create_impl(const md_params* boxes, int32_t nbox, void* stream, md_ctx
     // its cells hold kTileMinCell to kTileMaxCell on average: with fewer the copies of a slice
     // outweigh its pairs in the first builds of a run (2M particles at 2.2 to a cell, lists, forces and
     // energies of new positions FP64 1467 / 1788, FP32-mixed 1273 / 1430, steps 262 / 243, 220 / 215), with
-    // more its region is mostly margin, and many are near the staging capacity (steps, 37 to a cell
-    // 895 / 931, 687 / 615; 48 1120 / 1320, 852 / 810).
+    // more a slice and its neighbours come near the staging capacity, and past it every build is made
+    // twice.  Steps of 500,000 particles: FP32-mixed, 36 to a cell 166.6 / 130.7, 47 211 / 170, 63 257 / 192, 73
+    // 328 / 275; FP64 25 to a cell 156 / 141, 36 216 / 189, 47 275 / 266, but with one lane per key left
+    // where a tile does overflow (63 to a cell 330, with one lane 398).
     int big = 0;
     for (int b = 1; b < c->nbox; ++b)
         if (c->boxes[b].n > c->boxes[big].n) big = b;

@@ -76,7 +76,12 @@ static_assert(kPieces <= 64, "one lane per piece");
 static_assert(kPieces + 1 + kBeamRows <= 64, "one lane per word of a record");
 constexpr int kTileRec = kPieces + 1 + kBeamRows;   // words of a row tile's record
 constexpr int kRtBlock = 256;            // threads per block of the row-tile force kernel (keys per tile)
-constexpr int kStageCap = 2048;          // staged records per row tile (24 KB of LDS, FP64 48 KB)
+// Staged records per row tile.  FP32-mixed: 36 KB of LDS, as much as four blocks per CU leave.  FP64:
+// 48 KB, three blocks, or 64 KB (all that 16-bit entries reach) and two blocks where cells are so full
+// that the smaller capacity leaves a tile few slices (params_refresh).
+constexpr int kStageCap32 = 3072;
+constexpr int kStageCap64 = 2048, kStageDense64 = 2720;
+static_assert(12 * kStageCap32 < 65536 && 24 * kStageDense64 < 65536, "entries are 16-bit byte offsets");
 constexpr int kRedSeg = 2048;            // energy partials per first-level segment
 
 // Position record of one slot.  cc and cnt ride in the 8 bytes a double4
