@@ -1313,6 +1313,7 @@ __device__ __forceinline__ int list_group(const Dev& d, const Params& p, const P
             constexpr bool SELF0 = decltype(self0_c)::value;
             const int st0 = STAGED ? (int)(lds_addr(stage) >> 1) : 0;
             const int tsh = STAGED ? 0 : __builtin_ctz((unsigned)p.tpk);
+            const uint32_t tmask = (uint32_t)p.tpk - 1u;
             for (int a = 0; a < mb; ++a) {
                 const float Kx = readlane_f(kx, a), Ky = readlane_f(ky, a), Kz = readlane_f(kz, a);
                 const float lo = readlane_f(tlo, a), hi = readlane_f(thi, a);
@@ -1345,9 +1346,12 @@ __device__ __forceinline__ int list_group(const Dev& d, const Params& p, const P
                     } else {
                         const uint32_t pos = __builtin_amdgcn_mbcnt_hi(
                             (unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, (uint32_t)at));
+                        unsigned long long sm = mask;
+                        if (at + __popcll(mask) > cap)  // overflow: the entries that fit
+                            sm &= __builtin_amdgcn_ballot_w64((int)pos < cap);
                         const uint32_t mm = pos >> tsh;  // list_addr's offset of entry pos
-                        if (__builtin_amdgcn_inverse_ballot_w64(mask) && (int)pos < cap)
-                            kp[((mm & ~7u) << 6) + ((pos & (uint32_t)(p.tpk - 1)) << 3) + (mm & 7u)] = e;
+                        if (__builtin_amdgcn_inverse_ballot_w64(sm))
+                            kp[mm + __umul24(mm >> 3, 504u) + ((pos & tmask) << 3)] = e;
                     }
                     at = keep_scalar(at + __popcll(mask));
                 }
@@ -3063,12 +3067,12 @@ static void launch_list(const Dev& d, const Params& p, hipStream_t s) {
     int parts = 3072 / cells;
     parts = parts < 1 ? 1 : (parts > 8 ? 8 : parts);
     // Every group loads and converts all candidates of its cell again, so long lists, of which the
-    // buffer holds few, are stored directly by groups of a whole chunk instead: from fewer than 7 keys
-    // (4 where wavefronts share a cell) on.  Rebuild chain, 8.6M particles at density 0.84, staged /
-    // direct (us): 36 to a cell (cutoff 3.2, 10 keys fit) 5.1 / 5.9 ms, 58 (6) 8.8 / 8.7, 69 (5) 12.3 /
-    // 10.5, 134 (3) 50.1 / 17.7; 500,000 at 228 to a cell (1) 12.6 / 3.5 ms; 32,000 at 93 (5) 160 / 169 us,
-    // at 148 (3) 376 / 303.
-    const bool direct = p.exact || kStage / p.cap < (parts > 1 ? 4 : 7);
+    // buffer holds few, are stored directly by groups of a whole chunk instead: from fewer than 6 keys
+    // (4 where wavefronts share a cell) on.  Rebuild chain between steps, 8.6M particles at density
+    // 0.84, staged / direct: 36 to a cell (cutoff 3.2, 10 keys fit) 5.1 / 5.9 ms, 58 (6) 8.2 / 8.7, 69 (5)
+    // 12.0 / 10.3, 134 (3) 50.1 / 17.7; 500,000 at 228 to a cell (1) 12.6 / 3.5 ms; 32,000 at 93 (5)
+    // 160 / 169 us, at 148 (3) 376 / 303.
+    const bool direct = p.exact || kStage / p.cap < (parts > 1 ? 4 : 6);
     // With fewer than 5 particles to a cell one or two chunks hold all candidates and the registers
     // of four more cost two wavefronts of each SIMD's eight: 8.6M particles, six chunks / two
     // (us), 0.4 to a cell 6640 / 5480, 2.2 3140 / 2630, 4.4 2196 / 2102, 5.5 2044 / 2118, 6.6 1952 / 2081.

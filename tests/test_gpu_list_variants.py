@@ -39,14 +39,14 @@ def gas(cells, per_cell, seed, side=2.83, clump=(3, 0.9), at=1.0):
 
 
 # box, cutoff, list capacity, cell side over list radius: cells of 18 to 200 members in boxes whose cells are shared by
-# wavefronts (few cells: direct below 4 keys in the buffer) or not (below 7)
+# wavefronts (few cells: direct below 4 keys in the buffer) or not (below 6)
 CASES = {
     "shared, 4 keys": (lambda: liquid((4, 4, 3), 4.0, 61), 3.7, 512, 0.0),
     "shared, 3 keys": (lambda: liquid((4, 4, 3), 4.0, 61), 3.7, 704, 0.0),
     "shared, 200 to a cell": (lambda: liquid((3, 3, 4), 6.4, 62), 6.1, 0, 0.0),
     "shared, beyond the buffer": (lambda: liquid((3, 4, 3), 2.8, 63), 2.5, 3000, 0.0),
-    "whole, 7 keys": (lambda: liquid((12, 12, 14), 2.8, 64), 2.5, 320, 0.0),
     "whole, 6 keys": (lambda: liquid((12, 12, 14), 2.8, 64), 2.5, 400, 0.0),
+    "whole, 5 keys": (lambda: liquid((12, 12, 14), 2.8, 64), 2.5, 448, 0.0),
     "whole, 70 to a cell": (lambda: liquid((12, 11, 12), 4.4, 65), 4.1, 0, 0.0),
     "thin, empty cells": (lambda: gas((11, 9, 17), 0.4, 66), 2.5, 0, 0.0),
     "thin, 3 chunks": (lambda: gas((12, 13, 11), 4.6, 67), 2.5, 64, 0.0),
