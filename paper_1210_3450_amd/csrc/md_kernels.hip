@@ -1415,17 +1415,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(G == kTh
     uint16_t* stage = stage_all[wv];
     uint8_t* mark = mark_all[wv];
     int4* tab = tab_all[wv];
-    // Part `part` of home cell c of box b.
-    auto cell_body = [&](int c, int part, int b, const BoxGeom& g, const ListArgs& A) {
+    // Part `part` of home cell c (m members from slot cs0 on) of box b.
+    auto cell_body = [&](int c, int m, int cs0, int part, int b, const BoxGeom& g, const ListArgs& A) {
         const Dev& d = A.d;
         const Params& p = A.p;
         const int cap = p.cap;
         const BoxState& st = d.st[b];
         const int local = c - g.cell_off;
-        const int m = ld_const(d.cell_cnt + c);
         const int gk = m > kWave ? A.gk64 : A.gk;
         if (part * gk >= m) return;
-        const int cs0 = ld_const(d.cell_start + c);
         Pos* __restrict__ q = d.q[ld_const(&st.sq) ^ 1];  // permuted, made current after the build
         const int ly = gdiv(g, local, 0), cz = gdiv(g, local, 2);
         const int cx = local - ly * g.n[0], cy = ly - cz * g.n[1];
@@ -1546,12 +1544,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(G == kTh
         const Dev& d = A.d;
         const int ncells = A.p.ntile * kTile;
         const int part = A.parts > 1 ? it / ncells : 0, c = it - part * ncells;
-        // tables this kernel does not write, read through the scalar cache
+        // tables this kernel does not write, read through the scalar cache, the cell's own before its
+        // box is known (beyond the box's cells they may hold anything): an empty cell ends there
         const int b = ld_const(d.tile_box + c / kTile);
-        if (!ld_const(&d.st[b].rebuild)) continue;
+        const int m = ld_const(d.cell_cnt + c), cs0 = ld_const(d.cell_start + c);
+        if (m == 0 || !ld_const(&d.st[b].rebuild)) continue;
         const BoxGeom g = ld_geom(d.geom + b);
         if (c - g.cell_off >= g.ncell) continue;
-        cell_body(c, part, b, g, A);
+        cell_body(c, m, cs0, part, b, g, A);
     }
 }
 
