@@ -29,7 +29,7 @@
  *   - The context owns all internal device memory; it is allocated in
  *     md_create / md_batch_create.  Afterwards only a list build whose capacity
  *     overflowed grows the list, md_rescale_box re-allocates the cell arrays
- *     when the number of cells changes, and md_autotune re-allocates the cell
+ *     when the cells outgrow them, and md_autotune re-allocates the cell
  *     and list arrays for the layout it picks (plus a caller-order copy of the
  *     state on its first call).  No allocation happens per step otherwise.
  *   - Calls are asynchronous on the context stream unless marked

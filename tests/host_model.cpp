@@ -349,6 +349,24 @@ void autotune_without_tiles() {
         }
     std::remove(cache);
 }
+
+// Rescaling allocates only when the cells outgrow their arrays.
+void rescale_in_place() {
+    for (uint32_t flags : {0u, (uint32_t)MD_F_TILE_ON, (uint32_t)MD_F_HALF_LIST}) {
+        md_ctx* c = open(params(flags));
+        CHECK(md_step(c, 3, 0) == MD_OK);
+        CHECK(md_rescale_box(c, 1.5) == MD_OK && md_step(c, 3, 0) == MD_OK);
+        M.full = true;  // any allocation fails
+        for (double a : {1.0, 0.9, 1.01, 1.0 / 0.9 / 1.01}) {
+            CHECK(md_rescale_box(c, a) == MD_OK);
+            CHECK(md_step(c, 3, 0) == MD_OK);
+        }
+        M.full = false;
+        CHECK(md_rescale_box(c, 1.5) == MD_OK && md_step(c, 3, 0) == MD_OK);
+        md_destroy(c);
+    }
+    CHECK(M.size.empty());
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -358,6 +376,7 @@ int main(int argc, char** argv) {
     else if (what == "out_of_memory") out_of_memory();
     else if (what == "tile_arrays") tile_arrays();
     else if (what == "autotune_without_tiles") autotune_without_tiles();
+    else if (what == "rescale_in_place") rescale_in_place();
     else return std::fprintf(stderr, "unknown scenario\n"), 2;
     return g_fail ? 1 : 0;
 }
