@@ -507,7 +507,7 @@ void params_refresh(md_ctx* c) {
         if (hipGetDeviceProperties(&prop, c->device) == hipSuccess && prop.multiProcessorCount > 0)
             c->cus = prop.multiProcessorCount;
     }
-    if (P.tgrid <= 0) P.tgrid = std::max(8, c->cus * rowtile_blocks_per_cu(P));
+    if (P.tile && P.tgrid <= 0) P.tgrid = std::max(8, c->cus * rowtile_blocks_per_cu(P));
     P.fastrcp = (p.flags & MD_F_FAST_RCP) ? 1 : 0;
 }
 
@@ -1031,11 +1031,11 @@ md_status create_impl(const md_params* boxes, int32_t nbox, void* stream, md_ctx
     // steps, gathers / tiles (us): FP64 187,000 particles 48.1 / 48.5, 256,000 59.0 / 55.3, 442,000 98.3 /
     // 92.0, 1,049,000 187 / 161; FP32-mixed 39.3 / 39.7, 49.0 / 45.4, 79.7 / 74.1, 144 / 130.  So they are the
     // default for a largest box of kTileMinN particles or more (md_autotune measures instead), where
-    // its cells hold kTileMinCell to kTileMaxCell on average: with fewer the copies of a slice
-    // outweigh its pairs in the first builds of a run (2M particles at 2.2 to a cell, lists, forces and
-    // energies of new positions FP64 1467 / 1788, FP32-mixed 1273 / 1430, steps 262 / 243, 220 / 215), with
-    // more a slice and its neighbours come near the staging capacity, and past it every build is made
-    // twice.  Steps of 500,000 particles: FP32-mixed, 36 to a cell 166.6 / 130.7, 47 211 / 170, 63 257 / 192, 73
+    // its cells hold kTileMinCell to kTileMaxCell on average.  With fewer, what steps gain an evaluation
+    // of new positions loses (2M particles, evaluations and steps, gathers / tiles: 2.2 to a cell FP64
+    // 970 / 1080, 250 / 234, FP32-mixed 899 / 1003, 210 / 205; 3.6 to a cell 880 / 914, 271 / 223, 771 /
+    // 848, 207 / 192; 4.5 840 / 866, 264 / 210, 766 / 795, 209 / 178).  With more, a slice and its
+    // neighbours come near the staging capacity, past which the context builds again with gathers.  Steps of 500,000 particles: FP32-mixed, 36 to a cell 166.6 / 130.7, 47 211 / 170, 63 257 / 192, 73
     // 328 / 275; FP64 25 to a cell 156 / 141, 36 216 / 189, 47 275 / 266, but with one lane per key left
     // where a tile does overflow (63 to a cell 330, with one lane 398).
     int big = 0;

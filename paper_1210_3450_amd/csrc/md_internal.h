@@ -26,9 +26,9 @@
 //             lane reads 8 entries.  Entry = s << 11 | offset: s = stencil cell of
 //             the partner (z-major over offsets (ox, oy, oz) in {-1,0,1}^3, 0..26)
 //             and the partner's rank within that cell (cells hold at most 2048).
-//             Row-tile format (FP32-mixed, one lane per key): entry = 12 * the
-//             partner's index in its key's staged row tile (below): the LDS byte
-//             offset of its 12-byte record.
+//             Row-tile format (one lane per key): entry = 12 (FP32-mixed) or 24
+//             (FP64) * the partner's index in its key's staged row tile (below): the
+//             LDS byte offset of its record of as many bytes.
 //   cells     per box ncell counters and starts, box ranges aligned to 1024-cell tiles.
 //   row tiles rows of cells are taken kBy x kBz at a time ("beams": rows (cy, cz) with cy in
 //             [y0, y0 + by), cz in [z0, z0 + bz), fewer at the box's end), and a beam is cut
@@ -67,7 +67,6 @@ constexpr int kToldRing = 64;            // rebuild decisions in flight to the h
 constexpr int kNeedStripes = 256;        // slots per box for the longest list of a build
 constexpr int kNeedStride = 16;          // 64 bytes between slots
 constexpr int kTileWMax = 64;            // cells per row tile at most
-constexpr int kScapMax = 5461;           // staged records per row tile at most (16-bit entries of 12 * index)
 constexpr int kBy = 2, kBz = 1;          // rows of cells per beam
 constexpr int kBeamRows = kBy * kBz;
 constexpr int kTileRun = 512;            // consecutive tiles per XCD and turn, at most

@@ -2,12 +2,12 @@
 //
 // Per step (velocity Verlet, Sec. III.B; list validity by DUTC, Sec. II.A):
 //   force pass (kForceMid)  close step n (v += hF), open step n+1 (v += hF, q += dt v),
-//                           per-box max |v|^2 for the DUTC bound: k_force_t (FP32-mixed,
-//                           partners from a row tile staged in LDS) or k_force (gather
-//                           format: FP64, and FP32-mixed when tiles do not fit)
+//                           per-box max |v|^2 for the DUTC bound: k_force_t (FP32-mixed) and
+//                           k_force_t64 (FP64) with the partners of a row tile staged in LDS, or
+//                           k_force (gather format, either precision)
 //   k_dutc                  D += dt * max|v|; flag a rebuild when 2D > skin
 //   rebuild chain           (early exit unless flagged) wrap + cell id, counting sort
-//                           by cell, permute into coalesced arrays, row tiles, pair list
+//                           by cell, row tiles, permute into coalesced arrays, pair list
 // and at chunk ends the force pass in kForceEnd mode (closing half kick, F stored)
 // followed by k_kick_drift at the start of the next chunk.
 //
@@ -94,10 +94,6 @@ __device__ __forceinline__ double wave_sum(double v) {
 }
 __device__ __forceinline__ double wave_max(double v) {
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-    return v;
-}
-__device__ __forceinline__ int wave_max_i(int v) {
-    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
     return v;
 }
 __device__ __forceinline__ int wave_incl_scan(int v) {
@@ -203,10 +199,6 @@ struct __attribute__((packed, aligned(4))) U3 {
     int x, y, z;
 };
 __device__ __forceinline__ void put_u(int32_t* u, int s, int4 v) { *reinterpret_cast<U3*>(u + 3 * s) = U3{v.x, v.y, v.z}; }
-__device__ __forceinline__ int4 get_u(const int32_t* u, int s) {
-    const U3 t = *reinterpret_cast<const U3*>(u + 3 * s);
-    return make_int4(t.x, t.y, t.z, 0);
-}
 
 // ---------------------------------------------------------------- state I/O
 
@@ -864,12 +856,12 @@ __device__ __forceinline__ void tile_piece_img(const BoxGeom& g, int y0, int z0,
 
 // Cuts every beam into row tiles, greedily from x = 0: a tile grows by the
 // next slice of cells while its keys stay within kt, its staged region within scap records and
-// its width within kTileWMax cells.  One wavefront per row.  The column sums of the
-// 3 x 3 rows around it (cells x = -1 .. n, unwrapped) and the row's own counts go to
-// LDS as prefix sums; every lane then finds, for the cells x it holds, where a tile
-// starting at x would end (a binary search: both sums grow with the tile), and lane 0
-// follows those ends from x = 0, a handful of steps per row.  A one-cell tile whose
-// region exceeds scap sets error bit 2 of its box (the context then falls back to the
+// its width within kTileWMax cells.  One wavefront per beam.  The column sums of the
+// beam's rows and the rows around them (3 by kBy + 2 of them; cells x = -1 .. n, unwrapped)
+// and the beam's own counts go to LDS as prefix sums; every lane then finds, for the cells x
+// it holds, where a tile starting at x would end (a binary search: both sums grow with the
+// tile), and lane 0 follows those ends from x = 0, a handful of steps per beam.  A tile of one
+// cell per row whose region exceeds scap sets error bit 2 of its box (the context then falls back to the
 // gather format).
 __global__ __launch_bounds__(kBlock) void k_row_tiles(Dev d, Params p) {
     if (!ld_const(d.any) || halted(d)) return;  // no box rebuilds this step, or a build overflowed
@@ -1101,11 +1093,10 @@ __device__ __forceinline__ int nb_axis(int c, int o, int n, int& r) {
 // with |x_j|^2 held per candidate and (-2 x_i, t_i) read from lane i into scalar registers:
 // three FMAs, where differences and squares take six instructions, on half the registers of
 // FP64.  It decides only what it can: with R^2 the squared diagonal of a cell, |x_j|^2 is at
-// most 2.25 R^2 and |x_i| |x_j| 0.75 R^2, and the roundings of the coordinates (their products
-// 3 R^2, in units of 2^-24), of |x_j|^2 (6.75 R^2), of the three FMAs (11.25 R^2) and of t_i
-// (0.6 R^2) add up to less than 22 R^2 2^-24.  Candidates are compared with t_i - eps and
-// t_i + eps, eps = 32 R^2 2^-24 (4.5e-5 for cells of side 2.8; the FP32 thresholds' own
-// rounding fits in the difference); a key with a candidate between the two (one in 1300) is
+// most 2.25 R^2 and |x_i| |x_j| 0.75 R^2, and the roundings of the coordinates (in units of 2^-24,
+// in |x_j|^2 4.5 R^2, in the products 3 R^2), of the sum |x_j|^2 (6.75 R^2), of the three FMAs
+// (11.25 R^2) and of t_i (0.6 R^2) add up to less than 27 R^2 2^-24.  Candidates are compared with
+// t_i - eps and t_i + eps, eps = 32 R^2 2^-24 (4.5e-5 for cells of side 2.8); a key with a candidate between the two (one in 1300) is
 // done again by slow_key with the plain FP64 minimum-image definition, so every set is the
 // one that definition gives, bit for bit.  Units whose squared lengths leave FP32's range go
 // through slow_key alone (Params::exact).
@@ -1556,15 +1547,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(G == kTh
 }
 
 // ---------------------------------------------------------------- forces
-
-template <int PREC>
-struct ShiftT {
-    using V = double4;  // FP64: periodic image r * L subtracted from q_j - q_i
-};
-template <>
-struct ShiftT<MD_PREC_FP32_MIXED> {
-    using V = int4;  // FP32-mixed: stencil offset o * 2^28 added to u_j - u_i
-};
 
 // Compensated FP32 accumulation (Kahan): s + c tracks the running sum.
 __device__ __forceinline__ void kahan_add(float& s, float& c, float x) {
@@ -2209,7 +2191,7 @@ struct TileWalk {
 // 72.7, 16M 1408 / 1159 / 1095 / 1050, 2M with cutoff 3.0 326 / 292 / 258 / 248.  Against the third
 // figure, 2 x 2 rows: 16M 1209; 3 x 1: 1201; 512 threads and 2720 records: 1241; 1920 records: 1117.
 // Four wavefronts per SIMD also where the energies would take 138 registers: the
-// closing pass of 2M particles with all energies 306 -> 262 us, in spite of 10 spills.
+// closing pass of 2M particles with all energies 306 -> 262 us, in spite of 16 spills.
 template <int MODE, int ENERGY, bool CLAMP>
 __global__ __launch_bounds__(kRtBlock, 4) void k_force_t(Dev d, Params p) {
     if (step_off(d)) return;

@@ -159,7 +159,10 @@ void launch_rebuild_chain(const Dev& d, const Params& p, bool with_list, hipStre
     }
     *d.any = 0;
 }
-void launch_force(const Dev& d, const Params& p, int, int, hipStream_t) { need_arrays(d, p, "the force pass", true); }
+void launch_force(const Dev& d, const Params& p, int, int, hipStream_t) {
+    need_arrays(d, p, "the force pass", true);
+    if (p.tile) CHECK(p.tgrid >= 8);
+}
 void launch_kick_drift(const Dev&, const Params&, hipStream_t) {}
 void launch_dutc(const Dev& d, const Params& p, uint32_t seq, hipStream_t) {
     if (M.dutc++ == M.drop_dutc) {
