@@ -21,6 +21,8 @@ struct Model {
     int build_every = 4;           // drifts between list builds
     int need = 40;                 // longest list of a build
     bool tile_overflow = false;
+    double clock = 0.0;            // ms: builds without row tiles, cutting them, force passes with and without
+    double build = 1.5, cut = 0.5, force_tile = 0.9, force_gather = 1.0;
 } M;
 
 int g_fail = 0;
@@ -111,11 +113,13 @@ hipError_t hipGraphInstantiate(hipGraphExec_t*, hipGraph_t, hipGraphNode_t*, cha
 hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipErrorNotSupported; }
 hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
-hipError_t hipEventCreate(hipEvent_t* e) { return *e = nullptr, hipSuccess; }
-hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { return *e = reinterpret_cast<hipEvent_t>(new double(0.0)), hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { return delete reinterpret_cast<double*>(e), hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) { return *reinterpret_cast<double*>(e) = M.clock, hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 1.0f, hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {
+    return *ms = (float)(*reinterpret_cast<double*>(b) - *reinterpret_cast<double*>(a)), hipSuccess;
+}
 }
 
 // ---- the launchers
@@ -134,9 +138,15 @@ void launch_mark_rebuild(const Dev& d, const Params& p, hipStream_t) {
     *d.any = 1;
 }
 int rowtile_blocks_per_cu(const Params&) { return 4; }
-void launch_rebuild_chain(const Dev& d, const Params& p, bool with_list, hipStream_t) {
+void launch_row_tiles(const Dev& d, const Params& p, hipStream_t) {
+    need_arrays(d, p, "the tile cut", false);
+    if (*d.any && !*d.halt) M.clock += M.cut;
+}
+void launch_rebuild_chain(const Dev& d, const Params& p, bool with_list, hipStream_t s) {
     need_arrays(d, p, "the rebuild chain", with_list);
     if (!*d.any || *d.halt) return;
+    M.clock += M.build;
+    if (p.tile) launch_row_tiles(d, p, s);
     if (p.tile && M.tile_overflow) {
         d.st[0].err |= 4;
         *d.halt = 1;
@@ -162,6 +172,7 @@ void launch_rebuild_chain(const Dev& d, const Params& p, bool with_list, hipStre
 void launch_force(const Dev& d, const Params& p, int, int, hipStream_t) {
     need_arrays(d, p, "the force pass", true);
     if (p.tile) CHECK(p.tgrid >= 8);
+    if (!off(d)) M.clock += p.tile ? M.force_tile : M.force_gather + 0.1 * (p.tpk - 1);
 }
 void launch_kick_drift(const Dev&, const Params&, hipStream_t) {}
 void launch_dutc(const Dev& d, const Params& p, uint32_t seq, hipStream_t) {
@@ -370,6 +381,20 @@ void rescale_in_place() {
     }
     CHECK(M.size.empty());
 }
+
+// The autotuner where the force pass gains 0.1 ms from row tiles and cutting them costs 0.5: one box
+// cuts them with each of its builds, an ensemble whenever any box builds.
+void autotune_ensemble() {
+    M.build_every = 10;
+    for (int nbox : {1, 2, 64}) {
+        md_ctx* c = open(params(), nbox);
+        CHECK(md_step(c, 40, 0) == MD_OK);  // a build every 10 steps
+        CHECK(md_autotune(c, nullptr) == MD_OK);
+        CHECK(c->P.tile == (nbox == 1) && c->P.tpk == 1);
+        CHECK(md_step(c, 20, 0) == MD_OK && steps(c) == 60);
+        md_destroy(c);
+    }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -380,6 +405,7 @@ int main(int argc, char** argv) {
     else if (what == "tile_arrays") tile_arrays();
     else if (what == "autotune_without_tiles") autotune_without_tiles();
     else if (what == "rescale_in_place") rescale_in_place();
+    else if (what == "autotune_ensemble") autotune_ensemble();
     else return std::fprintf(stderr, "unknown scenario\n"), 2;
     return g_fail ? 1 : 0;
 }
