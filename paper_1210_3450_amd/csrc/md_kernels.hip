@@ -2188,7 +2188,8 @@ struct TileWalk {
 // two rows high stage 12 rows for the keys of two, where single rows staged 9 for one: a third
 // fewer records per key, and tiles long enough to fill 256 lanes.  Mid-step pass (us), gathers /
 // single rows / two rows / with the records read ahead and TileWalk: 1M particles 98 / 97.5 / 80.6 /
-// 72.7, 16M 1408 / 1159 / 1095 / 1050, 2M with cutoff 3.0 326 / 292 / 258 / 248.  Against the third
+// 72.7, 16M 1408 / 1159 / 1095 / 1050, 2M with cutoff 3.0 326 / 292 / 258 / 248, and 224 with 3072
+// records instead of 2048 (the others' tiles are full of keys before).  Against the third
 // figure, 2 x 2 rows: 16M 1209; 3 x 1: 1201; 512 threads and 2720 records: 1241; 1920 records: 1117.
 // Four wavefronts per SIMD also where the energies would take 138 registers: the
 // closing pass of 2M particles with all energies 306 -> 262 us, in spite of 16 spills.
