@@ -479,9 +479,15 @@ void params_refresh(md_ctx* c) {
     // leaves lanes without keys.  Steps of 500,000 particles at density 0.84 (us), FP32-mixed 2048 / 3072
     // records: 25 to a cell 104.6 / 102.4, 32 127.9 / 114.7, 47 196.5 / 170.0 (4096 and three blocks: 175.5),
     // 63 does not fit / 191.8; FP64 2048 / 2720: 25 to a cell 140.9 / 159.8, 32 182 / 168, 47 326 / 266.
-    double dense = 0.0;
-    for (const BoxGeom& g : c->geom) dense = std::max(dense, (double)g.npart / g.ncell);
-    const int32_t scap = p.precision != MD_PREC_FP64 ? kStageCap32 : (dense > 30.0 ? kStageDense64 : kStageCap64);
+    // In an ensemble most particles decide, unless a box would not fit the smaller capacity.
+    double densest = 0.0, mean = 0.0;  // particles to a cell, the mean over particles
+    for (const BoxGeom& g : c->geom) {
+        const double d = (double)g.npart / g.ncell;
+        densest = std::max(densest, d);
+        mean += d * g.npart / (double)c->ntotal;
+    }
+    const bool crowded = mean > 30.0 || densest > 45.0;
+    const int32_t scap = p.precision != MD_PREC_FP64 ? kStageCap32 : (crowded ? kStageDense64 : kStageCap64);
     if (scap != P.scap) P.tgrid = 0;  // another number of resident blocks
     P.scap = scap;
     P.nrows = c->nrows;

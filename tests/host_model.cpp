@@ -395,6 +395,32 @@ void autotune_ensemble() {
         md_destroy(c);
     }
 }
+
+// Staged records of FP64 row tiles: the larger capacity where most particles live in crowded cells or
+// a box needs it, the smaller elsewhere; rescaling moves a context over the line and back.
+void tile_capacity() {
+    auto box = [](int64_t n) {
+        md_params p = params(MD_F_TILE_ON);
+        p.n = n;  // of 7^3 cells
+        return p;
+    };
+    const struct {
+        std::vector<int64_t> n;
+        int scap;
+    } cases[] = {{{8000}, kStageCap64}, {{11000}, kStageDense64}, {{8000, 8000, 11000}, kStageCap64},
+                 {{8000, 8000, 16500}, kStageDense64}, {{4000, 12000, 12000}, kStageDense64}};
+    for (const auto& k : cases) {
+        std::vector<md_params> b;
+        for (int64_t n : k.n) b.push_back(box(n));
+        md_ctx* c = nullptr;
+        CHECK(md_batch_create(b.data(), (int32_t)b.size(), nullptr, &c) == MD_OK);
+        CHECK(c->P.scap == k.scap && c->P.tgrid >= 8);
+        const double x = 0.0;
+        CHECK(md_set_state(c, &x, &x) == MD_OK && md_rescale_box(c, 2.0) == MD_OK && c->P.scap == kStageCap64);
+        CHECK(md_rescale_box(c, 0.5) == MD_OK && c->P.scap == k.scap);
+        md_destroy(c);
+    }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -406,6 +432,7 @@ int main(int argc, char** argv) {
     else if (what == "autotune_without_tiles") autotune_without_tiles();
     else if (what == "rescale_in_place") rescale_in_place();
     else if (what == "autotune_ensemble") autotune_ensemble();
+    else if (what == "tile_capacity") tile_capacity();
     else return std::fprintf(stderr, "unknown scenario\n"), 2;
     return g_fail ? 1 : 0;
 }

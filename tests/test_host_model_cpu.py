@@ -21,7 +21,7 @@ def host_model(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["plain", "lost_decision", "out_of_memory", "tile_arrays",
-                                      "autotune_without_tiles", "rescale_in_place", "autotune_ensemble"])
+                                      "autotune_without_tiles", "rescale_in_place", "autotune_ensemble", "tile_capacity"])
 def test_host_model(host_model, scenario, tmp_path):
     r = subprocess.run([host_model, scenario], capture_output=True, text=True, timeout=120, cwd=tmp_path)
     assert r.returncode == 0, (r.returncode, r.stderr[-4000:])
